@@ -15,7 +15,7 @@ LIB_DIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(LIB_DIR, "liblre.so")
 SOURCES = [os.path.join(PKG, "csrc", f)
            for f in ("lre_abi.hip", "lre_batch.hip", "lre_project.hip", "lre_membench.hip")]
-DEPS = SOURCES + [os.path.join(PKG, "csrc", f) for f in ("lre_kernels.hpp", "lre_internal.hpp")] + [
+DEPS = SOURCES + [os.path.join(PKG, "csrc", f) for f in ("lre_kernels.hpp", "lre_tile.hpp", "lre_povm.hpp", "lre_internal.hpp")] + [
     os.path.join(ROOT, "include", "lre.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -13,6 +13,7 @@
 #include "lre_internal.hpp"
 #include "lre_kernels.hpp"
 #include "lre_povm.hpp"
+#include "lre_tile.hpp"
 
 using namespace lre;
 using lre_detail::aligned;
@@ -28,11 +29,9 @@ static __device__ __align__(256) char scratch[LRE_NOALLOC_SCRATCH_BYTES];
 
 namespace {
 
-constexpr int kMaxQ1 = 7;     // qubits folded by the counts pass
-constexpr int kMaxF = 3;      // qubits folded by a later pass in registers
-constexpr int kMaxFLast = 2;  // qubits folded by the final pass (below kMinHF4)
-constexpr int kMinHF4 = 5;    // from this many unfolded qubits on, the first later pass
-                              // folds 4 with LDS accumulators and the final one the rest
+constexpr int kMaxQ1 = 7;     // qubits folded by the int8-MFMA counts pass and lre_signed_sums
+constexpr int kSmallN = 5;    // up to this many qubits one workgroup does everything
+constexpr int kMaxTail = 4;   // qubits folded by the pass that ends a plan (fold_tail_kernel)
 constexpr int kRhoJ = 6;      // qubits of the low step-(ii) transform
 // Step (ii) goes through a complex128 intermediate of 4^n entries only beyond 12 qubits
 // (up to 10 the LDS tiles, at 11 and 12 the real-arithmetic tiles need none).
@@ -46,15 +45,18 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 struct Plan {
   int n = 0;
   bool per_basis = false;
-  int q1 = 0;
-  int chunks = 1;            // tiles per counts-pass block
+  bool mfma = false;         // counts pass on int8 MFMA
+  int q1 = 0;                // qubits folded by the counts pass
+  int chunks = 1;            // MFMA form: tiles per counts-pass block, one row group's
+  int64_t runs = 1;          // tiles (MFMA form: blocks) along a row
+  int64_t per_block = 0;     // tiles per counts-pass block (0: one, or the MFMA form)
   int64_t blocks1 = 0;       // counts-pass blocks
+  int64_t parts = 0;         // row-sum parts, of 3^q1 words
   Ty t1 = Ty::U32;           // counts-pass accumulator / output type
   int npass = 0;             // later passes
-  int F[8] = {0};
-  Ty tout[8] = {Ty::U32};
-  int J = 0;                 // low step-(ii) qubits
-  size_t off_a = 0, off_b = 0, off_rowpart = 0, off_nb = 0, off_inv = 0, off_tmp = 0, total = 0;
+  int F[4] = {0};
+  Ty tout[4] = {Ty::U32};
+  size_t off_a = 0, off_b = 0, off_rowpart = 0, off_nb = 0, off_tmp = 0, total = 0;
 };
 
 // Partial sums after folding f qubits are bounded by 3^f * (basis total).
@@ -64,38 +66,62 @@ Ty int_type_for(int folded, uint64_t shots) {
   return bound <= (long double)INT32_MAX ? Ty::U32 : Ty::F64;
 }
 
-bool make_plan(int n, uint64_t shots, uint32_t flags, Plan& P) {
-  if (n < 1 || n > LRE_MAX_QUBITS) return false;
+// Qubits the counts pass folds (n > kSmallN): enough that the passes after it stay short,
+// as long as its workgroups fill the chip.
+int counts_qubits(int n, bool mfma) {
+  if (mfma) return kMaxQ1;
+  return n <= 8 ? 5 : (n == 9 ? 6 : 7);
+}
+
+bool make_plan_form(int n, uint64_t shots, uint32_t flags, bool mfma, Plan& P) {
   P = Plan();
   P.n = n;
   P.per_basis = shots == 0;
-  P.q1 = n < kMaxQ1 ? n : kMaxQ1;
-  const int64_t tiles_per_row = (int64_t)1 << (n - P.q1);
+  P.mfma = mfma;
+  const size_t tmp = (!(flags & LRE_NO_RHO) && rho_needs_tmp(n)) ? (size_t)ipow4(n) * 16 : 0;
+  if (n <= kSmallN) {
+    P.total = 256;
+    return true;
+  }
+  P.q1 = counts_qubits(n, mfma);
   const int64_t row_groups = ipow3(n - P.q1);
-  int64_t chunks = 1;
-  while (chunks * 2 <= tiles_per_row && chunks < 16 &&
-         row_groups * (tiles_per_row / (chunks * 2)) >= 1024)
-    chunks *= 2;
-  P.chunks = (int)chunks;
-  P.blocks1 = row_groups * (tiles_per_row / chunks);
+  if (mfma) {
+    const int64_t tiles_per_row = (int64_t)1 << (n - kMaxQ1);
+    int64_t chunks = 1;
+    while (chunks * 2 <= tiles_per_row && chunks < 16 &&
+           row_groups * (tiles_per_row / (chunks * 2)) >= 1024)
+      chunks *= 2;
+    P.chunks = (int)chunks;
+    P.runs = tiles_per_row / chunks;
+    P.blocks1 = P.parts = row_groups * P.runs;
+  } else {
+    // outcomes of a tile: 2^q1, or the 64 of a sub-tile where a tile folds fewer than 6 bits
+    P.runs = (int64_t)1 << (n - (P.q1 < 6 ? 6 : P.q1));
+    const int64_t tiles = row_groups * P.runs;
+    P.blocks1 = P.parts = tiles;
+    if (P.q1 > 5) {
+      // Blocks of equal numbers of tiles: one per workgroup the chip holds, or, where there
+      // are many tiles each, four, so that the workgroups' unequal speeds even out.
+      const int64_t slots = P.per_basis ? 256 : 512;
+      const int64_t want = tiles >= 32 * slots ? 4 * slots : slots;
+      P.per_block = (tiles + want - 1) / want;
+      P.blocks1 = (tiles + P.per_block - 1) / P.per_block;
+      P.parts = row_groups + P.blocks1;
+    }
+  }
   P.t1 = P.per_basis ? Ty::F64 : int_type_for(P.q1, shots);
 
-  // Later passes: the last folds at most kMaxFLast qubits (it also divides every
-  // output, which costs registers); the others split the rest evenly, <= kMaxF each.
+  // Later passes: up to 4 remaining qubits in one pass; more (n >= 12) as 4 with LDS
+  // accumulators, then the remaining 1..3 in registers, which reads and writes far less
+  // than 3 + 2 + 2 (53 GB instead of 70 GB of partials at n = 14).
   const int h = n - P.q1;
-  if (h >= kMinHF4 && h <= 4 + kMaxF) {
-    // Two passes: 4 qubits (LDS) then the remaining 1..3 in registers, which reads and
-    // writes far less than 3 + 2 + 2 (53 GB instead of 70 GB of partials at n = 14).
+  if (h > kMaxTail) {
     P.npass = 2;
     P.F[0] = 4;
     P.F[1] = h - 4;
-  } else {
-    const int last = h < kMaxFLast ? h : kMaxFLast;
-    const int rest = h - last;
-    const int nrest = (rest + kMaxF - 1) / kMaxF;
-    P.npass = nrest + (last > 0 ? 1 : 0);
-    for (int k = 0; k < nrest; ++k) P.F[k] = rest / nrest + (k < rest % nrest ? 1 : 0);
-    if (last > 0) P.F[nrest] = last;
+  } else if (h > 0) {
+    P.npass = 1;
+    P.F[0] = h;
   }
   int folded = P.q1;
   Ty prev = P.t1;
@@ -107,34 +133,33 @@ bool make_plan(int n, uint64_t shots, uint32_t flags, Plan& P) {
     prev = t;
   }
 
-  // Workspace: ping-pong partial buffers A (counts pass, odd later passes) and B.
-  size_t sizeA = 0, sizeB = 0;
-  {
-    int hh = n - P.q1, ll = P.q1;
-    if (P.npass > 0) sizeA = (size_t)(ipow3(hh) << hh) * (size_t)ipow4(ll) * ty_size(P.t1);
-    for (int k = 0; k + 1 < P.npass; ++k) {  // outputs of all but the last later pass
-      hh -= P.F[k];
-      ll += P.F[k];
-      size_t sz = (size_t)(ipow3(hh) << hh) * (size_t)ipow4(ll) * ty_size(P.tout[k]);
-      if (k % 2 == 0) sizeB = sizeB > sz ? sizeB : sz;
-      else sizeA = sizeA > sz ? sizeA : sz;
-    }
-  }
-  const size_t rowpart = (size_t)P.blocks1 * (size_t)ipow3(P.q1) * 4;
-  const size_t nbytes = P.per_basis ? (size_t)ipow3(n) * 4 : 0;
-  P.J = n < kRhoJ ? n : kRhoJ;
-  const size_t tmp = (!(flags & LRE_NO_RHO) && rho_needs_tmp(n)) ? (size_t)ipow4(n) * 16 : 0;
+  // Workspace: partial buffers A (counts pass) and B (first of two later passes).
+  const size_t sizeA = P.npass > 0 ? (size_t)(ipow3(h) << h) * (size_t)ipow4(P.q1) * ty_size(P.t1) : 0;
+  const int h2 = h - P.F[0];
+  const size_t sizeB =
+      P.npass > 1 ? (size_t)(ipow3(h2) << h2) * (size_t)ipow4(n - h2) * ty_size(P.tout[0]) : 0;
+  const size_t rowpart = (size_t)P.parts * (size_t)ipow3(P.q1) * 4;
 
   size_t off = 0;
   P.off_a = off; off += align256(sizeA);
   P.off_b = off; off += align256(sizeB);
   P.off_rowpart = off; off += align256(rowpart);
-  P.off_nb = off; off += align256(nbytes);
-  P.off_inv = off; off += align256(P.per_basis ? (size_t)ipow3(n) * 8 : 0);
+  P.off_nb = off; off += align256(P.per_basis ? (size_t)ipow3(n) * 4 : 0);
   if (tmp && tmp <= sizeA) P.off_tmp = P.off_a;        // partials are dead by then
   else if (tmp && tmp <= sizeB) P.off_tmp = P.off_b;
   else { P.off_tmp = off; off += align256(tmp); }
   P.total = off;
+  return true;
+}
+
+bool make_plan(int n, uint64_t shots, uint32_t flags, Plan& P) {
+  if (n < 1 || n > LRE_MAX_QUBITS) return false;
+  // A workspace serves both forms of the counts pass, whichever it was sized for.
+  Plan other;
+  const bool mfma = (flags & LRE_WHT_MFMA) && n >= kMaxQ1;
+  if (n >= kMaxQ1) make_plan_form(n, shots, flags, !mfma, other);
+  make_plan_form(n, shots, flags, mfma, P);
+  P.total = std::max(P.total, other.total);
   return true;
 }
 
@@ -155,92 +180,45 @@ int64_t resident_blocks(K kernel, int threads, int64_t lds_bytes) {
 
 // ---- launch helpers -------------------------------------------------------------
 
+// A counts pass: nseg segments (blockIdx.y), counts advancing by seg_counts per segment,
+// out by seg_out elements and rowpart by seg_row words.
 struct Fold1Args {
   const uint16_t* counts;
   int n, chunks;
   int lrow;             // log2 of the row stride of counts (n for a whole instance)
-  const uint32_t* nb;   // per-basis totals (MFMA kernel)
-  const double* inv;    // their reciprocals (streaming kernel)
+  const uint32_t* nb;   // per-basis totals
   void* out;
   uint32_t* rowpart;
   uint64_t shots;
-  int64_t blocks;
+  int64_t tiles, per_block, blocks;
+  int nseg;
+  int64_t seg_counts, seg_out, seg_row;
   hipStream_t st;
 };
 
-// Counts-pass block: one row group per tile row-set, i.e. NRS * LPC threads (3^Q rows
-// of 2^Q outcomes); for Q = 7 (81 row-sets of 16 lanes) 432 threads, 27 groups of three
-// row-sets each.  (512 threads with uneven step ranges is slower: the groups of a wave
-// then flush their row-set sums at different steps and the wave runs both paths.)
-template <int Q>
-constexpr int fold1_threads() {
-  constexpr int t = StreamGeom<Q>::NRS * StreamGeom<Q>::LPC;
-  return t > 1024 ? t / 3 : (t < 64 ? 64 : t);
+template <int LV, bool PB, typename Acc>
+void launch_tile(const Fold1Args& a) {
+  const dim3 grid((unsigned)a.blocks, (unsigned)a.nseg);
+  if constexpr (LV == 0)
+    hipLaunchKernelGGL((counts_subtile_kernel<PB, Acc>), grid, dim3(256), 0, a.st, a.counts, a.n, a.lrow, a.nb,
+                       static_cast<Acc*>(a.out), a.rowpart, a.seg_counts, a.seg_out, a.seg_row);
+  else
+    hipLaunchKernelGGL((counts_tile_kernel<LV, PB, Acc>), grid, dim3(512), 0, a.st, a.counts, a.n, a.lrow, a.tiles,
+                       a.per_block, a.nb, static_cast<Acc*>(a.out), a.rowpart, a.seg_counts, a.seg_out, a.seg_row);
 }
 
-// Double-buffered row prefetch with one block per CU (256 registers per lane): faster
-// than two blocks per CU without it for 32-bit tiles too (1.04 vs 1.17 ms at n = 12).
-template <int Q, typename Acc>
-constexpr bool fold1_prefetch() {
-  return true;
+template <int LV>
+void tile_lv(Ty t, bool pb, const Fold1Args& a) {
+  if (pb) launch_tile<LV, true, double>(a);
+  else if (t == Ty::U32) launch_tile<LV, false, uint32_t>(a);
+  else launch_tile<LV, false, double>(a);
 }
 
-// Waves per SIMD the compiler must leave room for: two blocks per CU when two
-// accumulator tiles fit in LDS and the kernel runs without the prefetch, else no
-// constraint.
-template <int Q, typename Acc>
-constexpr int fold1_minwaves() {
-  constexpr int waves = (fold1_threads<Q>() + 63) / 64;
-  constexpr long lds = (long)StreamGeom<Q>::NACC * (long)sizeof(Acc) + 4L * StreamGeom<Q>::NROWS;
-  return (Q == 7 && !fold1_prefetch<Q, Acc>() && 2 * lds <= 160L * 1024) ? (2 * waves + 3) / 4 : 1;
-}
-
-template <int Q, typename Acc, bool PB, Out M, bool MAD24>
-void launch_fold1(const Fold1Args& a) {
-  constexpr int TH = fold1_threads<Q>();
-  static_assert(TH <= 1024 && (TH % StreamGeom<Q>::LPC) == 0, "counts-pass block shape");
-  hipLaunchKernelGGL((fold_counts_stream_kernel<Q, TH, Acc, PB, M, MAD24, fold1_minwaves<Q, Acc>(),
-                                               fold1_prefetch<Q, Acc>()>),
-                     dim3((unsigned)a.blocks), dim3(TH), 0,
-                     a.st, a.counts, a.n, a.chunks, a.inv, a.out, a.rowpart, a.shots, a.lrow);
-}
-
-// The lane butterflies of 32-bit sums use a 24-bit multiply-add when every value they
-// see is below 2^23 in magnitude: values are bounded by the counts of the 3^3 rows a
-// lane group walks, i.e. by 27 * shots for valid data (rows that exceed `shots` are
-// flagged by the row check, so wrong values then never reach the caller as a result).
-bool fold1_mad24(uint64_t shots) { return shots > 0 && 27ull * shots < (1ull << 23); }
-
-template <int Q>
-bool fold1_q(Ty t, bool pb, Out m, const Fold1Args& a) {
-  if (pb) {
-    if (m == Out::Partial) launch_fold1<Q, double, true, Out::Partial, false>(a);
-    else if (m == Out::CoefPerBasis) launch_fold1<Q, double, true, Out::CoefPerBasis, false>(a);
-    else return false;
-    return true;
-  }
-  if (t == Ty::U32) {
-    const bool m24 = fold1_mad24(a.shots);
-    switch (m) {
-      case Out::Partial:
-        m24 ? launch_fold1<Q, uint32_t, false, Out::Partial, true>(a)
-            : launch_fold1<Q, uint32_t, false, Out::Partial, false>(a);
-        return true;
-      case Out::CoefUniform:
-        m24 ? launch_fold1<Q, uint32_t, false, Out::CoefUniform, true>(a)
-            : launch_fold1<Q, uint32_t, false, Out::CoefUniform, false>(a);
-        return true;
-      case Out::PauliT:
-        m24 ? launch_fold1<Q, uint32_t, false, Out::PauliT, true>(a)
-            : launch_fold1<Q, uint32_t, false, Out::PauliT, false>(a);
-        return true;
-      default: return false;
-    }
-  }
-  switch (m) {
-    case Out::Partial: launch_fold1<Q, double, false, Out::Partial, false>(a); return true;
-    case Out::CoefUniform: launch_fold1<Q, double, false, Out::CoefUniform, false>(a); return true;
-    case Out::PauliT: launch_fold1<Q, double, false, Out::PauliT, false>(a); return true;
+bool fold1(int q, Ty t, bool pb, const Fold1Args& a) {
+  switch (q) {
+    case 5: tile_lv<0>(t, pb, a); return true;
+    case 6: tile_lv<1>(t, pb, a); return true;
+    case 7: tile_lv<2>(t, pb, a); return true;
     default: return false;
   }
 }
@@ -275,82 +253,114 @@ bool fold1_mfma(Ty t, bool pb, Out m, const Fold1Args& a) {
   }
 }
 
-bool fold1(int q, Ty t, bool pb, Out m, const Fold1Args& a) {
-  switch (q) {
-    case 1: return fold1_q<1>(t, pb, m, a);
-    case 2: return fold1_q<2>(t, pb, m, a);
-    case 3: return fold1_q<3>(t, pb, m, a);
-    case 4: return fold1_q<4>(t, pb, m, a);
-    case 5: return fold1_q<5>(t, pb, m, a);
-    case 6: return fold1_q<6>(t, pb, m, a);
-    case 7: return fold1_q<7>(t, pb, m, a);
-    default: return false;
-  }
-}
-
-struct FoldKArgs {
+// A later pass folding F qubits of [3^h][2^h][4^l], nseg segments (blockIdx.y); chk: row
+// totals to check in the same launch (nbases 0: none).
+struct FoldArgs {
   const void* in;
   void* out;
   int n, h, l;
   uint64_t shots;
-  int64_t ncols;
+  int nseg;
+  int64_t seg_in, seg_out;
+  RowCheck chk;
   hipStream_t st;
 };
 
 template <int F, typename Tin, typename Acc, Out M>
-void launch_foldk(const FoldKArgs& a) {
-  const int64_t blocks = (a.ncols + 255) / 256;
-  hipLaunchKernelGGL((fold_partial_kernel<F, Tin, Acc, M>), dim3((unsigned)blocks), dim3(256), 0, a.st,
-                     static_cast<const Tin*>(a.in), a.out, a.n, a.h, a.l, a.shots, a.ncols);
+void launch_tail(const FoldArgs& a) {
+  using G = FoldTailGeom<F>;
+  const int64_t blocks = (ipow3(a.h - F) << (a.h - F)) * (ipow4(a.l) / G::COLS);
+  const int64_t checks = (a.chk.nbases + G::THREADS - 1) / G::THREADS;
+  hipLaunchKernelGGL((fold_tail_kernel<F, Tin, Acc, M>), dim3((unsigned)(blocks + checks), (unsigned)a.nseg),
+                     dim3(G::THREADS), 0, a.st, static_cast<const Tin*>(a.in), a.out, a.n, a.h, a.l, a.shots, blocks,
+                     a.seg_in, a.seg_out, a.chk);
+}
+
+template <int F, typename Tin, typename Acc>
+void tail_m(Out m, const FoldArgs& a) {
+  switch (m) {
+    case Out::Partial: launch_tail<F, Tin, Acc, Out::Partial>(a); break;
+    case Out::CoefUniform: launch_tail<F, Tin, Acc, Out::CoefUniform>(a); break;
+    case Out::CoefPerBasis: launch_tail<F, Tin, Acc, Out::CoefPerBasis>(a); break;
+    case Out::PauliT: launch_tail<F, Tin, Acc, Out::PauliT>(a); break;
+  }
+}
+
+template <int F>
+bool tail_f(Ty tin, Ty tacc, Out m, const FoldArgs& a) {
+  if (tin == Ty::U32 && tacc == Ty::U32) tail_m<F, uint32_t, uint32_t>(m, a);
+  else if (tin == Ty::U32) tail_m<F, uint32_t, double>(m, a);
+  else if (tacc == Ty::F64) tail_m<F, double, double>(m, a);
+  else return false;
+  return true;
+}
+
+// Element i of an output of mode M.
+template <typename Acc, Out M>
+void* elem_at(void* out, int64_t i) {
+  if constexpr (M == Out::Partial) return static_cast<Acc*>(out) + i;
+  else return static_cast<double*>(out) + i;     // coefficients and T: 8 bytes
+}
+
+template <int F, typename Tin, typename Acc, Out M>
+void launch_foldk(const FoldArgs& a) {
+  const int64_t ncols = (ipow3(a.h - F) << (a.h - F)) * ipow4(a.l);
+  for (int s = 0; s < a.nseg; ++s)
+    hipLaunchKernelGGL((fold_partial_kernel<F, Tin, Acc, M>), dim3((unsigned)((ncols + 255) / 256)), dim3(256), 0, a.st,
+                       static_cast<const Tin*>(a.in) + s * a.seg_in, elem_at<Acc, M>(a.out, s * a.seg_out), a.n, a.h,
+                       a.l, a.shots, ncols);
 }
 
 template <typename Tin, typename Acc>
-void launch_fold4(const FoldKArgs& a) {
+void launch_fold4(const FoldArgs& a) {
   // Persistent blocks: as many as the device holds at once, each walking
   // groups with a stride of the grid.
   const int64_t groups = (ipow3(a.h - 4) << (a.h - 4)) * (((int64_t)1 << (2 * a.l)) / kF4Cols);
   const int64_t cap = resident_blocks(fold_partial4_kernel<Tin, Acc>, 64 * kF4Waves,
                                       (int64_t)256 * kF4Cols * (int64_t)sizeof(Acc));
   const int64_t blocks = groups < cap ? groups : cap;
-  hipLaunchKernelGGL((fold_partial4_kernel<Tin, Acc>), dim3((unsigned)blocks), dim3(64 * kF4Waves), 0, a.st,
-                     static_cast<const Tin*>(a.in), static_cast<Acc*>(a.out), a.h, a.l);
+  for (int s = 0; s < a.nseg; ++s)
+    hipLaunchKernelGGL((fold_partial4_kernel<Tin, Acc>), dim3((unsigned)blocks), dim3(64 * kF4Waves), 0, a.st,
+                       static_cast<const Tin*>(a.in) + s * a.seg_in, static_cast<Acc*>(a.out) + s * a.seg_out, a.h,
+                       a.l);
 }
 
-template <int F, typename Tin, typename Acc>
-bool foldk_m(Out m, const FoldKArgs& a) {
-  if constexpr (F == 4) {         // LDS pass, partials only
-    if (m != Out::Partial || a.h < 4 || a.l < 3) return false;
+// The two passes of a plan with more than kMaxTail qubits left: large instances, a launch
+// per segment.
+template <typename Tin, typename Acc>
+bool two_pass_t(int F, bool last, Out m, const FoldArgs& a) {
+  if (!last) {
     launch_fold4<Tin, Acc>(a);
-    return true;
-  } else if constexpr (F > kMaxF) {  // only the final pass writes coefficients
-    if (m != Out::Partial) return false;
-    launch_foldk<F, Tin, Acc, Out::Partial>(a);
-    return true;
-  } else {
-    switch (m) {
-      case Out::Partial: launch_foldk<F, Tin, Acc, Out::Partial>(a); return true;
-      case Out::CoefUniform: launch_foldk<F, Tin, Acc, Out::CoefUniform>(a); return true;
-      case Out::CoefPerBasis: launch_foldk<F, Tin, Acc, Out::CoefPerBasis>(a); return true;
-      case Out::PauliT: launch_foldk<F, Tin, Acc, Out::PauliT>(a); return true;
-    }
+    return F == 4;
   }
-  return false;
+  auto run = [&](auto fc) {
+    constexpr int FF = decltype(fc)::value;
+    switch (m) {
+      case Out::Partial: launch_foldk<FF, Tin, Acc, Out::Partial>(a); break;
+      case Out::CoefUniform: launch_foldk<FF, Tin, Acc, Out::CoefUniform>(a); break;
+      case Out::CoefPerBasis: launch_foldk<FF, Tin, Acc, Out::CoefPerBasis>(a); break;
+      case Out::PauliT: launch_foldk<FF, Tin, Acc, Out::PauliT>(a); break;
+    }
+  };
+  if (F == 1) run(std::integral_constant<int, 1>{});
+  else if (F == 2) run(std::integral_constant<int, 2>{});
+  else if (F == 3) run(std::integral_constant<int, 3>{});
+  else return false;
+  return true;
 }
 
-template <int F>
-bool foldk_f(Ty tin, Ty tacc, Out m, const FoldKArgs& a) {
-  if (tin == Ty::U32 && tacc == Ty::U32) return foldk_m<F, uint32_t, uint32_t>(m, a);
-  if (tin == Ty::U32 && tacc == Ty::F64) return foldk_m<F, uint32_t, double>(m, a);
-  if (tin == Ty::F64 && tacc == Ty::F64) return foldk_m<F, double, double>(m, a);
-  return false;
+bool two_pass(int F, bool last, Ty tin, Ty tacc, Out m, const FoldArgs& a) {
+  if (tin == Ty::U32 && tacc == Ty::U32) return two_pass_t<uint32_t, uint32_t>(F, last, m, a);
+  if (tin == Ty::U32) return two_pass_t<uint32_t, double>(F, last, m, a);
+  return tacc == Ty::F64 && two_pass_t<double, double>(F, last, m, a);
 }
 
-bool foldk(int F, Ty tin, Ty tacc, Out m, const FoldKArgs& a) {
+bool fold_tail(int F, Ty tin, Ty tacc, Out m, const FoldArgs& a) {
   switch (F) {
-    case 1: return foldk_f<1>(tin, tacc, m, a);
-    case 2: return foldk_f<2>(tin, tacc, m, a);
-    case 3: return foldk_f<3>(tin, tacc, m, a);
-    case 4: return foldk_f<4>(tin, tacc, m, a);
+    case 1: return tail_f<1>(tin, tacc, m, a);
+    case 2: return tail_f<2>(tin, tacc, m, a);
+    case 3: return tail_f<3>(tin, tacc, m, a);
+    case 4: return tail_f<4>(tin, tacc, m, a);
     default: return false;
   }
 }
@@ -415,79 +425,150 @@ void launch_rho(const Plan& P, const double* coef, void* rho, char* ws, hipStrea
 }
 
 
-// Per-basis totals N_b of `nbases` rows of 2^lrow counts: the caller's nb_in, else the
-// row sums into nb_ws; their reciprocals into inv.  Returns the totals to use.
-const uint32_t* prepare_totals(int64_t nbases, int lrow, const uint16_t* counts, const uint32_t* nb_in,
-                               uint32_t* nb_ws, double* inv, hipStream_t st) {
-  const uint32_t* nb = nb_in;
-  if (!nb) {
-    hipLaunchKernelGGL(row_totals_kernel, dim3((unsigned)nbases), dim3(256), 0, st, counts, lrow, nb_ws);
-    nb = nb_ws;
+// Row sums of `nbases` rows of 2^lrow counts (lrow >= 6) into nb.
+void launch_row_sums(int64_t nbases, int lrow, const uint16_t* counts, uint32_t* nb, hipStream_t st) {
+  const int lr = std::min(6, lrow - 3);
+  const int64_t per_block = (256 >> lr) * 4;
+  const dim3 grid((unsigned)((nbases + per_block - 1) / per_block));
+  switch (lr) {
+    case 3: hipLaunchKernelGGL((row_sums_kernel<3, 4>), grid, dim3(256), 0, st, counts, lrow, nbases, nb); break;
+    case 4: hipLaunchKernelGGL((row_sums_kernel<4, 4>), grid, dim3(256), 0, st, counts, lrow, nbases, nb); break;
+    case 5: hipLaunchKernelGGL((row_sums_kernel<5, 4>), grid, dim3(256), 0, st, counts, lrow, nbases, nb); break;
+    default: hipLaunchKernelGGL((row_sums_kernel<6, 4>), grid, dim3(256), 0, st, counts, lrow, nbases, nb); break;
   }
-  hipLaunchKernelGGL(reciprocal_kernel, dim3((unsigned)((nbases + 255) / 256)), dim3(256), 0, st, nb, inv, nbases);
-  return nb;
 }
 
-// The passes of step (i) over 3^n rows of 2^n counts read with row stride 2^lrow: the
-// counts pass (row-sum parts into rowpart) and the later passes, into `final_out` with
-// final mode `fm`.  Per-basis mode reads nb (MFMA form) or inv (plain form).
-lre_status run_passes(lre_ctx* ctx, const Plan& P, const uint16_t* counts, int lrow, uint64_t shots,
-                      const uint32_t* nb, const double* inv, uint32_t* rowpart, void* final_out, Out fm, char* ws,
-                      hipStream_t st, bool mfma) {
+// What the passes of step (i) read and write.  nseg segments of the counts (a streamed
+// slab's) run in the same launches: segment s reads counts + s * seg_counts, writes its
+// row-sum parts at rowpart + s * seg_row and its final sums at final_out + s * seg_final
+// elements; its partials are the s-th of bufA's and bufB's.
+struct PassIO {
+  const uint16_t* counts;
+  int lrow;                // log2 of the row stride of counts
+  const uint32_t* nb;      // per-basis totals
+  uint32_t* rowpart;
+  void* final_out;
+  void* bufA;
+  void* bufB;
+  int nseg = 1;
+  int64_t seg_counts = 0, seg_row = 0, seg_final = 0;
+  RowCheck chk{};          // checked with the last pass (nbases 0: not)
+};
+
+// The counts pass (n > kSmallN) and the later passes, into final_out with final mode `fm`.
+lre_status run_passes(lre_ctx* ctx, const Plan& P, const PassIO& io, uint64_t shots, Out fm, hipStream_t st) {
   const int n = P.n;
-  Fold1Args a1{counts, n, P.chunks, lrow, nb, inv, nullptr, rowpart, shots, P.blocks1, st};
+  int h = n - P.q1, l = P.q1;
   const bool single = P.npass == 0;
-  a1.out = single ? final_out : (void*)(ws + P.off_a);
-  const bool ok = (mfma && P.q1 == 7) ? fold1_mfma(P.t1, P.per_basis, single ? fm : Out::Partial, a1)
-                                       : fold1(P.q1, P.t1, P.per_basis, single ? fm : Out::Partial, a1);
+  Fold1Args a1{};
+  a1.counts = io.counts;
+  a1.n = n;
+  a1.chunks = P.chunks;
+  a1.lrow = io.lrow;
+  a1.nb = io.nb;
+  a1.out = single ? io.final_out : io.bufA;
+  a1.rowpart = io.rowpart;
+  a1.shots = shots;
+  a1.tiles = ipow3(n - P.q1) * P.runs;
+  a1.per_block = P.per_block;
+  a1.blocks = P.blocks1;
+  a1.nseg = io.nseg;
+  a1.seg_counts = io.seg_counts;
+  a1.seg_out = (ipow3(h) << h) * ipow4(l);
+  a1.seg_row = io.seg_row;
+  a1.st = st;
+  const bool ok = P.mfma ? io.nseg == 1 && fold1_mfma(P.t1, P.per_basis, single ? fm : Out::Partial, a1)
+                         : !single && fold1(P.q1, P.t1, P.per_basis, a1);
   if (!ok) return LRE_E_UNSUPPORTED;
   if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
   record_stage(ctx, 1, st);
 
-  int h = n - P.q1, l = P.q1;
   Ty tin = P.t1;
   for (int k = 0; k < P.npass; ++k) {
     const bool last = k + 1 == P.npass;
-    FoldKArgs ak;
-    ak.in = ws + (k % 2 == 0 ? P.off_a : P.off_b);
-    ak.out = last ? final_out : (void*)(ws + (k % 2 == 0 ? P.off_b : P.off_a));
-    ak.n = n;
-    ak.h = h;
-    ak.l = l;
-    ak.shots = shots;
-    ak.ncols = (ipow3(h - P.F[k]) << (h - P.F[k])) * ipow4(l);
-    ak.st = st;
-    if (!foldk(P.F[k], tin, P.tout[k], last ? fm : Out::Partial, ak)) return LRE_E_UNSUPPORTED;
-    if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
+    FoldArgs a{};
+    a.in = k == 0 ? io.bufA : io.bufB;
+    a.out = last ? io.final_out : io.bufB;
+    a.n = n;
+    a.h = h;
+    a.l = l;
+    a.shots = shots;
+    a.nseg = io.nseg;
+    a.seg_in = (ipow3(h) << h) * ipow4(l);
     h -= P.F[k];
     l += P.F[k];
+    a.seg_out = last ? io.seg_final : (ipow3(h) << h) * ipow4(l);
+    if (P.npass == 1) a.chk = io.chk;
+    a.st = st;
+    const bool done = P.npass == 1 ? fold_tail(P.F[k], tin, P.tout[k], fm, a)
+                                   : two_pass(P.F[k], last, tin, P.tout[k], fm, a);
+    if (!done) return LRE_E_UNSUPPORTED;
+    if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
     tin = P.tout[k];
+  }
+  if (P.npass != 1 && io.chk.nbases) {
+    hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)((io.chk.nbases + 255) / 256)), dim3(256), 0, st, io.chk);
+    if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
   }
   return LRE_OK;
 }
 
-// Step (i) into `final_out` (coef or T) with final mode `fm`.
-lre_status run_step1(lre_ctx* ctx, const Plan& P, const uint16_t* counts, uint64_t shots,
-                     const uint32_t* nb_in, void* final_out, Out fm, char* ws, hipStream_t st,
-                     bool mfma) {
-  const int n = P.n;
-  const int64_t nbases = ipow3(n);
-  const uint32_t* nb = nb_in;
-  double* inv = nullptr;
-  if (P.per_basis) {
-    inv = reinterpret_cast<double*>(ws + P.off_inv);
-    nb = prepare_totals(nbases, n, counts, nb_in, reinterpret_cast<uint32_t*>(ws + P.off_nb), inv, st);
-  }
-  uint32_t* rowpart = reinterpret_cast<uint32_t*>(ws + P.off_rowpart);
-  const lre_status s = run_passes(ctx, P, counts, n, shots, nb, inv, rowpart, final_out, fm, ws, st, mfma);
-  if (s != LRE_OK) return s;
+// An instance of n <= kSmallN qubits: everything in one launch.  fm: what `out` receives.
+template <int N, bool PB, Out M, bool RHO, typename OutT>
+void launch_small(const uint16_t* counts, uint64_t shots, const uint32_t* nb, void* out, void* rho, uint32_t* flags,
+                  hipStream_t st) {
+  hipLaunchKernelGGL((small_estimate_kernel<N, PB, M, RHO, OutT>), dim3(1), dim3(256), 0, st, counts, shots, nb, out,
+                     rho, flags);
+}
 
-  const int64_t rows = ipow3(P.q1);
-  const int64_t runs = ((int64_t)1 << (n - P.q1)) / P.chunks;
-  hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)((nbases + 255) / 256)), dim3(256), 0, st,
-                     (const uint32_t*)rowpart, rows, runs, nb, P.per_basis ? (uint64_t)0 : shots, nbases,
-                     ctx->flags);
+template <int N>
+void small_n(Out fm, const uint16_t* counts, uint64_t shots, const uint32_t* nb, void* out, void* rho, bool fp32,
+             uint32_t* flags, hipStream_t st) {
+  if (fm == Out::PauliT) launch_small<N, false, Out::PauliT, false, double>(counts, shots, nb, out, rho, flags, st);
+  else if (fm == Out::CoefUniform) {
+    if (!rho) launch_small<N, false, Out::CoefUniform, false, double>(counts, shots, nb, out, rho, flags, st);
+    else if (fp32) launch_small<N, false, Out::CoefUniform, true, float>(counts, shots, nb, out, rho, flags, st);
+    else launch_small<N, false, Out::CoefUniform, true, double>(counts, shots, nb, out, rho, flags, st);
+  } else {
+    if (!rho) launch_small<N, true, Out::CoefPerBasis, false, double>(counts, shots, nb, out, rho, flags, st);
+    else if (fp32) launch_small<N, true, Out::CoefPerBasis, true, float>(counts, shots, nb, out, rho, flags, st);
+    else launch_small<N, true, Out::CoefPerBasis, true, double>(counts, shots, nb, out, rho, flags, st);
+  }
+}
+
+lre_status run_small(lre_ctx* ctx, int n, Out fm, const uint16_t* counts, uint64_t shots, const uint32_t* nb,
+                     void* out, void* rho, bool fp32, hipStream_t st) {
+  switch (n) {
+    case 1: small_n<1>(fm, counts, shots, nb, out, rho, fp32, ctx->flags, st); break;
+    case 2: small_n<2>(fm, counts, shots, nb, out, rho, fp32, ctx->flags, st); break;
+    case 3: small_n<3>(fm, counts, shots, nb, out, rho, fp32, ctx->flags, st); break;
+    case 4: small_n<4>(fm, counts, shots, nb, out, rho, fp32, ctx->flags, st); break;
+    default: small_n<5>(fm, counts, shots, nb, out, rho, fp32, ctx->flags, st); break;
+  }
   return hipGetLastError() == hipSuccess ? LRE_OK : LRE_E_HIP;
+}
+
+// Step (i) of an instance of n > kSmallN qubits into `final_out` (coef or T) with final
+// mode `fm`.
+lre_status run_step1(lre_ctx* ctx, const Plan& P, const uint16_t* counts, uint64_t shots,
+                     const uint32_t* nb_in, void* final_out, Out fm, char* ws, hipStream_t st) {
+  const int64_t nbases = ipow3(P.n);
+  PassIO io{};
+  io.counts = counts;
+  io.lrow = P.n;
+  io.nb = P.per_basis ? nb_in : nullptr;
+  if (P.per_basis && !nb_in) {
+    uint32_t* nb = reinterpret_cast<uint32_t*>(ws + P.off_nb);
+    launch_row_sums(nbases, P.n, counts, nb, st);
+    io.nb = nb;
+  }
+  io.rowpart = reinterpret_cast<uint32_t*>(ws + P.off_rowpart);
+  io.final_out = final_out;
+  io.bufA = ws + P.off_a;
+  io.bufB = ws + P.off_b;
+  io.chk = RowCheck{io.rowpart, ipow3(P.q1), P.runs, P.per_block, nbases, io.nb,
+                    P.per_basis ? (uint64_t)0 : shots, ctx->flags, 1, 0};
+  return run_passes(ctx, P, io, shots, fm, st);
 }
 
 // Steps (i) and (ii) of one instance into caller-given workspace (lre_estimate).
@@ -509,9 +590,14 @@ lre_status estimate_impl(lre_ctx* ctx, int n, const uint16_t* counts, uint64_t s
   char* ws = static_cast<char*>(workspace);
 
   record_stage(ctx, 0, st);
-  lre_status s = run_step1(ctx, P, counts, shots, n_per_basis, coef,
-                           P.per_basis ? Out::CoefPerBasis : Out::CoefUniform, ws, st,
-                           (flags & LRE_WHT_MFMA) != 0);
+  const Out fm = P.per_basis ? Out::CoefPerBasis : Out::CoefUniform;
+  if (n <= kSmallN) {
+    const lre_status s = run_small(ctx, n, fm, counts, shots, n_per_basis, coef, want_rho ? rho : nullptr,
+                                   (flags & LRE_RHO_FP32) != 0, st);
+    for (int k = 1; k < 4; ++k) record_stage(ctx, k, st);
+    return s;
+  }
+  const lre_status s = run_step1(ctx, P, counts, shots, n_per_basis, coef, fm, ws, st);
   if (s != LRE_OK) return s;
   record_stage(ctx, 2, st);
   if (want_rho) {
@@ -634,8 +720,9 @@ lre_status lre_pauli_sums(lre_ctx* ctx, int n, const uint16_t* counts, uint64_t 
   if (workspace_bytes < P.total) return LRE_E_WORKSPACE;
   DeviceGuard g(ctx->device);
   if (!g.ok) return LRE_E_HIP;
-  return run_step1(ctx, P, counts, shots, nullptr, T, Out::PauliT, static_cast<char*>(workspace),
-                   static_cast<hipStream_t>(stream), (flags & LRE_WHT_MFMA) != 0);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (n <= kSmallN) return run_small(ctx, n, Out::PauliT, counts, shots, nullptr, T, nullptr, false, st);
+  return run_step1(ctx, P, counts, shots, nullptr, T, Out::PauliT, static_cast<char*>(workspace), st);
 }
 
 lre_status lre_signed_sums(lre_ctx* ctx, int n, const uint16_t* counts, const int64_t* bases,
@@ -688,7 +775,8 @@ struct lre_stream {
   std::vector<uint8_t> pushed;
   int64_t npushed = 0;
   double* coef = nullptr;     // accumulator / output, set by lre_stream_begin
-  size_t off_seg = 0, off_V = 0, off_rowpart = 0, off_stage = 0, off_tmp = 0, total = 0;
+  int par = 1;                // segments per launch
+  size_t off_a = 0, off_b = 0, off_nb = 0, off_V = 0, off_rowpart = 0, off_stage = 0, off_tmp = 0, total = 0;
   size_t seg_rowpart = 0;     // bytes of one segment's row-sum parts
   size_t stage_bytes = 0;
   hipEvent_t copied = nullptr;
@@ -721,26 +809,31 @@ lre_status stream_slab(lre_stream* S, int64_t slab, const uint16_t* counts, cons
   const Plan& P = S->P;
   const int np = S->np, n = S->n, h = S->h;
   const int64_t nbases = ipow3(np);
-  char* seg_ws = ws + S->off_seg;
-  const uint32_t* nb = nb_in;
-  double* inv = nullptr;
-  if (P.per_basis) {
-    inv = reinterpret_cast<double*>(seg_ws + P.off_inv);
-    nb = prepare_totals(nbases, n, counts, nb_in, reinterpret_cast<uint32_t*>(seg_ws + P.off_nb), inv, st);
+  PassIO io{};
+  io.lrow = n;
+  io.nb = P.per_basis ? nb_in : nullptr;
+  if (P.per_basis && !nb_in) {
+    uint32_t* nb = reinterpret_cast<uint32_t*>(ws + S->off_nb);
+    launch_row_sums(nbases, n, counts, nb, st);
+    io.nb = nb;
   }
+  io.bufA = ws + S->off_a;
+  io.bufB = ws + S->off_b;
+  io.nseg = S->par;
+  io.seg_counts = (int64_t)1 << np;
+  io.seg_row = (int64_t)(S->seg_rowpart / 4);
+  io.seg_final = ipow4(np);
   const size_t vbytes = (size_t)ipow4(np) * ty_size(S->tV);
-  for (int sg = 0; sg < (1 << h); ++sg) {
-    uint32_t* rowpart = reinterpret_cast<uint32_t*>(ws + S->off_rowpart + (size_t)sg * S->seg_rowpart);
-    void* V = ws + S->off_V + (size_t)sg * vbytes;
-    const lre_status s = run_passes(S->ctx, P, counts + ((int64_t)sg << np), n, S->shots, nb, inv, rowpart, V,
-                                    Out::Partial, seg_ws, st, (S->flags & LRE_WHT_MFMA) != 0);
+  for (int sg = 0; sg < (1 << h); sg += S->par) {
+    io.counts = counts + ((int64_t)sg << np);
+    io.rowpart = reinterpret_cast<uint32_t*>(ws + S->off_rowpart + (size_t)sg * S->seg_rowpart);
+    io.final_out = ws + S->off_V + (size_t)sg * vbytes;
+    const lre_status s = run_passes(S->ctx, P, io, S->shots, Out::Partial, st);
     if (s != LRE_OK) return s;
   }
-  const int64_t rows = ipow3(P.q1);
-  const int64_t runs = ((int64_t)1 << (np - P.q1)) / P.chunks;
-  hipLaunchKernelGGL(check_rows_seg_kernel, dim3((unsigned)((nbases + 255) / 256)), dim3(256), 0, st,
-                     (const uint32_t*)(ws + S->off_rowpart), (int64_t)(S->seg_rowpart / 4), 1 << h, rows, runs, nb,
-                     P.per_basis ? (uint64_t)0 : S->shots, nbases, S->ctx->flags);
+  const RowCheck chk{reinterpret_cast<const uint32_t*>(ws + S->off_rowpart), ipow3(P.q1), P.runs, P.per_block, nbases,
+                     io.nb, P.per_basis ? (uint64_t)0 : S->shots, S->ctx->flags, 1 << h, io.seg_row};
+  hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)((nbases + 255) / 256)), dim3(256), 0, st, chk);
   // Letters of the top qubits: digit p of the slab index (base 3) is qubit h - p.
   uint32_t atop = 0;
   int64_t t = slab;
@@ -794,9 +887,19 @@ lre_status lre_stream_create(lre_ctx* ctx, int n, int h, uint64_t shots, uint32_
   S->slabs = ipow3(h);
   S->pushed.assign((size_t)S->slabs, 0);
   const size_t segs = (size_t)1 << h;
-  S->seg_rowpart = align256((size_t)S->P.blocks1 * (size_t)ipow3(S->P.q1) * 4);
+  S->seg_rowpart = align256((size_t)S->P.parts * (size_t)ipow3(S->P.q1) * 4);
+  // Segments of a slab run side by side as far as their partials stay within 4 GiB (one
+  // launch of a small segment does not fill the chip); the MFMA form takes one at a time.
+  const int hs = S->np - S->P.q1, h2 = hs - S->P.F[0];
+  const size_t sizeA = S->P.npass ? (size_t)(ipow3(hs) << hs) * (size_t)ipow4(S->P.q1) * ty_size(S->P.t1) : 0;
+  const size_t sizeB =
+      S->P.npass > 1 ? (size_t)(ipow3(h2) << h2) * (size_t)ipow4(S->np - h2) * ty_size(S->P.tout[0]) : 0;
+  if (!S->P.mfma)
+    while (S->par < (int)segs && (sizeA + sizeB) * 2 * (size_t)S->par <= (size_t)4 << 30) S->par *= 2;
   size_t off = 0;
-  S->off_seg = off; off += align256(S->P.total);
+  S->off_a = off; off += align256(sizeA * (size_t)S->par);
+  S->off_b = off; off += align256(sizeB * (size_t)S->par);
+  S->off_nb = off; off += align256(S->P.per_basis ? (size_t)ipow3(S->np) * 4 : 0);
   S->off_V = off; off += align256(segs * (size_t)ipow4(S->np) * ty_size(S->tV));
   S->off_rowpart = off; off += segs * S->seg_rowpart;
   S->stage_bytes = (size_t)ipow3(S->np) << n;

@@ -731,18 +731,6 @@ __device__ __forceinline__ void counts_block(const uint16_t* __restrict__ counts
   }
 }
 
-template <int Q, int THREADS, typename Acc, bool PER_BASIS, Out MODE, bool MAD24, int MINWAVES = 1,
-          bool PREFETCH = PER_BASIS>
-__global__ __launch_bounds__(THREADS, MINWAVES) void fold_counts_stream_kernel(
-    const uint16_t* __restrict__ counts, int n, int chunks, const double* __restrict__ inv_nb,
-    void* __restrict__ out, uint32_t* __restrict__ rowpart, uint64_t shots, int lrow) {
-  __shared__ Acc acc[StreamGeom<Q>::NACC];
-  __shared__ uint32_t rs_acc[StreamGeom<Q>::NROWS];
-  counts_block<Q, THREADS, Acc, PER_BASIS, MODE, MAD24, PREFETCH>(counts, n, chunks, inv_nb, out, rowpart, shots,
-                                                                 blockIdx.x, threadIdx.x, acc, rs_acc, nullptr,
-                                                                 nullptr, lrow);
-}
-
 // ---------------------------------------------------------------------------------
 // Counts pass on int8 MFMA (Q = 7 qubits per tile).  The Walsh-Hadamard transform over
 // the low 6 outcome bits of every basis row is a dense +-1 contraction,
@@ -1217,65 +1205,6 @@ static __global__ void fill_u32_kernel(uint32_t* __restrict__ p, int64_t count, 
   if (i < count) p[i] = v;
 }
 
-// One block of 256 threads per basis row.
-static __global__ __launch_bounds__(256) void row_totals_kernel(const uint16_t* __restrict__ counts,
-                                                         int n, uint32_t* __restrict__ nb) {
-  const int64_t b = blockIdx.x;
-  const int64_t d = (int64_t)1 << n;
-  const uint16_t* row = counts + b * d;
-  uint32_t s = 0;
-  if (n >= 3) {
-    // 16-byte loads of 8 counts (rows of 2^n >= 8 counts start 16-byte aligned)
-#pragma unroll 4
-    for (int64_t i = (int64_t)threadIdx.x * 8; i < d; i += 256 * 8) {
-      typedef uint32_t u32x4_v __attribute__((ext_vector_type(4)));
-      const u32x4_v v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_v*>(row + i));
-      s += (v.x & 0xFFFFu) + (v.x >> 16) + (v.y & 0xFFFFu) + (v.y >> 16) + (v.z & 0xFFFFu) + (v.z >> 16) +
-           (v.w & 0xFFFFu) + (v.w >> 16);
-    }
-  } else {
-    for (int64_t i = threadIdx.x; i < d; i += 256) s += row[i];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  __shared__ uint32_t part[4];
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) nb[b] = part[0] + part[1] + part[2] + part[3];
-}
-
-// inv[b] = 1 / N_b (0 for an empty basis, which the row check flags), correctly rounded.
-static __global__ void reciprocal_kernel(const uint32_t* __restrict__ nb, double* __restrict__ inv, int64_t count) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < count) inv[i] = nb[i] ? 1.0 / (double)nb[i] : 0.0;
-}
-
-// rowpart as written by fold_counts_kernel: [3^n / rows][runs][rows].
-// Basis b = grp * rows + j of row group grp.
-__device__ __forceinline__ void check_row_gj(const uint32_t* __restrict__ rowpart, int64_t rows, int64_t runs,
-                                             const uint32_t* __restrict__ nb, uint64_t shots, int64_t grp, int64_t j,
-                                             uint32_t* __restrict__ flags) {
-  const int64_t b = grp * rows + j;
-  uint64_t tot = 0;
-  for (int64_t r = 0; r < runs; ++r) tot += rowpart[(grp * runs + r) * rows + j];
-  const uint64_t want = shots ? shots : (uint64_t)nb[b];
-  if (tot != want) atomicOr(flags, (uint32_t)FLAG_SHOTS);
-  if (!shots && want == 0) atomicOr(flags, (uint32_t)FLAG_EMPTY);
-}
-
-__device__ __forceinline__ void check_row(const uint32_t* __restrict__ rowpart, int64_t rows, int64_t runs,
-                                          const uint32_t* __restrict__ nb, uint64_t shots, int64_t b,
-                                          uint32_t* __restrict__ flags) {
-  check_row_gj(rowpart, rows, runs, nb, shots, b / rows, b % rows, flags);
-}
-
-static __global__ void check_rows_kernel(const uint32_t* __restrict__ rowpart, int64_t rows, int64_t runs,
-                                  const uint32_t* __restrict__ nb, uint64_t shots,
-                                  int64_t nbases, uint32_t* __restrict__ flags) {
-  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b < nbases) check_row(rowpart, rows, runs, nb, shots, b, flags);
-}
-
 // ---------------------------------------------------------------------------------
 // Streamed estimation: the counts arrive in slabs of consecutive bases (fixed letters of
 // the top h qubits).  Each slab is cut into its 2^h outcome segments (fixed outcome bits
@@ -1283,21 +1212,6 @@ static __global__ void check_rows_kernel(const uint32_t* __restrict__ rowpart, i
 // the stride of the full rows, and goes through the same passes as any instance, ending
 // in unnormalised sums V[s_top][a'].  The top qubits are then folded into the
 // coefficient array, which accumulates over the slabs.
-
-// Row totals of a slab: sum the parts every segment's counts pass wrote.
-static __global__ void check_rows_seg_kernel(const uint32_t* __restrict__ rowpart, int64_t seg_stride, int nseg,
-                                             int64_t rows, int64_t runs, const uint32_t* __restrict__ nb,
-                                             uint64_t shots, int64_t nbases, uint32_t* __restrict__ flags) {
-  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b >= nbases) return;
-  const int64_t grp = b / rows, j = b % rows;
-  uint64_t tot = 0;
-  for (int sg = 0; sg < nseg; ++sg)
-    for (int64_t r = 0; r < runs; ++r) tot += rowpart[sg * seg_stride + (grp * runs + r) * rows + j];
-  const uint64_t want = shots ? shots : (uint64_t)nb[b];
-  if (tot != want) atomicOr(flags, (uint32_t)FLAG_SHOTS);
-  if (!shots && want == 0) atomicOr(flags, (uint32_t)FLAG_EMPTY);
-}
 
 // Fold of the top H qubits of one slab into the accumulator: for every column a' (the
 // letters of the other qubits) and subset m of the top qubits,

@@ -1,0 +1,762 @@
+// lre_tile.hpp -- gfx950 counts pass in sub-tiles folded through LDS, the later pass that
+// ends a small plan, and the one-workgroup path of at most 5 qubits.
+//
+// Counts pass.  A sub-tile is 3^5 rows (the letters of the 5 lowest qubits) x 64 outcomes
+// (the bits of the 6 lowest): 128 bytes of each row.  Three stages:
+//   1. a thread (lam = outcome bits 3-5, rs = letters of qubits 2-4) holds 9 rows x 8
+//      outcomes, transforms outcome bits 0-2 in registers, folds qubits 0 and 1 and
+//      stores 32 values, [letters of qubits 0, 1][Walsh bit 2], to V;
+//   2. a thread (letters of qubits 0, 1; outcome bits 4, 5; basis letter of qubit 4) reads
+//      its 3 x 3 x 2 x 2 values of qubits 2 and 3 from V, folds both and stores 16 to W;
+//   3. a thread owns 4 of the 4^5 Pauli indices of the sub-tile (the letters of qubit 4),
+//      folds qubit 4 from W, and folds the qubits above with accumulators in registers:
+//      the sub-tiles of 5 + LV qubits follow one another, letter of the top qubit outermost
+//      and its outcome bits innermost, so a letter's odd part is final as soon as it is
+//      formed and only the identity letter is kept.
+// Every value passes LDS twice, each time as a plain store and load (no atomics), and no
+// stage has a chain longer than one thread's fold, so a small instance is not one workgroup's
+// serial walk: n = 7 (per-basis totals from the rows) 49.8 -> 16.5 us a call, n = 8 33 -> 14.9,
+// n = 10 66 -> 52.  At n >= 12 the pass is bound by memory: with 10 % (n = 12) to 19 % (n = 13,
+// binary64) of its traffic being writes the device moves 5.2 TB/s (loads alone: 7.0 and 6.4),
+// n = 12 927 -> 904 us, n = 13 6.40 -> 6.13 ms.
+#pragma once
+#include "lre_kernels.hpp"
+
+namespace lre {
+
+constexpr int kTileRows = 243;      // 3^5 rows of a sub-tile
+constexpr int kTileUnits = 216;     // stage-1 threads: 27 row sets x 8 lanes of 8 outcomes
+constexpr int kTileVP = 218;        // stride of V's 32 codes (26 mod 32: stage 2 reads 16 codes
+                                    // x 2 neighbours at a time, all on different banks)
+constexpr int kTileUnits2 = 192;    // stage-2 threads: 16 codes x 2 x (3 letters x 2 outcomes)
+constexpr int kTileWP = 208;        // stride of W's 16 codes (16 mod 32: stage 3 reads two)
+constexpr int kTileV = 32 * kTileVP, kTileW = 16 * kTileWP;
+
+// Qubits folded and outcomes covered by a tile of level LV.
+template <int LV>
+struct TileGeom {
+  static constexpr int Q = 5 + LV;
+  static constexpr int NROWS = (int)ipow3(Q);
+  static constexpr int WB = LV <= 1 ? 6 : 5 + LV;        // log2 of the outcomes of a tile
+  static constexpr int NL = (int)ipow3(LV);              // row blocks of 243 rows
+  static constexpr int NS = 1 << (WB - 6);               // 64-outcome columns
+};
+
+typedef uint32_t tile_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t tile_u32x2 __attribute__((ext_vector_type(2)));
+
+// A pointer every lane of the wave holds, moved to scalar registers.
+template <typename T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(uniform_ptr(static_cast<const char*>(p))), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00027000);
+}
+
+// The three stages of a sub-tile.  Elem: double (per-basis totals) or int32_t (a sub-tile's
+// sums of at most 243 x 64 counts fit).
+template <bool PB>
+struct TileStages {
+  using Elem = std::conditional_t<PB, double, int32_t>;
+
+  // Stage 1 of thread t < kTileUnits.
+  struct Rows {
+    uint32_t raw[9][4];
+    Elem L1[4][2];
+    uint32_t rtot;           // lane lam: the total of row lam (r < 8)
+    uint32_t rtot8;          // the total of row 8
+  };
+
+  // Byte offset of thread t's rows in the sub-tile.  The waves' threads beyond kTileUnits go
+  // through stage 1 with the others, on rows out of the descriptor's range (zeros, no traffic)
+  // and with the spare columns of V: around a branch, the compiler would have to count the
+  // loads it may have skipped and wait for nearly all that are in flight.
+  static __device__ __forceinline__ int row_offset(int t, int rowbytes) {
+    return t < kTileUnits ? (t >> 3) * 9 * rowbytes + (t & 7) * 16 : 0x40000000;
+  }
+
+  static __device__ __forceinline__ void load_row(Rows& R, __amdgpu_buffer_rsrc_t rsrc, int voff, int rowbytes, int r) {
+    const tile_u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(
+        rsrc, voff, __builtin_amdgcn_readfirstlane(r * rowbytes), 2 /* nt */);
+    R.raw[r][0] = u.x; R.raw[r][1] = u.y; R.raw[r][2] = u.z; R.raw[r][3] = u.w;
+  }
+
+  static __device__ __forceinline__ void load_rows(Rows& R, __amdgpu_buffer_rsrc_t rsrc, int voff, int rowbytes) {
+#pragma unroll
+    for (int r = 0; r < 9; ++r) load_row(R, rsrc, voff, rowbytes, r);
+  }
+
+  // Rows 3 D1 .. 3 D1 + 2 into Vt = V + (place of t); each row's registers take the row of
+  // the sub-tile behind `next` as soon as it has been transformed.
+  template <int D1>
+  static __device__ __forceinline__ void stage1(Rows& R, Elem* Vt, const double* inv9, int lam,
+                                                __amdgpu_buffer_rsrc_t next, int voff, int rowbytes) {
+    if constexpr (D1 == 0) {
+      R.rtot = 0;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) R.L1[a][0] = R.L1[a][1] = Elem(0);
+    }
+    Elem L0[4] = {Elem(0), Elem(0), Elem(0), Elem(0)};         // [m1 + 2 m2]
+    double inv[3];
+    if constexpr (PB) {
+#pragma unroll
+      for (int d0 = 0; d0 < 3; ++d0) inv[d0] = inv9[3 * D1 + d0];
+    }
+#pragma unroll
+    for (int d0 = 0; d0 < 3; ++d0) {
+      const int r = 3 * D1 + d0;
+      int32_t x[8];
+      unpack_raw<8>(R.raw[r], x);
+      wht_regs<3>(x);
+      // Not earlier: the old row's registers would still be in use and the loop would
+      // copy all 36 of them.
+      __builtin_amdgcn_sched_barrier(0);
+      load_row(R, next, voff, rowbytes, r);
+      const uint32_t tot = lane_sum<3>((uint32_t)x[0]);
+      if (r < 8) R.rtot = lam == r ? tot : R.rtot;
+      else R.rtot8 = tot;
+      Elem y[8];
+      if constexpr (PB) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) y[v] = (double)x[v] * inv[d0];
+      } else {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) y[v] = x[v];
+      }
+#pragma unroll
+      for (int mr = 0; mr < 4; ++mr) {
+        const int m1 = mr & 1, m2 = mr >> 1;
+        L0[mr] += y[2 * mr];
+        if (m1 == 0) R.L1[d0 + 1][m2] += y[2 * mr + 1];
+        else Vt[(d0 + 1 + 4 * (D1 + 1) + 16 * m2) * kTileVP] = y[2 * mr + 1];
+      }
+      // The row's values end here: without this the sums of three rows are formed together
+      // and hold their terms (99 registers instead of 52 for one sub-tile of integers).
+#pragma unroll
+      for (int mr = 0; mr < 4; ++mr) asm volatile("" : "+v"(L0[mr]));
+      asm volatile("" : "+v"(R.L1[d0 + 1][0]), "+v"(R.L1[d0 + 1][1]));
+    }
+#pragma unroll
+    for (int mr = 0; mr < 4; ++mr) {
+      const int m1 = mr & 1, m2 = mr >> 1;
+      if (m1 == 0) R.L1[0][m2] += L0[mr];
+      else Vt[(4 * (D1 + 1) + 16 * m2) * kTileVP] = L0[mr];
+    }
+    if constexpr (D1 == 2) {
+#pragma unroll
+      for (int a0 = 0; a0 < 4; ++a0)
+#pragma unroll
+        for (int m2 = 0; m2 < 2; ++m2) Vt[(a0 + 16 * m2) * kTileVP] = R.L1[a0][m2];
+    }
+  }
+
+  // The 9 rows' totals into rt (LDS): set (first tile of the rows) or added.
+  static __device__ __forceinline__ void row_totals(const Rows& R, uint32_t* rt, int lam, bool set) {
+    if (set) {
+      rt[lam] = R.rtot;
+      if (lam == 0) rt[8] = R.rtot8;
+    } else {
+      atomicAdd(&rt[lam], R.rtot);
+      if (lam == 0) atomicAdd(&rt[8], R.rtot8);
+    }
+  }
+
+  // Place of stage-1 thread t in V: outcome bit 5 lowest, then bits 3 and 4.
+  static __device__ __forceinline__ int place(int t) {
+    return t < kTileUnits ? (t & ~7) | ((t >> 2) & 1) | ((t & 3) << 1) : kTileUnits + (t & 1);
+  }
+  // Its rows' places among the 243.
+  static __device__ __forceinline__ int row_of(int t) { return (t < kTileUnits ? t >> 3 : 0) * 9; }
+
+  // Stage 2 of thread u < kTileUnits2 = code + 16 s5 + 32 (s4 + 2 d4).
+  static __device__ __forceinline__ void stage2(const Elem* V, Elem* W, int u) {
+    const int q = u >> 5;
+    const Elem* const V2 = V + (u & 15) * kTileVP + ((u >> 4) & 1) + 4 * (q & 1) + 72 * (q >> 1);
+    Elem* const W2 = W + u;
+    Elem I2[4];                                                 // letter I of qubit 2, per a3
+#pragma unroll
+    for (int d2 = 0; d2 < 3; ++d2) {
+#pragma unroll
+      for (int m2 = 0; m2 < 2; ++m2) {
+        Elem e[3], o[3];
+#pragma unroll
+        for (int d3 = 0; d3 < 3; ++d3) {
+          const Elem a = V2[16 * m2 * kTileVP + 8 * d2 + 24 * d3], b = V2[16 * m2 * kTileVP + 8 * d2 + 24 * d3 + 2];
+          e[d3] = a + b;
+          o[d3] = a - b;
+        }
+        const Elem r[4] = {e[0] + e[1] + e[2], o[0], o[1], o[2]};
+#pragma unroll
+        for (int a3 = 0; a3 < 4; ++a3) {
+          if (m2 == 1) W2[(d2 + 1 + 4 * a3) * kTileWP] = r[a3];
+          else if (d2 == 0) I2[a3] = r[a3];
+          else I2[a3] += r[a3];
+        }
+      }
+    }
+#pragma unroll
+    for (int a3 = 0; a3 < 4; ++a3) W2[4 * a3 * kTileWP] = I2[a3];
+  }
+
+  // Stage 3 of thread t < 256 = code + 16 a2 + 64 a3: T[s5] of Pauli indices t + 256 a4.
+  static __device__ __forceinline__ void stage3(const Elem* W, int t, Elem (&T0)[4], Elem (&T1)[4]) {
+    const Elem* const W3 = W + (t >> 4) * kTileWP + (t & 15);
+    auto fold = [&](const Elem* w, Elem (&T)[4]) __attribute__((always_inline)) {
+      Elem e[3];
+#pragma unroll
+      for (int d4 = 0; d4 < 3; ++d4) {
+        const Elem a = w[64 * d4], b = w[64 * d4 + 32];
+        e[d4] = a + b;
+        T[d4 + 1] = a - b;
+      }
+      T[0] = e[0] + e[1] + e[2];
+    };
+    fold(W3, T0);
+    fold(W3 + 16, T1);
+  }
+};
+
+// A row total's reciprocal, correctly rounded (0 for an empty basis, which the row check
+// flags).
+__device__ __forceinline__ double tile_reciprocal(uint32_t N) { return N ? 1.0 / (double)N : 0.0; }
+
+template <bool NT, typename Acc>
+__device__ __forceinline__ void tile_put(__amdgpu_buffer_rsrc_t rsrc, int t, int i, Acc v) {
+  const int soff = __builtin_amdgcn_readfirstlane(i * (int)sizeof(Acc));
+  if constexpr (sizeof(Acc) == 4) {
+    __builtin_amdgcn_raw_buffer_store_b32((uint32_t)v, rsrc, t * 4, soff, NT ? 2 : 0);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(tile_u32x2, v), rsrc, t * 8, soff, NT ? 2 : 0);
+  }
+}
+
+// One sub-tile per workgroup of 256 threads, 5 qubits folded (plans too small to fill the
+// chip with anything larger): blockIdx.x = (b_hi, 64-outcome column), blockIdx.y = segment (a
+// streamed slab's outcome segment; counts advance by seg_counts, out and rowpart by seg_out
+// elements and seg_row words).
+// out: [3^(n-5)][2^(n-5)][4^5] partial sums; rowpart: [block][243] row sums of the block.
+// nb: per-basis totals (PB), of which every row's reciprocal is formed here.
+template <bool PB, typename Acc>
+__global__ __launch_bounds__(256) void counts_subtile_kernel(const uint16_t* __restrict__ counts, int n, int lrow,
+                                                             const uint32_t* __restrict__ nb, Acc* __restrict__ out,
+                                                             uint32_t* __restrict__ rowpart, int64_t seg_counts,
+                                                             int64_t seg_out, int64_t seg_row) {
+  using S = TileStages<PB>;
+  using Elem = typename S::Elem;
+  __shared__ Elem V[kTileV], W[kTileW];
+  __shared__ uint32_t rs_acc[kTileRows];
+  __shared__ double invt[PB ? kTileRows : 1];
+  const int tid = threadIdx.x, lam = tid & 7;
+  const int64_t b_hi = blockIdx.x >> (n - 6), col = blockIdx.x & ((1 << (n - 6)) - 1);
+  const int rowbytes = 2 << lrow;
+  const bool on1 = tid < kTileUnits;
+  typename S::Rows R;
+  const int voff = S::row_offset(tid, rowbytes);
+  const auto src = tile_rsrc(counts + blockIdx.y * seg_counts + ((b_hi * kTileRows) << lrow) + (col << 6),
+                             (kTileRows - 1) * rowbytes + 128);
+  const auto none = tile_rsrc(counts, 0);
+  S::load_rows(R, src, voff, rowbytes);
+  if constexpr (PB) {
+    if (tid < kTileRows) invt[tid] = tile_reciprocal(nb[b_hi * kTileRows + tid]);
+    lds_barrier();
+  }
+  {
+    Elem* const Vt = V + S::place(tid);
+    const double* const inv9 = invt + (PB ? S::row_of(tid) : 0);
+    S::template stage1<0>(R, Vt, inv9, lam, none, voff, rowbytes);
+    S::template stage1<1>(R, Vt, inv9, lam, none, voff, rowbytes);
+    S::template stage1<2>(R, Vt, inv9, lam, none, voff, rowbytes);
+    if (on1) S::row_totals(R, rs_acc + S::row_of(tid), lam, true);
+  }
+  lds_barrier();
+  if (tid < kTileUnits2) S::stage2(V, W, tid);
+  lds_barrier();
+  Elem T0[4], T1[4];
+  S::stage3(W, tid, T0, T1);
+  const auto o = tile_rsrc(out + blockIdx.y * seg_out + (((b_hi << (n - 5)) + 2 * col) << 10), 2048 * (int)sizeof(Acc));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    tile_put<false>(o, tid, 256 * k, (Acc)T0[k]);
+    tile_put<false>(o, tid, 1024 + 256 * k, (Acc)T1[k]);
+  }
+  uint32_t* __restrict__ rp = rowpart + blockIdx.y * seg_row + (int64_t)blockIdx.x * kTileRows;
+  if (tid < kTileRows) rp[tid] = rs_acc[tid];
+}
+
+// Tiles of 5 + LV qubits (LV = 1, 2), 512 threads: waves 0-3 run stage 1 of one sub-tile
+// while waves 4-7 run stages 2 and 3 of the one before (V double-buffered), so one's loads
+// and transforms overlap the other's LDS traffic and stores; a SIMD holds a wave of each
+// kind.  Two barriers per sub-tile: at its end, and between stages 2 and 3, which waves 0-3
+// meet after two thirds of their rows.  The rows of sub-tile j + 2 are loaded as those
+// of j are used, into the same registers.  Only waves 4-7 store to memory, so no load's wait
+// covers a store.
+// Binary64 sub-tiles take the LDS of a CU (one workgroup), integers half of it.
+// blockIdx.x: `per_block` consecutive tiles, ordered (b_hi, tile of the row); blockIdx.y:
+// segment, as above.  out: [3^(n-Q)][2^(n-Q)][4^Q]; rowpart: [b_hi + block][3^Q], the row sums
+// over the block's tiles of b_hi.
+template <int LV, bool PB, typename Acc>
+__global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
+    const uint16_t* __restrict__ counts, int n, int lrow, int64_t tiles, int64_t per_block,
+    const uint32_t* __restrict__ nb, Acc* __restrict__ out, uint32_t* __restrict__ rowpart, int64_t seg_counts,
+    int64_t seg_out, int64_t seg_row) {
+  static_assert(LV == 1 || LV == 2, "levels above the sub-tile");
+  using G = TileGeom<LV>;
+  using S = TileStages<PB>;
+  using Elem = typename S::Elem;
+  // Partials of the larger plans are read again only after more than the caches hold.
+  constexpr bool kNT = PB && LV >= 2;
+  constexpr int NST = G::NL * G::NS;                           // sub-tiles of a tile
+  __shared__ Elem Vbuf[2 * kTileV];
+  __shared__ Elem W[kTileW];
+  __shared__ uint32_t rs_acc[G::NROWS];
+  __shared__ double invt[PB ? 2 * kTileRows : 1];
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lgT = n - G::WB;                                   // log2 of the tiles of a row
+  const int64_t t0 = blockIdx.x * per_block;
+  const int nt = (int)(tiles - t0 < per_block ? tiles - t0 : per_block);
+  const int nsteps = nt * NST;
+  const int rowbytes = 2 << lrow;
+  counts = uniform_ptr(counts + blockIdx.y * seg_counts);
+  const auto first_of_row = [&](int t) { return t == 0 || (((t0 + t) >> lgT) != ((t0 + t - 1) >> lgT)); };
+
+  if (wave < 4) {
+    // ---- stage 1
+    const int tid = threadIdx.x, lam = tid & 7;
+    const bool on1 = tid < kTileUnits;
+    const int voff = S::row_offset(tid, rowbytes);
+    typename S::Rows R[2];
+    // Sub-tile (tile t of the block, row block lblk, column s).
+    struct At { int t, lblk, s; };
+    auto advance = [&](At& a) __attribute__((always_inline)) {
+      if (++a.s == G::NS) {
+        a.s = 0;
+        if (++a.lblk == G::NL) { a.lblk = 0; ++a.t; }
+      }
+    };
+    auto src = [&](const At& a) __attribute__((always_inline)) {
+      const int64_t tile = t0 + (a.t < nt ? a.t : 0);
+      const uint16_t* p = counts + (((tile >> lgT) * G::NROWS + a.lblk * kTileRows) << lrow) +
+                          ((tile & (((int64_t)1 << lgT) - 1)) << G::WB) + a.s * 64;
+      return tile_rsrc(p, a.t < nt ? (kTileRows - 1) * rowbytes + 128 : 0);
+    };
+    At cur{0, 0, 0}, ahead{0, 0, 0};
+    S::load_rows(R[0], src(ahead), voff, rowbytes);
+    advance(ahead);
+    S::load_rows(R[1], src(ahead), voff, rowbytes);
+    advance(ahead);
+    lds_barrier();                                             // reciprocals of the first rows
+    int rho = 0;                                               // row blocks so far
+    auto step = [&](typename S::Rows& Rj, int buf) __attribute__((always_inline)) {
+      Elem* const Vt = Vbuf + buf * kTileV + S::place(tid);
+      const double* const inv9 = invt + (PB ? (rho & 1) * kTileRows + S::row_of(tid) : 0);
+      const auto next = src(ahead);
+      S::template stage1<0>(Rj, Vt, inv9, lam, next, voff, rowbytes);
+      S::template stage1<1>(Rj, Vt, inv9, lam, next, voff, rowbytes);
+      lds_barrier();
+      S::template stage1<2>(Rj, Vt, inv9, lam, next, voff, rowbytes);
+      if (on1)
+        S::row_totals(Rj, rs_acc + cur.lblk * kTileRows + S::row_of(tid), lam, cur.s == 0 && first_of_row(cur.t));
+      lds_barrier();
+      advance(ahead);
+      advance(cur);
+      if (cur.s == 0) ++rho;
+    };
+    int j = 0;
+    for (; j + 1 < nsteps; j += 2) {
+      step(R[0], 0);
+      step(R[1], 1);
+    }
+    if (j < nsteps) step(R[0], 0);
+    lds_barrier();
+    lds_barrier();
+  } else {
+    // ---- stages 2 and 3 of the sub-tile before
+    const int tid = threadIdx.x - 256;
+    // Totals of row block r of the block's sequence.
+    auto load_nb = [&](int r) __attribute__((always_inline)) {
+      const int t = r / G::NL;
+      const int64_t row = ((t0 + t) >> lgT) * G::NROWS + (r % G::NL) * kTileRows;
+      return PB && t < nt && tid < kTileRows ? nb[row + tid] : 0u;
+    };
+    auto set_inv = [&](int r, uint32_t N) __attribute__((always_inline)) {
+      if (PB && tid < kTileRows) invt[(r & 1) * kTileRows + tid] = tile_reciprocal(N);
+    };
+    set_inv(0, load_nb(0));
+    uint32_t nbn = load_nb(1);
+    lds_barrier();
+    int rho = 0;                                               // row block of the sub-tile processed
+    if constexpr (G::NS == 1) {                                // sub-tile 1 has other rows already
+      set_inv(1, nbn);
+      nbn = load_nb(2);
+    }
+    lds_barrier();
+    lds_barrier();
+    int j = 0;
+    Elem T0[4], T1[4];
+    // Stages 2 and 3 of sub-tile j; the reciprocals the sub-tile after next needs.
+    auto stages = [&](int lblk, int s, bool last_of_rows) __attribute__((always_inline)) {
+      if (tid < kTileUnits2) S::stage2(Vbuf + (j & 1) * kTileV, W, tid);
+      if (s == 0) {
+        const int r = rho + (G::NS == 1 ? 2 : 1);
+        set_inv(r, nbn);
+        nbn = load_nb(r + 1);
+      }
+      lds_barrier();
+      S::stage3(W, tid, T0, T1);
+      if (s == G::NS - 1) ++rho;
+      ++j;
+    };
+    // The totals of the rows just finished, once the block's last tile of them is done.
+    auto flush = [&](int t, int lblk) __attribute__((always_inline)) {
+      if (t + 1 == nt || first_of_row(t + 1)) {
+        uint32_t* rp = rowpart + blockIdx.y * seg_row + (((t0 + t) >> lgT) + blockIdx.x) * G::NROWS + lblk * kTileRows;
+        if (tid < kTileRows) rp[tid] = rs_acc[lblk * kTileRows + tid];
+      }
+    };
+    Acc i5S[4], i5D[4];          // identity letter of qubit 5 (LV 2: even and odd in outcome bit 6)
+    Acc i6[4][4];                // LV 2: identity letter of qubit 6, per letter of qubit 5
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      i5S[k] = i5D[k] = Acc(0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) i6[q][k] = Acc(0);
+    }
+    for (int t = 0; t < nt; ++t) {
+      const int64_t tile = t0 + t;
+      const int64_t first = (((tile >> lgT) << (n - G::Q)) + (tile & (((int64_t)1 << lgT) - 1))) << (2 * G::Q);
+      const auto o = tile_rsrc(out + blockIdx.y * seg_out + first, (1 << (2 * G::Q)) * (int)sizeof(Acc));
+      if constexpr (LV == 1) {
+        StaticFor<0, 3>::run([&](auto lc) __attribute__((always_inline)) {
+          constexpr int l5 = decltype(lc)::value;
+          stages(l5, 0, false);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            tile_put<kNT>(o, tid, 1024 * (l5 + 1) + 256 * k, (Acc)(T0[k] - T1[k]));
+            i5S[k] += (Acc)(T0[k] + T1[k]);
+          }
+          flush(t, l5);
+          if constexpr (l5 == 2) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              tile_put<kNT>(o, tid, 256 * k, i5S[k]);
+              i5S[k] = Acc(0);
+            }
+          }
+          lds_barrier();
+        });
+      } else {
+        for (int l6 = 0; l6 < 3; ++l6) {
+          StaticFor<0, 3>::run([&](auto lc) __attribute__((always_inline)) {
+            constexpr int l5 = decltype(lc)::value;
+            Acc hS[4], hD[4];                                  // outcome bit 6 = 0
+            stages(3 * l6 + l5, 0, false);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              hS[k] = (Acc)(T0[k] + T1[k]);
+              hD[k] = (Acc)(T0[k] - T1[k]);
+            }
+            lds_barrier();
+            stages(3 * l6 + l5, 1, false);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const Acc Sk = (Acc)(T0[k] + T1[k]), Dk = (Acc)(T0[k] - T1[k]);
+              tile_put<kNT>(o, tid, 4096 * (l6 + 1) + 1024 * (l5 + 1) + 256 * k, hD[k] - Dk);
+              i5S[k] += hS[k] + Sk;
+              i5D[k] += hS[k] - Sk;
+              i6[l5 + 1][k] += hD[k] + Dk;
+            }
+            flush(t, 3 * l6 + l5);
+            if constexpr (l5 == 2) {
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                tile_put<kNT>(o, tid, 4096 * (l6 + 1) + 256 * k, i5D[k]);
+                i6[0][k] += i5S[k];
+                i5S[k] = i5D[k] = Acc(0);
+              }
+              if (l6 == 2) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                  for (int k = 0; k < 4; ++k) {
+                    tile_put<kNT>(o, tid, 1024 * q + 256 * k, i6[q][k]);
+                    i6[q][k] = Acc(0);
+                  }
+              }
+            }
+            lds_barrier();
+          });
+        }
+      }
+    }
+  }
+}
+
+// Row totals: where the parts of basis row group g = b / rows are.  per_block > 0: part
+// g + w for every block w of the counts pass that held one of the group's `runs` tiles;
+// else parts g * runs .. + runs - 1.  seg_row: words between the parts of the nseg segments.
+struct RowCheck {
+  const uint32_t* rowpart;
+  int64_t rows, runs, per_block, nbases;
+  const uint32_t* nb;
+  uint64_t shots;
+  uint32_t* flags;
+  int nseg;
+  int64_t seg_row;
+};
+
+__device__ __forceinline__ void check_row_total(const RowCheck& c, int64_t b) {
+  const int64_t g = (uint32_t)b / (uint32_t)c.rows, j = (uint32_t)b % (uint32_t)c.rows;
+  int64_t p0 = g * c.runs, p1 = p0 + c.runs;
+  if (c.per_block > 0) {
+    const uint32_t w0 = (uint32_t)p0 / (uint32_t)c.per_block, w1 = (uint32_t)(p1 - 1) / (uint32_t)c.per_block;
+    p0 = g + w0;
+    p1 = g + w1 + 1;
+  }
+  uint64_t tot = 0;
+  for (int s = 0; s < c.nseg; ++s)
+    for (int64_t p = p0; p < p1; ++p) tot += c.rowpart[s * c.seg_row + p * c.rows + j];
+  const uint64_t want = c.shots ? c.shots : (uint64_t)c.nb[b];
+  if (tot != want) atomicOr(c.flags, (uint32_t)FLAG_SHOTS);
+  if (!c.shots && want == 0) atomicOr(c.flags, (uint32_t)FLAG_EMPTY);
+}
+
+static __global__ __launch_bounds__(256) void check_rows_kernel(RowCheck c) {
+  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (b < c.nbases) check_row_total(c, b);
+}
+
+// ---------------------------------------------------------------------------------
+// Later pass folding F <= 4 qubits without atomics: a thread folds the two lowest of the F
+// for one column and one (letters, outcomes) of the others (36 loads, all independent),
+// the 6^(F-2) x 16 values of a column meet in LDS and a thread per (column, code) folds
+// the rest.  COLS consecutive columns a_l per block.  Blocks from fold_blocks on check the
+// row totals instead (launched with the pass: one launch less for a small instance).
+template <int F>
+struct FoldTailGeom {
+  static constexpr int COLS = F == 4 ? 16 : (F == 3 ? 32 : 64);
+  static constexpr int SUB = F <= 2 ? 1 : (F == 3 ? 6 : 36);   // threads per column
+  static constexpr int THREADS = COLS * SUB;
+};
+
+template <int F, typename Tin, typename Acc, Out MODE>
+__global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
+    const Tin* __restrict__ in, void* __restrict__ out, int n, int h, int l, uint64_t shots, int64_t fold_blocks,
+    int64_t seg_in, int64_t seg_out, RowCheck chk) {
+  using G = FoldTailGeom<F>;
+  constexpr int COLS = G::COLS, F1 = F < 2 ? F : 2, N1 = 1 << (2 * F1);
+  const int tid = threadIdx.x;
+  if ((int64_t)blockIdx.x >= fold_blocks) {
+    const int64_t b = ((int64_t)blockIdx.x - fold_blocks) * G::THREADS + tid;
+    if (b < chk.nbases) check_row_total(chk, b);
+    return;
+  }
+  in += blockIdx.y * seg_in;
+  const int64_t L = (int64_t)1 << (2 * l);
+  const int64_t per_outer = L / COLS;
+  const int64_t bs = blockIdx.x / per_outer;
+  const int64_t a_l = (blockIdx.x % per_outer) * COLS + tid % COLS;
+  const int q = tid / COLS;
+  const int64_t rowstride = ((int64_t)1 << h) * L;
+
+  // Final value of folded code a: divided by 3^(n-w) (and the shots) unless partial.
+  const int wl = MODE == Out::Partial ? 0 : pauli_weight((uint64_t)a_l);
+  auto put = [&](int a, Acc v) __attribute__((always_inline)) {
+    if constexpr (MODE == Out::Partial) {
+      static_cast<Acc*>(out)[blockIdx.y * seg_out + ((bs << (2 * F)) + a) * L + a_l] = v;
+    } else {
+      const int64_t i = (int64_t)a * L + a_l;
+      const int w = wl + pauli_weight((uint64_t)a);
+      if constexpr (MODE == Out::CoefUniform)
+        static_cast<double*>(out)[i] = acc_to_double(v) / (pow3d(n - w) * (double)shots);
+      else if constexpr (MODE == Out::CoefPerBasis) static_cast<double*>(out)[i] = acc_to_double(v) / pow3d(n - w);
+      else static_cast<int64_t*>(out)[i] = acc_to_i64(v);
+    }
+  };
+
+  const int dq = q >> (F > 2 ? F - 2 : 0), sq = q & ((1 << (F > 2 ? F - 2 : 0)) - 1);
+  const Tin* __restrict__ p =
+      in + fold_in_offset<F>(h, l, (bs << (2 * l)) + a_l, dq * (int)ipow3(F1), sq << F1);
+  Acc o[N1];
+#pragma unroll
+  for (int a = 0; a < N1; ++a) o[a] = Acc(0);
+  StaticFor<0, (int)ipow3(F1)>::run([&](auto bc) __attribute__((always_inline)) {
+    constexpr int beta = decltype(bc)::value;
+    Acc x[1 << F1];
+#pragma unroll
+    for (int sg = 0; sg < (1 << F1); ++sg) x[sg] = in_to_acc<Tin, Acc>(p[beta * rowstride + sg * L]);
+    wht_regs<F1>(x);
+    StaticFor<0, (1 << F1)>::run([&](auto mc) __attribute__((always_inline)) {
+      constexpr int m = decltype(mc)::value;
+      constexpr int a = fold_index(beta, m, F1);
+      o[a] += x[m];
+    });
+  });
+  if constexpr (F <= 2) {
+#pragma unroll
+    for (int a = 0; a < N1; ++a) put(a, o[a]);
+  } else {
+    __shared__ Acc mid[G::SUB * 16 * COLS];
+    const int col = tid % COLS;
+#pragma unroll
+    for (int a = 0; a < 16; ++a) mid[(q * 16 + a) * COLS + col] = o[a];
+    __syncthreads();
+    for (int t = tid; t < 16 * COLS; t += G::THREADS) {        // column t % COLS = tid % COLS
+      const int code = t / COLS;
+      const Acc* __restrict__ m0 = mid + code * COLS + col;
+      constexpr int F2 = F - 2, N2 = 1 << (2 * F2);
+      Acc r[N2];
+#pragma unroll
+      for (int a = 0; a < N2; ++a) r[a] = Acc(0);
+      StaticFor<0, (int)ipow3(F2)>::run([&](auto bc) __attribute__((always_inline)) {
+        constexpr int beta = decltype(bc)::value;
+        Acc x[1 << F2];
+#pragma unroll
+        for (int sg = 0; sg < (1 << F2); ++sg) x[sg] = m0[(((beta << F2) | sg) * 16) * COLS];
+        wht_regs<F2>(x);
+        StaticFor<0, (1 << F2)>::run([&](auto mc) __attribute__((always_inline)) {
+          constexpr int m = decltype(mc)::value;
+          constexpr int a = fold_index(beta, m, F2);
+          r[a] += x[m];
+        });
+      });
+#pragma unroll
+      for (int a = 0; a < N2; ++a) put(code + 16 * a, r[a]);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------
+// Totals of `rows` consecutive rows of 2^lrow counts (lrow >= 3): 2^LR lanes per row, R
+// rows per lane group with all their loads issued before any is summed.
+template <int LR, int R>
+__global__ __launch_bounds__(256) void row_sums_kernel(const uint16_t* __restrict__ counts, int lrow, int64_t rows,
+                                                       uint32_t* __restrict__ nb) {
+  constexpr int LPR = 1 << LR, GROUPS = 256 / LPR;
+  const int lane = threadIdx.x % LPR, grp = threadIdx.x / LPR;
+  const int per = 1 << (lrow - 3 - LR);                       // 16-byte loads per lane and row
+  const int64_t b0 = ((int64_t)blockIdx.x * GROUPS + grp) * R;
+  const tile_u32x4* __restrict__ base = reinterpret_cast<const tile_u32x4*>(counts);
+  uint32_t sum[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) sum[r] = 0;
+  for (int k = 0; k < per; k += 2) {
+    tile_u32x4 w[R][2];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        w[r][j] = (b0 + r < rows && k + j < per)
+                      ? __builtin_nontemporal_load(base + ((b0 + r) << (lrow - 3)) + (k + j) * LPR + lane)
+                      : tile_u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[r] += (w[r][j][e] & 0xFFFFu) + (w[r][j][e] >> 16);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+#pragma unroll
+    for (int o = LPR / 2; o > 0; o >>= 1) sum[r] += __shfl_xor(sum[r], o, 64);
+    if (lane == 0 && b0 + r < rows) nb[b0 + r] = sum[r];
+  }
+}
+
+// ---------------------------------------------------------------------------------
+// An instance of N <= 5 qubits in one workgroup and one launch: a thread per basis row
+// sums, checks and transforms its row (2^N counts in registers), the identity letters are
+// summed qubit by qubit in place in LDS, and the coefficients, divided, go to memory and to
+// step (ii).  Sums are held in binary64; with uniform shots they are integers below 2^53,
+// so the coefficients are the same correctly rounded quotients as on the other paths.
+// MODE: what `out` receives (PauliT: no rho).
+template <int N, bool PB, Out MODE, bool RHO, typename OutT>
+__global__ __launch_bounds__(256) void small_estimate_kernel(const uint16_t* __restrict__ counts, uint64_t shots,
+                                                             const uint32_t* __restrict__ nb_in,
+                                                             void* __restrict__ out, void* __restrict__ rho,
+                                                             uint32_t* __restrict__ flags) {
+  constexpr int B = (int)ipow3(N), D = 1 << N, NA = 1 << (2 * N), DP = D + 1;
+  // the rows' sums, then step (ii)'s two planes
+  constexpr int NSUM = B * DP > 2 * RhoLowLds<N>::SIZE ? B * DP : 2 * RhoLowLds<N>::SIZE;
+  __shared__ double S[NSUM];
+  __shared__ double E[RHO ? NA : 1];
+  const int tid = threadIdx.x;
+  if (tid < B) {
+    int32_t x[D];
+    const uint32_t* __restrict__ p = reinterpret_cast<const uint32_t*>(counts) + tid * (D / 2);
+    if constexpr (D >= 8) {
+#pragma unroll
+      for (int k = 0; k < D / 8; ++k) {
+        const uint4 u = reinterpret_cast<const uint4*>(p)[k];
+        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+        unpack_raw<8>(w, x + 8 * k);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < D / 2; ++k) {
+        const uint32_t u = p[k];
+        x[2 * k] = (int32_t)(u & 0xffffu);
+        x[2 * k + 1] = (int32_t)(u >> 16);
+      }
+    }
+    wht_regs<N>(x);
+    const uint32_t tot = (uint32_t)x[0];
+    double inv = 1.0;
+    if constexpr (PB) {
+      const uint32_t want = nb_in ? nb_in[tid] : tot;
+      if (tot != want) atomicOr(flags, (uint32_t)FLAG_SHOTS);
+      if (want == 0) atomicOr(flags, (uint32_t)FLAG_EMPTY);
+      inv = want ? 1.0 / (double)want : 0.0;
+    } else {
+      if ((uint64_t)tot != shots) atomicOr(flags, (uint32_t)FLAG_SHOTS);
+    }
+#pragma unroll
+    for (int m = 0; m < D; ++m) S[tid * DP + m] = PB ? (double)x[m] * inv : (double)x[m];
+  }
+  __syncthreads();
+  // Identity letter of qubit k: rows with letter 0 there collect the other two letters',
+  // for the Walsh indices even in bit k.
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    constexpr int I = (B / 3) * (D / 2);
+    const int p3 = (int)ipow3(k);
+    for (int t = tid; t < I; t += 256) {
+      const int mi = t % (D / 2), bi = t / (D / 2);
+      const int m = ((mi >> k) << (k + 1)) | (mi & ((1 << k) - 1));
+      const int b = (bi / p3) * 3 * p3 + bi % p3;
+      S[b * DP + m] += S[(b + p3) * DP + m] + S[(b + 2 * p3) * DP + m];
+    }
+    __syncthreads();
+  }
+  for (int a = tid; a < NA; a += 256) {
+    int b = 0, m = 0;
+#pragma unroll
+    for (int k = N - 1; k >= 0; --k) {
+      const int d = (a >> (2 * k)) & 3;
+      b = 3 * b + (d ? d - 1 : 0);
+      m = 2 * m + (d != 0);
+    }
+    const double v = S[b * DP + m];
+    const int w = pauli_weight((uint64_t)a);
+    if constexpr (MODE == Out::PauliT) {
+      static_cast<int64_t*>(out)[a] = (int64_t)v;
+    } else {
+      const double e = MODE == Out::CoefUniform ? v / (pow3d(N - w) * (double)shots) : v / pow3d(N - w);
+      static_cast<double*>(out)[a] = e;
+      if constexpr (RHO) E[a] = e;
+    }
+  }
+  if constexpr (RHO) {
+    __syncthreads();                       // S is dead, E complete
+    rho_low_block<N, true, OutT, 256>(E, rho, N, 0, tid, S, S + RhoLowLds<N>::SIZE);
+  }
+}
+
+}  // namespace lre

@@ -26,7 +26,8 @@ import re
 import statistics
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-KERNEL_SOURCES = ("paper_1602_08604_amd/csrc/lre_kernels.hpp", "paper_1602_08604_amd/csrc/lre_abi.hip")
+KERNEL_SOURCES = ("paper_1602_08604_amd/csrc/lre_kernels.hpp", "paper_1602_08604_amd/csrc/lre_tile.hpp",
+                  "paper_1602_08604_amd/csrc/lre_abi.hip")
 BATCH_SOURCES = KERNEL_SOURCES + ("paper_1602_08604_amd/csrc/lre_batch.hip",)
 
 
