@@ -167,18 +167,18 @@ lre_status lre_signed_sums(lre_ctx* ctx, int n, const uint16_t* counts, const in
  * lre_estimate returns for it (steps (i) and (ii), Sec. II eqs. 3-4): the same
  * kernels' arithmetic, bit-identical coefficients and rho.
  *
- * lre_batch_plan builds a work list (an instance of n <= 7 qubits is one item; a larger
+ * A plan runs in one of two forms (lre_batch_tiles.staged).  Staged (a new plan's form): one
+ * launch per stage over all instances -- row sums, counts passes over a table of tiles,
+ * instances of at most 5 qubits, the remaining folds with the row check, step (ii) -- in
+ * stream order.  Unstaged: a work list (an instance of n <= 7 qubits is one item; a larger
  * one is split into its counts-pass row groups, later pass and step-(ii) blocks, in
- * dependency order) and uploads it.  lre_batch_run enqueues a fill kernel that clears the
- * item and dependency counters in the workspace, then one persistent kernel whose
- * workgroups take items from the list in order; an item that needs the results of
- * earlier items waits for their counters (a bounded wait: on expiry the item is
- * skipped and LRE_E_TIMEOUT is raised through lre_check).  For a plan with instances
- * of 7 or more qubits it then enqueues the staged form's fold and step-(ii) kernels,
- * which return at once unless the plan's shape is staged (lre_batch_tiles.staged), so
- * that a captured run replays correctly after lre_batch_set_tiles or lre_batch_tune.
- * lre_batch_run makes no allocation, copy or memset and may be captured into a HIP
- * graph.
+ * dependency order); lre_batch_run enqueues a fill kernel that clears the item and
+ * dependency counters in the workspace, then one persistent kernel whose workgroups take
+ * items from the list in order; an item that needs the results of earlier items waits for
+ * their counters (a bounded wait: on expiry the item is skipped and LRE_E_TIMEOUT is raised
+ * through lre_check).  lre_batch_run makes no allocation, copy or memset and may be captured
+ * into a HIP graph; a captured run keeps the form it was captured in and stays valid after
+ * lre_batch_set_tiles or lre_batch_tune.
  */
 #define LRE_BATCH_MAX_QUBITS 9
 
@@ -202,7 +202,8 @@ typedef struct {
   int workers_per_cu;   /* persistent workgroups per compute unit: 1 or 2 */
   int counts_tiles;     /* counts-pass row groups (3^7 rows, all their outcomes) per item at
                            most, >= 1; an instance's groups are split into that many items
-                           of equal size (to one group) */
+                           of equal size (to one group).  Staged: tiles per counts-pass
+                           workgroup at most */
   int fold_cols;        /* later-pass columns per item at most, multiple of 432 (split as
                            evenly as counts_tiles) */
   int rho_blocks;       /* step-(ii) work per item, >= 1: high-qubit row patterns x_hi
@@ -210,21 +211,17 @@ typedef struct {
   int interleave;       /* 0: stage by stage, largest instances first;
                            1: instance by instance (all stages of an instance together) */
   int staged;           /* 0: every stage in the persistent kernel's work list;
-                           1: the list holds the per-basis totals, the counts pass and the
-                           instances of at most 7 qubits (step (ii) of those of exactly 7
-                           excepted), and the later fold and step (ii) follow as two
-                           kernels of their own (one thread per column; one block per
-                           step-(ii) unit), in stream order; fold_cols, rho_blocks and
-                           interleave then do not matter */
+                           1: a launch per stage (see above); workers_per_cu, fold_cols,
+                           rho_blocks and interleave then do not matter */
 } lre_batch_tiles;
 
 typedef struct lre_batch lre_batch;
 
 /* Plan a batch of `count` instances (count >= 1).  flags: LRE_NO_RHO | LRE_RHO_FP32
  * (applied to every instance).  The instance array is copied; the buffers it points
- * to must stay valid while the plan is used.  Allocates the device work list (once:
- * lre_batch_set_tiles and lre_batch_tune reuse it).
- * A plan with a per-basis instance (shots == 0) runs one workgroup per compute unit
+ * to must stay valid while the plan is used.  Allocates the device work list and the staged
+ * form's tables (once: lre_batch_set_tiles and lre_batch_tune reuse them).
+ * Unstaged, a plan with a per-basis instance (shots == 0) runs one workgroup per compute unit
  * (its binary64 accumulators fill the LDS), whatever workers_per_cu says.
  * Errors: LRE_E_ARG (bad instance: n < 1, pointer, alignment, shots too large),
  * LRE_E_UNSUPPORTED (n > LRE_BATCH_MAX_QUBITS), LRE_E_HIP. */
@@ -235,20 +232,21 @@ lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uin
  * intermediate buffers); 0 for a NULL plan. */
 size_t lre_batch_workspace_bytes(const lre_batch* plan);
 
-/* Replace the plan's work-item shape and rebuild its work list (synchronous: waits
- * for the device to be idle, then uploads).  The list keeps its device address for
- * the plan's lifetime (it is allocated once by lre_batch_plan, at the length of the
- * longest shape) and the persistent kernel reads the item count from device memory,
- * so an lre_batch_run captured into a HIP graph before a retune stays valid: its
- * replays run the current list (with the grid and per-CU worker count of the
- * captured launch).  Errors: LRE_E_ARG for out-of-range fields, LRE_E_HIP. */
+/* Replace the plan's work-item shape.  To an unstaged shape: rebuilds the work list
+ * (synchronous: waits for the device to be idle, then uploads).  The list keeps its device
+ * address for the plan's lifetime (it is allocated once by lre_batch_plan, at the length of
+ * the longest shape) and the persistent kernel reads the item count from device memory, so an
+ * unstaged lre_batch_run captured into a HIP graph before a retune stays valid: its replays
+ * run the current list (with the grid and per-CU worker count of the captured launch).  The
+ * staged form's tables do not depend on the shape.  Errors: LRE_E_ARG for out-of-range
+ * fields, LRE_E_HIP. */
 lre_status lre_batch_set_tiles(lre_batch* plan, const lre_batch_tiles* tiles);
 
-/* The plan's current work-item shape and work-item count. */
+/* The plan's current work-item shape and work-item count (staged: workgroups). */
 lre_status lre_batch_get_tiles(const lre_batch* plan, lre_batch_tiles* tiles, int* num_items);
 
 /* Autotuner: runs the batch (lre_batch_run) for each of 82 candidate work-item shapes
- * (72 unstaged and 10 staged; 41 for a plan with per-basis instances, which run one
+ * (72 unstaged and 10 staged; 41 for a plan with per-basis instances, whose list runs one
  * workgroup per CU),
  * `reps` timed runs each after one warm-up, keeps the fastest shape and returns its
  * mean time in *best_ms (may be NULL).  Synchronous on `stream`; overwrites the

@@ -386,11 +386,11 @@ void launch_rho_real(const double* coef, void* rho, hipStream_t st) {
 template <typename OutT>
 void launch_rho(const Plan& P, const double* coef, void* rho, char* ws, hipStream_t st) {
   const int n = P.n;
-  if (n <= kRhoJ) {
+  if (n < kRhoJ) {
     switch (n) {
 #define LRE_RHO_SMALL(J) \
   case J: hipLaunchKernelGGL((rho_low_kernel<J, true, OutT>), dim3(1), dim3(256), 0, st, coef, rho, n); break;
-      LRE_RHO_SMALL(1) LRE_RHO_SMALL(2) LRE_RHO_SMALL(3) LRE_RHO_SMALL(4) LRE_RHO_SMALL(5) LRE_RHO_SMALL(6)
+      LRE_RHO_SMALL(1) LRE_RHO_SMALL(2) LRE_RHO_SMALL(3) LRE_RHO_SMALL(4) LRE_RHO_SMALL(5)
 #undef LRE_RHO_SMALL
     }
     return;
@@ -399,6 +399,7 @@ void launch_rho(const Plan& P, const double* coef, void* rho, char* ws, hipStrea
     // up to 4 high qubits: units (x_hi, 8 x_lo) from coefficients to mu in LDS
     const dim3 grid((unsigned)((int64_t)8 << (n - kRhoJ)));
     switch (n - kRhoJ) {
+      case 0: hipLaunchKernelGGL((rho_tile_kernel<0, OutT>), grid, dim3(512), 0, st, coef, rho); break;
       case 1: hipLaunchKernelGGL((rho_tile_kernel<1, OutT>), grid, dim3(512), 0, st, coef, rho); break;
       case 2: hipLaunchKernelGGL((rho_tile_kernel<2, OutT>), grid, dim3(512), 0, st, coef, rho); break;
       case 3: hipLaunchKernelGGL((rho_tile_kernel<3, OutT>), grid, dim3(512), 0, st, coef, rho); break;
@@ -567,7 +568,7 @@ lre_status run_step1(lre_ctx* ctx, const Plan& P, const uint16_t* counts, uint64
   io.bufA = ws + P.off_a;
   io.bufB = ws + P.off_b;
   io.chk = RowCheck{io.rowpart, ipow3(P.q1), P.runs, P.per_block, nbases, io.nb,
-                    P.per_basis ? (uint64_t)0 : shots, ctx->flags, 1, 0};
+                    P.per_basis ? (uint64_t)0 : shots, ctx->flags, 1, 0, 0, 0};
   return run_passes(ctx, P, io, shots, fm, st);
 }
 
@@ -832,7 +833,7 @@ lre_status stream_slab(lre_stream* S, int64_t slab, const uint16_t* counts, cons
     if (s != LRE_OK) return s;
   }
   const RowCheck chk{reinterpret_cast<const uint32_t*>(ws + S->off_rowpart), ipow3(P.q1), P.runs, P.per_block, nbases,
-                     io.nb, P.per_basis ? (uint64_t)0 : S->shots, S->ctx->flags, 1 << h, io.seg_row};
+                     io.nb, P.per_basis ? (uint64_t)0 : S->shots, S->ctx->flags, 1 << h, io.seg_row, 0, 0};
   hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)((nbases + 255) / 256)), dim3(256), 0, st, chk);
   // Letters of the top qubits: digit p of the slab index (base 3) is qubit h - p.
   uint32_t atop = 0;

@@ -1,21 +1,23 @@
 // lre_batch.hip -- batched estimation (lre_batch_* in include/lre.h): many independent
-// instances of steps (i) and (ii) in one persistent kernel driven by a work list.
+// instances of steps (i) and (ii), by the single-instance kernels' device functions
+// (lre_kernels.hpp, lre_tile.hpp), in one of two forms.
 //
-// An instance of at most 7 qubits is one counts-pass tile: one work item runs it from
-// the counts to rho inside one workgroup (the phases ordered by workgroup barriers).
-// A larger instance is cut into items per stage -- counts-pass tiles, the row-total
-// check, the later fold pass, step (ii) per group of x_hi row patterns --
-// the same per-block device functions the single-instance kernels run
-// (lre_kernels.hpp).  The host lists the items so that an item only ever depends on
-// items listed before it.  Each persistent workgroup takes the next item (one atomic
-// counter), waits until the items it depends on have finished (per-instance, per-stage
-// completion counters, agent-scope acquire), runs it and, when a later item consumes
-// its output, releases it and bumps its stage's counter.  Items are taken in list
-// order by running workgroups, so every item waited for has already been taken by a
-// running workgroup and every wait ends; the wait is bounded anyway (FLAG_WAIT) so
-// that no wave can spin forever.  In the staged form the list stops after the counts
-// pass and two kernels of their own run the later folds and step (ii) (see
-// batch_fold_kernel).
+// Staged (a new plan's form, batch_tiles_kernel and its neighbours below): one launch per stage
+// over all instances.  512 uniform-shot instances of 3 to 9 qubits take 0.63 ms (the work list
+// 0.79 at its best shape, 0.94 at its first), 40 of 5 to 9 qubits with totals from the rows
+// 0.13 (0.71).
+//
+// Unstaged: one persistent kernel driven by a work list.  An instance of at most 7 qubits is
+// one counts-pass tile: one work item runs it from the counts to rho inside one workgroup (the
+// phases ordered by workgroup barriers).  A larger instance is cut into items per stage --
+// counts-pass tiles, the row-total check, the later fold pass, step (ii) per group of x_hi
+// row patterns.  The host lists the items so that an item only ever depends on items listed
+// before it.  Each persistent workgroup takes the next item (one atomic counter), waits until
+// the items it depends on have finished (per-instance, per-stage completion counters,
+// agent-scope acquire), runs it and, when a later item consumes its output, releases it and
+// bumps its stage's counter.  Items are taken in list order by running workgroups, so every
+// item waited for has already been taken by a running workgroup and every wait ends; the wait
+// is bounded anyway (FLAG_WAIT) so that no wave can spin forever.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,6 +30,7 @@
 #include "lre.h"
 #include "lre_internal.hpp"
 #include "lre_kernels.hpp"
+#include "lre_tile.hpp"
 
 using namespace lre;
 using lre_detail::aligned;
@@ -113,7 +116,7 @@ __device__ __forceinline__ BInstPB pb_view(const BInst& I) {
 
 constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
 constexpr size_t kLdsCounts = (size_t)StreamGeom<kQ>::NACC * 4 + (size_t)StreamGeom<kQ>::NROWS * 4;
-constexpr size_t kLdsRhoLow = 2 * (size_t)RhoLowLds<kJ>::SIZE * 8;
+constexpr size_t kLdsRhoLow = 2 * (size_t)RhoLowLds<kJ - 1>::SIZE * 8;
 constexpr size_t kLds = cmax(kLdsCounts, kLdsRhoLow);
 static_assert(RhoTileGeom<3>::NV * sizeof(double) <= kLds, "step-(ii) units of n = 9 fit the LDS buffer");
 // per-basis plans: binary64 accumulators (one workgroup per CU)
@@ -132,7 +135,7 @@ __device__ __forceinline__ T* l2p(LRE_LDS char* p) { return (T*)p; }
 template <int Q, typename OutT>
 __device__ __forceinline__ void small_rho(const BInstG& I, int tid, double* re, double* im) {
   const double* coef = (const double*)I.coef;
-  if constexpr (Q <= kJ) {
+  if constexpr (Q < kJ) {
     rho_low_block<Q, true, OutT, kBT>(coef, (void*)g2p(I.rho), I.n, 0, tid, re, im);
   } else {
     rho_tiles<Q - kJ, OutT, kBT>(coef, (void*)g2p(I.rho), 0, (int64_t)8 << (Q - kJ), tid, re);
@@ -465,56 +468,143 @@ __global__ __launch_bounds__(kBT, WORKERS == 2 ? 4 : 1) void batch_kernel(
   }
 }
 
-// Staged form (lre_batch_tiles.staged = 1): the work list holds only the per-basis
-// totals, the counts pass and the instances of at most 7 qubits (those of exactly 7
-// without their step (ii)); the later fold and step (ii) run afterwards, in stream
-// order, as the two kernels below, shaped for their own work (many small workgroups instead of one 7-wave worker
-// per CU).  Both read the plan's form from device memory (stage[1]) and do nothing for
-// an unstaged list, so that a captured launch stays valid whichever shape the plan
-// takes later.  Blocks are persistent (the grid is fixed when the plan is made) and
-// walk their work with a stride of the grid.
+// Staged form (lre_batch_tiles.staged = 1): the single-instance kernels' device functions over
+// all instances at once, one launch per stage, in stream order:
+//   instances of n <= 5 qubits, a workgroup each (batch_small_kernel);
+//   row sums of the per-basis instances without given totals (batch_sums_kernel);
+//   the counts passes over a table of tiles (batch_tiles_kernel), instances of 7 and more
+//     qubits in 7-qubit tiles and 6-qubit ones in 6-qubit tiles, or all in 6-qubit tiles
+//     where the batch has too few of the larger for the chip (staged_level);
+//   the remaining folds and the row check (batch_tail_kernel);
+//   step (ii) (batch_rho_kernel).
+// The tables are made with the plan and do not change with its shape, and no kernel reads the
+// plan's form: a captured run stays valid across lre_batch_set_tiles.
+constexpr int kSmallN = 5;
 
-// The later fold of every instance with n > 7: 4^7 columns per instance, 256 per block
-// (64 blocks per instance), one thread per column, the fold items' column function.
-template <bool PB>
-__global__ __launch_bounds__(256) void batch_fold_kernel(const int* __restrict__ stage,
-                                                         const int32_t* __restrict__ fold_inst, int nblocks,
-                                                         const BInst* __restrict__ insts, char* __restrict__ ws_arg) {
-  if (stage[1] == 0) return;
-  LRE_GLOBAL char* ws = (LRE_GLOBAL char*)ws_arg;
-  for (int b = blockIdx.x; b < nblocks; b += gridDim.x) {
-    const BInst& D = insts[fold_inst[b]];   // 64 consecutive blocks per instance
-    const BInstG I = global_view(D);
-    const int64_t col = ((int64_t)(b & 63) << 8) | threadIdx.x;
-    double* coef = (double*)I.coef;
-    const int F = I.n - kQ;
-    if (PB && I.shots == 0) {
-      const double* in = reinterpret_cast<const double*>(g2p(ws + I.off_part));
-      if (F == 1) fold_partial_col<1, double, double, Out::CoefPerBasis>(in, coef, I.n, 1, kQ, 0, col);
-      else fold_partial_col<2, double, double, Out::CoefPerBasis>(in, coef, I.n, 2, kQ, 0, col);
-    } else {
-      const uint32_t* in = reinterpret_cast<const uint32_t*>(g2p(ws + I.off_part));
-      if (F == 1) fold_partial_col<1, uint32_t, uint32_t, Out::CoefUniform>(in, coef, I.n, 1, kQ, I.shots, col);
-      else fold_partial_col<2, uint32_t, uint32_t, Out::CoefUniform>(in, coef, I.n, 2, kQ, I.shots, col);
-    }
+struct StagedInst {
+  RowCheck chk;                // rowpart and nb: filled in by the kernel from the offsets
+  int64_t off_rowpart;
+  int32_t q, per_block_of;     // qubits folded by the counts pass; index of its pass
+};
+
+template <bool RHO, typename OutT>
+__global__ __launch_bounds__(256) void batch_small_kernel(const int32_t* __restrict__ which,
+                                                          const BInst* __restrict__ insts,
+                                                          uint32_t* __restrict__ flags) {
+  __shared__ double S[SmallLds<kSmallN>::S];
+  __shared__ double E[RHO ? SmallLds<kSmallN>::E : 1];
+  const BInst& D = insts[which[blockIdx.x]];
+  const BInstG I = global_view(D);
+  const uint16_t* counts = (const uint16_t*)I.counts;
+  double* coef = (double*)I.coef;
+  void* rho = (void*)g2p(I.rho);
+  const uint32_t* nb = (const uint32_t*)(const LRE_GLOBAL uint32_t*)D.nb_in;
+  const int tid = threadIdx.x;
+  auto run = [&](auto nc) __attribute__((always_inline)) {
+    constexpr int N = decltype(nc)::value;
+    if (I.shots == 0)
+      small_estimate_block<N, true, Out::CoefPerBasis, RHO, OutT>(counts, 0, nb, coef, rho, flags, tid, S, E);
+    else
+      small_estimate_block<N, false, Out::CoefUniform, RHO, OutT>(counts, I.shots, nullptr, coef, rho, flags, tid, S, E);
+  };
+  switch (I.n) {
+    case 1: run(std::integral_constant<int, 1>{}); break;
+    case 2: run(std::integral_constant<int, 2>{}); break;
+    case 3: run(std::integral_constant<int, 3>{}); break;
+    case 4: run(std::integral_constant<int, 4>{}); break;
+    default: run(std::integral_constant<int, 5>{}); break;
   }
 }
 
-// Step (ii) of every instance with n >= 7: one rho_tiles unit (x_hi, 8 x_lo) per block.
+constexpr int kSumRows = 4;                       // rows per lane group (row_sums_block)
+constexpr int sums_per_block(int n) { return (256 >> (n - 3)) * kSumRows; }
+
+// (instance, block of rows) per workgroup, n in [6, 9].
+static __global__ __launch_bounds__(256) void batch_sums_kernel(const int2* __restrict__ work,
+                                                                const BInst* __restrict__ insts,
+                                                                char* __restrict__ ws) {
+  const int2 w = work[blockIdx.x];
+  const BInst& D = insts[w.x];
+  const BInstG I = global_view(D);
+  const uint16_t* counts = (const uint16_t*)I.counts;
+  uint32_t* nb = reinterpret_cast<uint32_t*>(ws + D.off_nb);
+  const int64_t rows = ipow3(I.n);
+  switch (I.n) {
+    case 6: row_sums_block<3, kSumRows>(counts, 6, rows, nb, w.y); break;
+    case 7: row_sums_block<4, kSumRows>(counts, 7, rows, nb, w.y); break;
+    case 8: row_sums_block<5, kSumRows>(counts, 8, rows, nb, w.y); break;
+    default: row_sums_block<6, kSumRows>(counts, 9, rows, nb, w.y); break;
+  }
+}
+
+// Tiles per block of each counts pass, by value (they follow the shape of the plan).
+struct PassShape {
+  int per_block[4];   // (level 1 or 2) x (integers or binary64)
+};
+
+// Per workgroup (instance, block): block >= 0 of the instance's fold, or -1 - block of its
+// row check (256 rows).  A fold block takes 256 columns (F <= 2 qubits left: a thread per
+// column) or 32 (F = 3, fold_tail_block).
+template <typename Acc, Out MODE>
+__device__ __forceinline__ void batch_tail_fold(const Acc* in, double* coef, int n, int q, uint64_t shots, int blk,
+                                                Acc* mid) {
+  const int64_t col = (int64_t)blk * 256 + threadIdx.x;
+  const int F = n - q;
+  if (F == 0) {
+    const Acc v = in[col];
+    const int w = pauli_weight((uint64_t)col);
+    coef[col] = MODE == Out::CoefUniform ? acc_to_double(v) / (pow3d(n - w) * (double)shots) : acc_to_double(v) / pow3d(n - w);
+  } else if (F == 1) {
+    fold_partial_col<1, Acc, Acc, MODE>(in, coef, n, 1, q, shots, col);
+  } else if (F == 2) {
+    fold_partial_col<2, Acc, Acc, MODE>(in, coef, n, 2, q, shots, col);
+  } else {
+    fold_tail_block<3, Acc, Acc, MODE>(in, coef, n, 3, q, shots, blk, threadIdx.x, mid);
+  }
+}
+
+static __global__ __launch_bounds__(256) void batch_tail_kernel(const int2* __restrict__ work,
+                                                                const BInst* __restrict__ insts,
+                                                                const StagedInst* __restrict__ sinst,
+                                                                char* __restrict__ ws, PassShape shape) {
+  __shared__ double mid[FoldTailGeom<3>::SUB * 16 * FoldTailGeom<3>::COLS];
+  const int2 w = work[blockIdx.x];
+  const BInst& D = insts[w.x];
+  const BInstG I = global_view(D);
+  const StagedInst& X = sinst[w.x];
+  if (w.y < 0) {
+    const int64_t b = (int64_t)(-1 - w.y) * 256 + threadIdx.x;
+    RowCheck c = X.chk;
+    c.rowpart = reinterpret_cast<const uint32_t*>(ws + X.off_rowpart);
+    c.per_block = shape.per_block[X.per_block_of];
+    if (I.shots == 0) c.nb = D.nb_in ? D.nb_in : reinterpret_cast<const uint32_t*>(ws + D.off_nb);
+    if (b < c.nbases) check_row_total(c, b);
+    return;
+  }
+  double* coef = (double*)I.coef;
+  if (I.shots == 0)
+    batch_tail_fold<double, Out::CoefPerBasis>(reinterpret_cast<const double*>(ws + I.off_part), coef, I.n, X.q, 0, w.y,
+                                               mid);
+  else
+    batch_tail_fold<uint32_t, Out::CoefUniform>(reinterpret_cast<const uint32_t*>(ws + I.off_part), coef, I.n, X.q,
+                                                I.shots, w.y, reinterpret_cast<uint32_t*>(mid));
+}
+
+// Step (ii) of every instance with n >= 6: one rho_tiles unit (x_hi, 8 x_lo) per workgroup.
 template <typename OutT>
-__global__ __launch_bounds__(256) void batch_rho_kernel(const int* __restrict__ stage, const int2* __restrict__ units,
-                                                        int nblocks, const BInst* __restrict__ insts) {
+__global__ __launch_bounds__(256) void batch_rho_kernel(const int2* __restrict__ units,
+                                                        const BInst* __restrict__ insts) {
   __shared__ double V[RhoTileGeom<3>::NV];
-  if (stage[1] == 0) return;
-  for (int b = blockIdx.x; b < nblocks; b += gridDim.x) {
-    const int2 w = units[b];
-    const BInstG I = global_view(insts[w.x]);
-    const double* coef = (const double*)I.coef;
-    void* rho = (void*)g2p(I.rho);
-    if (I.n == kJ + 1) rho_tiles<1, OutT, 256>(coef, rho, w.y, (int64_t)w.y + 1, threadIdx.x, V);
-    else if (I.n == kJ + 2) rho_tiles<2, OutT, 256>(coef, rho, w.y, (int64_t)w.y + 1, threadIdx.x, V);
-    else rho_tiles<3, OutT, 256>(coef, rho, w.y, (int64_t)w.y + 1, threadIdx.x, V);
-    lds_barrier();  // the next unit's staging overwrites V
+  const int2 w = units[blockIdx.x];
+  const BInstG I = global_view(insts[w.x]);
+  const double* coef = (const double*)I.coef;
+  void* rho = (void*)g2p(I.rho);
+  const int64_t u = w.y;
+  switch (I.n) {
+    case 6: rho_tiles<0, OutT, 256>(coef, rho, u, u + 1, threadIdx.x, V); break;
+    case 7: rho_tiles<1, OutT, 256>(coef, rho, u, u + 1, threadIdx.x, V); break;
+    case 8: rho_tiles<2, OutT, 256>(coef, rho, u, u + 1, threadIdx.x, V); break;
+    default: rho_tiles<3, OutT, 256>(coef, rho, u, u + 1, threadIdx.x, V); break;
   }
 }
 
@@ -528,6 +618,15 @@ struct InstMeta {
   int64_t counts = 0;           // 6^n, the ordering key
 };
 
+// A counts pass of the staged form: the tiles of every instance of one level and kind.
+struct TilePass {
+  int lv = 0;
+  bool pb = false;
+  int tiles = 0;
+  TileEntry* d_table = nullptr;
+  int64_t off_rowpart = 0;
+};
+
 }  // namespace
 
 struct lre_batch {
@@ -539,11 +638,13 @@ struct lre_batch {
   lre_batch_tiles tiles{};
   BInst* d_inst = nullptr;
   BItem* d_items = nullptr;     // work list, allocated once at the largest list any
-  int* d_nitems = nullptr;      // shape can give (fixed addresses for captured runs);
-                                // [0] item count, [1] staged form
-  int32_t* d_fold = nullptr;    // staged form: instance of each fold block (64 per
-  int2* d_units = nullptr;      // instance of n > 7) and (instance, unit) of each rho block
-  int nfold = 0, nunits = 0;
+  int* d_nitems = nullptr;      // shape can give (fixed addresses for captured runs)
+  // staged form: counts passes and, per block of its other kernels, what the block does
+  std::vector<TilePass> passes;
+  StagedInst* d_sinst = nullptr;
+  int32_t* d_small = nullptr;   // instances of n <= 5
+  int2 *d_sums = nullptr, *d_tail = nullptr, *d_units = nullptr;
+  int nsmall = 0, nsums = 0, ntail = 0, nunits = 0;
   size_t items_cap = 0;
   int nitems = 0;
   size_t ctl_bytes = 0;
@@ -600,10 +701,8 @@ void emit_stage(const lre_batch& B, const lre_batch_tiles& t, int j, int stage, 
   const uint8_t pb = m.pb ? V_PB : 0;
   const int32_t c_counts = 1 + 3 * j, c_fold = 2 + 3 * j, c_tot = 3 + 3 * j;
   if (m.n <= kQ) {  // one tile: the whole instance is one item
-    // (staged: step (ii) of a 7-qubit instance runs in the step-(ii) kernel instead)
-    const bool rho_here = want_rho && !(t.staged && m.n == kQ);
     if (stage == 0)
-      add_range(out, j, K_SMALL, (uint8_t)(mad | fp32 | pb | (rho_here ? V_RHO : 0)), 1, 1, -1, 0, -1, nullptr);
+      add_range(out, j, K_SMALL, (uint8_t)(mad | fp32 | pb | (want_rho ? V_RHO : 0)), 1, 1, -1, 0, -1, nullptr);
     return;
   }
   switch (stage) {
@@ -634,26 +733,17 @@ std::vector<BItem> list_items(const lre_batch& B, const lre_batch_tiles& t) {
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B.meta[a].counts > B.meta[b].counts; });
   std::vector<BItem> items;
   std::vector<StageCounts> sc(count);
-  const int stages = t.staged ? 2 : kStages;   // staged: folds and step (ii) run as kernels of their own
   if (t.interleave) {
     for (int j : order)
-      for (int s = 0; s < stages; ++s) emit_stage(B, t, j, s, items, sc[j]);
-  } else if (t.staged) {
-    // the long counts-pass items first, the one-item instances (n <= 7) after them to
-    // fill the end of the launch, largest first
-    for (int s = 0; s < stages; ++s)
-      for (int j : order)
-        if (B.meta[j].n > kQ) emit_stage(B, t, j, s, items, sc[j]);
-    for (int j : order)
-      if (B.meta[j].n <= kQ) emit_stage(B, t, j, 0, items, sc[j]);
+      for (int s = 0; s < kStages; ++s) emit_stage(B, t, j, s, items, sc[j]);
   } else {
-    for (int s = 0; s < stages; ++s)
+    for (int s = 0; s < kStages; ++s)
       for (int j : order) emit_stage(B, t, j, s, items, sc[j]);
   }
   return items;
 }
 
-// Upload the list of the plan's current shape into the fixed device list.
+// Upload the list of the plan's current unstaged shape into the fixed device list.
 lre_status rebuild(lre_batch& B) {
   const std::vector<BItem> items = list_items(B, B.tiles);
   if (items.size() > B.items_cap) return LRE_E_UNSUPPORTED;  // the capacity is the largest list
@@ -664,33 +754,199 @@ lre_status rebuild(lre_batch& B) {
   if (!items.empty() &&
       hipMemcpy(B.d_items, items.data(), items.size() * sizeof(BItem), hipMemcpyHostToDevice) != hipSuccess)
     return LRE_E_HIP;
-  const int hdr[2] = {(int)items.size(), B.tiles.staged};
-  if (hipMemcpy(B.d_nitems, hdr, sizeof hdr, hipMemcpyHostToDevice) != hipSuccess) return LRE_E_HIP;
-  const int cnt = hdr[0];
+  const int cnt = (int)items.size();
+  if (hipMemcpy(B.d_nitems, &cnt, sizeof cnt, hipMemcpyHostToDevice) != hipSuccess) return LRE_E_HIP;
   B.nitems = cnt;
   return LRE_OK;
 }
 
-// The staged form's fold and step-(ii) kernels (they return at once for an unstaged
-// list; see batch_fold_kernel).
-void launch_staged(const lre_batch& B, char* ws, hipStream_t st) {
-  if (B.nfold) {
-    const unsigned grid = (unsigned)std::min(B.nfold, B.num_cu * 8);
-    if (B.pb)
-      hipLaunchKernelGGL((batch_fold_kernel<true>), dim3(grid), dim3(256), 0, st, (const int*)B.d_nitems,
-                         (const int32_t*)B.d_fold, B.nfold, (const BInst*)B.d_inst, ws);
-    else
-      hipLaunchKernelGGL((batch_fold_kernel<false>), dim3(grid), dim3(256), 0, st, (const int*)B.d_nitems,
-                         (const int32_t*)B.d_fold, B.nfold, (const BInst*)B.d_inst, ws);
+// ---- staged form: plan and launches
+
+// Qubits the counts pass folds of an instance of n > kSmallN under level lv.
+int staged_qubits(int n, int lv) { return lv == 2 && n >= 7 ? 7 : 6; }
+
+// Workgroups of the tiles kernel the device holds at once (TileLds: one per CU in binary64,
+// two for integers).
+int tile_slots(int num_cu, bool pb) { return pb ? num_cu : 2 * num_cu; }
+
+// Level of the counts passes.  7-qubit tiles write a third less than 6-qubit ones and leave
+// shorter folds, but are six times the work each (18 sub-tiles against 3): they are taken
+// unless rounding their number up to whole rounds of the chip's workgroups costs more than
+// the extra partials (15 % of the counts pass).
+int staged_level(const lre_instance* inst, int count, int num_cu) {
+  int64_t tiles[2][2] = {{0, 0}, {0, 0}};   // [level - 1][per-basis]
+  for (int j = 0; j < count; ++j) {
+    const int n = inst[j].n;
+    if (n <= kSmallN) continue;
+    tiles[0][inst[j].shots == 0] += ipow3(n - 6) << (n - 6);
+    if (n > 6) tiles[1][inst[j].shots == 0] += ipow3(n - 7) << (n - 7);
   }
-  if (B.nunits) {
-    const unsigned grid = (unsigned)std::min(B.nunits, B.num_cu * 4);
-    if (B.flags & LRE_RHO_FP32)
-      hipLaunchKernelGGL((batch_rho_kernel<float>), dim3(grid), dim3(256), 0, st, (const int*)B.d_nitems,
-                         (const int2*)B.d_units, B.nunits, (const BInst*)B.d_inst);
+  auto steps = [&](int lv) {
+    int64_t s = 0;
+    for (int pb = 0; pb < 2; ++pb) {
+      const int64_t slots = tile_slots(num_cu, pb != 0);
+      s += (tiles[lv - 1][pb] + slots - 1) / slots * (lv == 2 ? 18 : 3);
+    }
+    return s;
+  };
+  return tiles[1][0] + tiles[1][1] > 0 && steps(2) * 100 <= steps(1) * 115 ? 2 : 1;
+}
+
+struct StagedTables {
+  std::vector<std::vector<TileEntry>> tiles;   // per pass
+  std::vector<int32_t> small;
+  std::vector<int2> sums, tail, units;
+};
+
+// Tiles per block of a counts pass under the plan's shape: blocks of at most counts_tiles
+// tiles, in whole rounds of the workgroups the device holds.
+int tiles_per_block(const lre_batch& B, const TilePass& p) {
+  const int64_t slots = tile_slots(B.num_cu, p.pb);
+  const int64_t rounds = std::max<int64_t>(1, (p.tiles + slots * B.tiles.counts_tiles - 1) / (slots * B.tiles.counts_tiles));
+  return (int)std::max<int64_t>(1, (p.tiles + slots * rounds - 1) / (slots * rounds));
+}
+
+// The staged form's passes and tables; `off` (workspace) advances over their row-sum parts.
+void plan_staged(lre_batch& B, int lv, size_t& off, std::vector<StagedInst>& sinst, StagedTables& tab) {
+  const int count = (int)B.inst.size();
+  const bool want_rho = !(B.flags & LRE_NO_RHO);
+  sinst.assign(count, StagedInst{});
+  std::vector<int> order(count);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B.meta[a].counts > B.meta[b].counts; });
+  std::vector<int64_t> groups;
+  auto pass_of = [&](int level, bool pb) {
+    for (size_t k = 0; k < B.passes.size(); ++k)
+      if (B.passes[k].lv == level && B.passes[k].pb == pb) return (int)k;
+    TilePass p;
+    p.lv = level;
+    p.pb = pb;
+    B.passes.push_back(p);
+    tab.tiles.emplace_back();
+    groups.push_back(0);
+    return (int)B.passes.size() - 1;
+  };
+  for (int j : order) {
+    const InstMeta& m = B.meta[j];
+    const BInst& d = B.dinst_host[j];
+    if (m.n <= kSmallN) {
+      tab.small.push_back(j);
+      continue;
+    }
+    const int q = staged_qubits(m.n, lv), h = m.n - q;
+    const int k = pass_of(q - 5, m.pb);
+    TilePass& p = B.passes[k];
+    const int64_t row_groups = ipow3(h), runs = (int64_t)1 << h, rows = ipow3(q);
+    StagedInst& X = sinst[j];
+    X.q = q;
+    X.per_block_of = k;
+    X.chk = RowCheck{nullptr, rows, runs, 0, ipow3(m.n), nullptr, m.pb ? (uint64_t)0 : d.shots, B.ctx->flags, 1, 0,
+                     groups[k], (int64_t)tab.tiles[k].size()};
+    for (int64_t g = 0; g < row_groups; ++g)
+      for (int64_t r = 0; r < runs; ++r) {
+        TileEntry e{};
+        e.counts = d.counts + ((g * rows) << m.n) + (r << q);
+        e.out = d.off_part + (((g << h) + r) * ipow4(q)) * (m.pb ? 8 : 4);
+        e.nb_abs = m.pb && d.nb_in;
+        e.nb = e.nb_abs ? (int64_t) reinterpret_cast<uintptr_t>(d.nb_in + g * rows) : d.off_nb + g * rows * 4;
+        e.group = (int32_t)(groups[k] + g);
+        e.lrow = m.n;
+        tab.tiles[k].push_back(e);
+      }
+    groups[k] += row_groups;
+    p.tiles = (int)tab.tiles[k].size();
+    if (m.pb && !d.nb_in)
+      for (int64_t b = 0; b * sums_per_block(m.n) < ipow3(m.n); ++b) tab.sums.push_back(make_int2(j, (int)b));
+    const int64_t fold_blocks = ipow4(q) / (h <= 2 ? 256 : FoldTailGeom<3>::COLS);
+    for (int64_t b = 0; b < fold_blocks; ++b) tab.tail.push_back(make_int2(j, (int)b));
+    if (want_rho)
+      for (int u = 0; u < (8 << (m.n - kJ)); ++u) tab.units.push_back(make_int2(j, u));
+  }
+  for (int j : order)
+    if (B.meta[j].n > kSmallN)
+      for (int64_t b = 0; b * 256 < ipow3(B.meta[j].n); ++b) tab.tail.push_back(make_int2(j, (int)(-1 - b)));
+  for (size_t k = 0; k < B.passes.size(); ++k) {
+    TilePass& p = B.passes[k];
+    p.off_rowpart = (int64_t)off;
+    off += align256((size_t)(groups[k] + p.tiles) * (size_t)ipow3(5 + p.lv) * 4);
+  }
+  for (int j = 0; j < count; ++j)
+    if (B.meta[j].n > kSmallN) sinst[j].off_rowpart = B.passes[sinst[j].per_block_of].off_rowpart;
+  B.nsmall = (int)tab.small.size();
+  B.nsums = (int)tab.sums.size();
+  B.ntail = (int)tab.tail.size();
+  B.nunits = (int)tab.units.size();
+}
+
+template <typename T>
+bool upload(T** dst, const std::vector<T>& v) {
+  if (v.empty()) return true;
+  return hipMalloc(dst, v.size() * sizeof(T)) == hipSuccess &&
+         hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
+}
+
+bool upload_staged(lre_batch& B, const std::vector<StagedInst>& sinst, const StagedTables& tab) {
+  for (size_t k = 0; k < B.passes.size(); ++k)
+    if (!upload(&B.passes[k].d_table, tab.tiles[k])) return false;
+  return upload(&B.d_sinst, sinst) && upload(&B.d_small, tab.small) && upload(&B.d_sums, tab.sums) &&
+         upload(&B.d_tail, tab.tail) && upload(&B.d_units, tab.units);
+}
+
+// Workgroups of the staged form's launches.
+int staged_blocks(const lre_batch& B) {
+  int64_t n = (int64_t)B.nsmall + B.nsums + B.ntail + B.nunits;
+  for (const TilePass& p : B.passes) {
+    const int per = tiles_per_block(B, p);
+    n += (p.tiles + per - 1) / per;
+  }
+  return (int)n;
+}
+
+template <int LV>
+void launch_tiles(const TilePass& p, int per, char* ws, hipStream_t st) {
+  const dim3 grid((unsigned)((p.tiles + per - 1) / per));
+  uint32_t* rowpart = reinterpret_cast<uint32_t*>(ws + p.off_rowpart);
+  if (p.pb)
+    hipLaunchKernelGGL((batch_tiles_kernel<LV, true, double>), grid, dim3(512), 0, st, (const TileEntry*)p.d_table,
+                       p.tiles, per, ws, rowpart);
+  else
+    hipLaunchKernelGGL((batch_tiles_kernel<LV, false, uint32_t>), grid, dim3(512), 0, st, (const TileEntry*)p.d_table,
+                       p.tiles, per, ws, rowpart);
+}
+
+void launch_staged(const lre_batch& B, char* ws, hipStream_t st) {
+  const bool want_rho = !(B.flags & LRE_NO_RHO), fp32 = (B.flags & LRE_RHO_FP32) != 0;
+  const BInst* insts = B.d_inst;
+  if (B.nsums)
+    hipLaunchKernelGGL(batch_sums_kernel, dim3((unsigned)B.nsums), dim3(256), 0, st, (const int2*)B.d_sums, insts, ws);
+  PassShape shape{};
+  for (size_t k = 0; k < B.passes.size(); ++k) {
+    const TilePass& p = B.passes[k];
+    const int per = shape.per_block[k] = tiles_per_block(B, p);
+    if (p.lv == 2) launch_tiles<2>(p, per, ws, st);
+    else launch_tiles<1>(p, per, ws, st);
+  }
+  if (B.nsmall) {
+    const dim3 grid((unsigned)B.nsmall);
+    if (!want_rho)
+      hipLaunchKernelGGL((batch_small_kernel<false, double>), grid, dim3(256), 0, st, (const int32_t*)B.d_small, insts,
+                         B.ctx->flags);
+    else if (fp32)
+      hipLaunchKernelGGL((batch_small_kernel<true, float>), grid, dim3(256), 0, st, (const int32_t*)B.d_small, insts,
+                         B.ctx->flags);
     else
-      hipLaunchKernelGGL((batch_rho_kernel<double>), dim3(grid), dim3(256), 0, st, (const int*)B.d_nitems,
-                         (const int2*)B.d_units, B.nunits, (const BInst*)B.d_inst);
+      hipLaunchKernelGGL((batch_small_kernel<true, double>), grid, dim3(256), 0, st, (const int32_t*)B.d_small, insts,
+                         B.ctx->flags);
+  }
+  if (B.ntail)
+    hipLaunchKernelGGL(batch_tail_kernel, dim3((unsigned)B.ntail), dim3(256), 0, st, (const int2*)B.d_tail, insts,
+                       (const StagedInst*)B.d_sinst, ws, shape);
+  if (B.nunits) {
+    const dim3 grid((unsigned)B.nunits);
+    if (fp32)
+      hipLaunchKernelGGL((batch_rho_kernel<float>), grid, dim3(256), 0, st, (const int2*)B.d_units, insts);
+    else
+      hipLaunchKernelGGL((batch_rho_kernel<double>), grid, dim3(256), 0, st, (const int2*)B.d_units, insts);
   }
 }
 
@@ -727,6 +983,7 @@ lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uin
     delete B;
     return LRE_E_HIP;
   }
+  const int lv = staged_level(inst, count, B->num_cu);
   B->ctl_bytes = align256((size_t)(1 + 3 * (size_t)count) * 4);
   size_t off = B->ctl_bytes;
   for (int j = 0; j < count; ++j) {
@@ -749,9 +1006,14 @@ lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uin
     d.n = I.n;
     d.q1 = m.q1;
     d.off_part = 0;
-    if (m.F > 0) {
+    if (I.n > kSmallN) {
+      // partials of the staged form (its level's), of which those of 7 folded qubits serve
+      // the other form too
+      size_t elems = m.F > 0 ? (size_t)m.blocks1 * (size_t)ipow4(kQ) : 0;
+      const int h = I.n - staged_qubits(I.n, lv);
+      elems = std::max(elems, (size_t)(ipow3(h) << h) * (size_t)ipow4(I.n - h));
       d.off_part = (int64_t)off;
-      off += align256((size_t)m.blocks1 * (size_t)ipow4(kQ) * (m.pb ? 8 : 4));
+      off += align256(elems * (m.pb ? 8 : 4));
     }
     d.off_nb = d.off_inv = 0;
     if (m.pb) {
@@ -761,6 +1023,9 @@ lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uin
       off += align256((size_t)ipow3(I.n) * 8);
     }
   }
+  std::vector<StagedInst> sinst;
+  StagedTables tab;
+  plan_staged(*B, lv, off, sinst, tab);
   B->ws_bytes = off;
   if (hipMalloc(&B->d_inst, count * sizeof(BInst)) != hipSuccess) {
     delete B;
@@ -784,30 +1049,13 @@ lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uin
     return LRE_E_HIP;
   }
   B->items_cap = cap;
-  // staged form: fold blocks and step-(ii) units of the instances with n > 7
-  std::vector<int32_t> fold;
-  std::vector<int2> units;
-  for (int j = 0; j < count; ++j) {
-    if (B->meta[j].n < kQ) continue;
-    if (B->meta[j].n > kQ)
-      for (int k = 0; k < 64; ++k) fold.push_back(j);
-    if (want_rho)
-      for (int u = 0; u < (8 << (B->meta[j].n - kJ)); ++u) units.push_back(make_int2(j, u));
-  }
-  B->nfold = (int)fold.size();
-  B->nunits = (int)units.size();
-  if ((B->nfold && hipMalloc(&B->d_fold, fold.size() * sizeof(int32_t)) != hipSuccess) ||
-      (B->nunits && hipMalloc(&B->d_units, units.size() * sizeof(int2)) != hipSuccess)) {
+  if (!upload_staged(*B, sinst, tab)) {
     lre_batch_destroy(B);
     return LRE_E_HIP;
   }
-  if ((B->nfold && hipMemcpy(B->d_fold, fold.data(), fold.size() * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) ||
-      (B->nunits && hipMemcpy(B->d_units, units.data(), units.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess)) {
-    lre_batch_destroy(B);
-    return LRE_E_HIP;
-  }
-  B->tiles = lre_batch_tiles{1, 4, kBT * 16, 1, 0, 0};
+  B->tiles = lre_batch_tiles{1, 4, kBT * 16, 1, 0, 0};   // the unstaged list's first shape
   const lre_status s = rebuild(*B);
+  B->tiles = lre_batch_tiles{1, 16, kBT * 16, 1, 0, 1};
   if (s != LRE_OK) {
     lre_batch_destroy(B);
     return s;
@@ -821,13 +1069,14 @@ size_t lre_batch_workspace_bytes(const lre_batch* plan) { return plan ? plan->ws
 lre_status lre_batch_set_tiles(lre_batch* plan, const lre_batch_tiles* tiles) {
   if (!plan || !tiles || !valid_tiles(*tiles)) return LRE_E_ARG;
   plan->tiles = *tiles;
+  if (tiles->staged) return LRE_OK;   // its tables do not depend on the shape
   return rebuild(*plan);
 }
 
 lre_status lre_batch_get_tiles(const lre_batch* plan, lre_batch_tiles* tiles, int* num_items) {
   if (!plan) return LRE_E_ARG;
   if (tiles) *tiles = plan->tiles;
-  if (num_items) *num_items = plan->nitems;
+  if (num_items) *num_items = plan->tiles.staged ? staged_blocks(*plan) : plan->nitems;
   return LRE_OK;
 }
 
@@ -839,6 +1088,10 @@ lre_status lre_batch_run(lre_batch* plan, void* workspace, size_t workspace_byte
   if (!g.ok) return LRE_E_HIP;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
+  if (plan->tiles.staged) {
+    launch_staged(*plan, ws, st);
+    return hipGetLastError() == hipSuccess ? LRE_OK : LRE_E_HIP;
+  }
   uint32_t* ctl = reinterpret_cast<uint32_t*>(ws);
   const int64_t words = 1 + 3 * (int64_t)plan->inst.size();
   hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, ctl, words, 0u);
@@ -846,7 +1099,6 @@ lre_status lre_batch_run(lre_batch* plan, void* workspace, size_t workspace_byte
     hipLaunchKernelGGL((batch_kernel<1, true>), dim3((unsigned)plan->num_cu), dim3(kBT), 0, st,
                        (const BItem*)plan->d_items, (const int*)plan->d_nitems, (const BInst*)plan->d_inst, ws, ctl,
                        plan->ctx->flags);
-    launch_staged(*plan, ws, st);
     return hipGetLastError() == hipSuccess ? LRE_OK : LRE_E_HIP;
   }
   const int workers = plan->num_cu * plan->tiles.workers_per_cu;
@@ -856,7 +1108,6 @@ lre_status lre_batch_run(lre_batch* plan, void* workspace, size_t workspace_byte
   else
     hipLaunchKernelGGL((batch_kernel<2, false>), dim3((unsigned)workers), dim3(kBT), 0, st, (const BItem*)plan->d_items,
                        (const int*)plan->d_nitems, (const BInst*)plan->d_inst, ws, ctl, plan->ctx->flags);
-  launch_staged(*plan, ws, st);
   return hipGetLastError() == hipSuccess ? LRE_OK : LRE_E_HIP;
 }
 
@@ -921,8 +1172,11 @@ void lre_batch_destroy(lre_batch* plan) {
     if (plan->d_items) (void)hipFree(plan->d_items);
     if (plan->d_nitems) (void)hipFree(plan->d_nitems);
     if (plan->d_inst) (void)hipFree(plan->d_inst);
-    if (plan->d_fold) (void)hipFree(plan->d_fold);
-    if (plan->d_units) (void)hipFree(plan->d_units);
+    for (TilePass& p : plan->passes)
+      if (p.d_table) (void)hipFree(p.d_table);
+    void* const tables[] = {plan->d_sinst, plan->d_small, plan->d_sums, plan->d_tail, plan->d_units};
+    for (void* p : tables)
+      if (p) (void)hipFree(p);
   }
   delete plan;
 }

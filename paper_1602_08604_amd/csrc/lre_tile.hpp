@@ -289,6 +289,59 @@ __global__ __launch_bounds__(256) void counts_subtile_kernel(const uint16_t* __r
   if (tid < kTileRows) rp[tid] = rs_acc[tid];
 }
 
+// What the tiles kernel asks about tile t of its block.
+// One instance, or the segments of a slab: tiles ordered (b_hi, tile of the row).
+template <int LV, typename Acc>
+struct InstanceTiles {
+  using G = TileGeom<LV>;
+  const uint16_t* counts_;
+  const uint32_t* nb_;
+  Acc* out_;
+  uint32_t* rowpart_;
+  int64_t t0;
+  int n, lrow, lgT;        // lgT: log2 of the tiles of a row
+  __device__ __forceinline__ int64_t group(int t) const { return (t0 + t) >> lgT; }
+  __device__ __forceinline__ int64_t tile_of_row(int t) const { return (t0 + t) & (((int64_t)1 << lgT) - 1); }
+  __device__ __forceinline__ const uint16_t* counts(int t) const {
+    return counts_ + ((group(t) * G::NROWS) << lrow) + (tile_of_row(t) << G::WB);
+  }
+  __device__ __forceinline__ int rowbytes(int) const { return 2 << lrow; }
+  __device__ __forceinline__ const uint32_t* nb(int t) const { return nb_ + group(t) * G::NROWS; }
+  __device__ __forceinline__ Acc* out(int t) const {
+    return out_ + (((group(t) << (n - G::Q)) + tile_of_row(t)) << (2 * G::Q));
+  }
+  __device__ __forceinline__ bool first_of_row(int t) const { return t == 0 || group(t) != group(t - 1); }
+  __device__ __forceinline__ uint32_t* part(int t) const { return rowpart_ + (group(t) + blockIdx.x) * G::NROWS; }
+};
+
+// The tiles of many instances, from a table (batched estimation).
+struct TileEntry {
+  const uint16_t* counts;      // first row and outcome
+  int64_t out, nb;             // byte offset in the workspace of its partial sums; totals: an
+  int32_t group, lrow;         // offset too, or (nb_abs) an address
+  int32_t nb_abs, pad;
+};
+
+template <int LV, typename Acc>
+struct BatchTiles {
+  using G = TileGeom<LV>;
+  // The block's first tile; in the constant address space, so that entries come through
+  // scalar loads (a vector load's wait would cover every row in flight).
+  const __attribute__((address_space(4))) TileEntry* e;
+  char* ws;
+  uint32_t* rowpart_;
+  __device__ __forceinline__ const uint16_t* counts(int t) const { return e[t].counts; }
+  __device__ __forceinline__ int rowbytes(int t) const { return 2 << e[t].lrow; }
+  __device__ __forceinline__ const uint32_t* nb(int t) const {
+    return reinterpret_cast<const uint32_t*>(e[t].nb_abs ? reinterpret_cast<char*>(e[t].nb) : ws + e[t].nb);
+  }
+  __device__ __forceinline__ Acc* out(int t) const { return reinterpret_cast<Acc*>(ws + e[t].out); }
+  __device__ __forceinline__ bool first_of_row(int t) const { return t == 0 || e[t].group != e[t - 1].group; }
+  __device__ __forceinline__ uint32_t* part(int t) const {
+    return rowpart_ + ((int64_t)e[t].group + blockIdx.x) * G::NROWS;
+  }
+};
+
 // Tiles of 5 + LV qubits (LV = 1, 2), 512 threads: waves 0-3 run stage 1 of one sub-tile
 // while waves 4-7 run stages 2 and 3 of the one before (V double-buffered), so one's loads
 // and transforms overlap the other's LDS traffic and stores; a SIMD holds a wave of each
@@ -297,76 +350,83 @@ __global__ __launch_bounds__(256) void counts_subtile_kernel(const uint16_t* __r
 // of j are used, into the same registers.  Only waves 4-7 store to memory, so no load's wait
 // covers a store.
 // Binary64 sub-tiles take the LDS of a CU (one workgroup), integers half of it.
-// blockIdx.x: `per_block` consecutive tiles, ordered (b_hi, tile of the row); blockIdx.y:
-// segment, as above.  out: [3^(n-Q)][2^(n-Q)][4^Q]; rowpart: [b_hi + block][3^Q], the row sums
-// over the block's tiles of b_hi.
-template <int LV, bool PB, typename Acc>
-__global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
-    const uint16_t* __restrict__ counts, int n, int lrow, int64_t tiles, int64_t per_block,
-    const uint32_t* __restrict__ nb, Acc* __restrict__ out, uint32_t* __restrict__ rowpart, int64_t seg_counts,
-    int64_t seg_out, int64_t seg_row) {
+template <int LV, bool PB>
+struct TileLds {
+  using Elem = typename TileStages<PB>::Elem;
+  Elem V[2 * kTileV];
+  Elem W[kTileW];
+  double invt[PB ? 2 * kTileRows : 1];
+  uint32_t rs_acc[TileGeom<LV>::NROWS];
+};
+
+// The nt tiles of `tiles`, in sequence.  out of a tile: [4^Q] partial sums; part: [3^Q], the
+// row sums over the block's tiles of one row group.
+template <int LV, bool PB, typename Acc, class Tiles>
+__device__ __forceinline__ void counts_tiles_block(const Tiles& tiles, int nt, TileLds<LV, PB>& lds) {
   static_assert(LV == 1 || LV == 2, "levels above the sub-tile");
   using G = TileGeom<LV>;
   using S = TileStages<PB>;
   using Elem = typename S::Elem;
-  // Partials of the larger plans are read again only after more than the caches hold.
+  // Binary64 partials of the larger plans are read again only after more than the caches
+  // hold (plain stores: n = 13 6.99 instead of 6.84 ms, n = 12 integers 921 instead of 941 us).
   constexpr bool kNT = PB && LV >= 2;
-  constexpr int NST = G::NL * G::NS;                           // sub-tiles of a tile
-  __shared__ Elem Vbuf[2 * kTileV];
-  __shared__ Elem W[kTileW];
-  __shared__ uint32_t rs_acc[G::NROWS];
-  __shared__ double invt[PB ? 2 * kTileRows : 1];
-
+  const int nsteps = nt * G::NL * G::NS;                       // sub-tiles
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lgT = n - G::WB;                                   // log2 of the tiles of a row
-  const int64_t t0 = blockIdx.x * per_block;
-  const int nt = (int)(tiles - t0 < per_block ? tiles - t0 : per_block);
-  const int nsteps = nt * NST;
-  const int rowbytes = 2 << lrow;
-  counts = uniform_ptr(counts + blockIdx.y * seg_counts);
-  const auto first_of_row = [&](int t) { return t == 0 || (((t0 + t) >> lgT) != ((t0 + t - 1) >> lgT)); };
+  Elem* const W = lds.W;
 
   if (wave < 4) {
     // ---- stage 1
     const int tid = threadIdx.x, lam = tid & 7;
     const bool on1 = tid < kTileUnits;
-    const int voff = S::row_offset(tid, rowbytes);
     typename S::Rows R[2];
-    // Sub-tile (tile t of the block, row block lblk, column s).
-    struct At { int t, lblk, s; };
-    auto advance = [&](At& a) __attribute__((always_inline)) {
-      if (++a.s == G::NS) {
-        a.s = 0;
-        if (++a.lblk == G::NL) { a.lblk = 0; ++a.t; }
+    // The sub-tile loaded next: tile at, row block alblk, column as.
+    int at = 0, alblk = 0, as = 0;
+    const uint16_t* abase = uniform_ptr(tiles.counts(0));
+    int arow = __builtin_amdgcn_readfirstlane(tiles.rowbytes(0));
+    int voff = S::row_offset(tid, arow);
+    auto next_rsrc = [&]() __attribute__((always_inline)) {
+      const char* p = reinterpret_cast<const char*>(abase) + (int64_t)alblk * kTileRows * arow + as * 128;
+      return tile_rsrc(p, at < nt ? (kTileRows - 1) * arow + 128 : 0);
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
+      if (++as == G::NS) {
+        as = 0;
+        if (++alblk == G::NL) {
+          alblk = 0;
+          if (++at < nt) {
+            abase = uniform_ptr(tiles.counts(at));
+            arow = __builtin_amdgcn_readfirstlane(tiles.rowbytes(at));
+            voff = S::row_offset(tid, arow);
+          }
+        }
       }
     };
-    auto src = [&](const At& a) __attribute__((always_inline)) {
-      const int64_t tile = t0 + (a.t < nt ? a.t : 0);
-      const uint16_t* p = counts + (((tile >> lgT) * G::NROWS + a.lblk * kTileRows) << lrow) +
-                          ((tile & (((int64_t)1 << lgT) - 1)) << G::WB) + a.s * 64;
-      return tile_rsrc(p, a.t < nt ? (kTileRows - 1) * rowbytes + 128 : 0);
-    };
-    At cur{0, 0, 0}, ahead{0, 0, 0};
-    S::load_rows(R[0], src(ahead), voff, rowbytes);
-    advance(ahead);
-    S::load_rows(R[1], src(ahead), voff, rowbytes);
-    advance(ahead);
+    S::load_rows(R[0], next_rsrc(), voff, arow);
+    advance();
+    S::load_rows(R[1], next_rsrc(), voff, arow);
+    advance();
     lds_barrier();                                             // reciprocals of the first rows
-    int rho = 0;                                               // row blocks so far
+    int ct = 0, clblk = 0, cs = 0, rho = 0;                    // the sub-tile in hand; row blocks so far
+    bool first = true;                                         // its tile is the block's first of its rows
     auto step = [&](typename S::Rows& Rj, int buf) __attribute__((always_inline)) {
-      Elem* const Vt = Vbuf + buf * kTileV + S::place(tid);
-      const double* const inv9 = invt + (PB ? (rho & 1) * kTileRows + S::row_of(tid) : 0);
-      const auto next = src(ahead);
-      S::template stage1<0>(Rj, Vt, inv9, lam, next, voff, rowbytes);
-      S::template stage1<1>(Rj, Vt, inv9, lam, next, voff, rowbytes);
+      Elem* const Vt = lds.V + buf * kTileV + S::place(tid);
+      const double* const inv9 = lds.invt + (PB ? (rho & 1) * kTileRows + S::row_of(tid) : 0);
+      const auto next = next_rsrc();
+      S::template stage1<0>(Rj, Vt, inv9, lam, next, voff, arow);
+      S::template stage1<1>(Rj, Vt, inv9, lam, next, voff, arow);
       lds_barrier();
-      S::template stage1<2>(Rj, Vt, inv9, lam, next, voff, rowbytes);
-      if (on1)
-        S::row_totals(Rj, rs_acc + cur.lblk * kTileRows + S::row_of(tid), lam, cur.s == 0 && first_of_row(cur.t));
+      S::template stage1<2>(Rj, Vt, inv9, lam, next, voff, arow);
+      if (on1) S::row_totals(Rj, lds.rs_acc + clblk * kTileRows + S::row_of(tid), lam, cs == 0 && first);
       lds_barrier();
-      advance(ahead);
-      advance(cur);
-      if (cur.s == 0) ++rho;
+      advance();
+      if (++cs == G::NS) {
+        cs = 0;
+        ++rho;
+        if (++clblk == G::NL) {
+          clblk = 0;
+          if (++ct < nt) first = tiles.first_of_row(ct);
+        }
+      }
     };
     int j = 0;
     for (; j + 1 < nsteps; j += 2) {
@@ -381,12 +441,12 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
     const int tid = threadIdx.x - 256;
     // Totals of row block r of the block's sequence.
     auto load_nb = [&](int r) __attribute__((always_inline)) {
+      if constexpr (!PB) return 0u;
       const int t = r / G::NL;
-      const int64_t row = ((t0 + t) >> lgT) * G::NROWS + (r % G::NL) * kTileRows;
-      return PB && t < nt && tid < kTileRows ? nb[row + tid] : 0u;
+      return t < nt && tid < kTileRows ? tiles.nb(t)[(r % G::NL) * kTileRows + tid] : 0u;
     };
     auto set_inv = [&](int r, uint32_t N) __attribute__((always_inline)) {
-      if (PB && tid < kTileRows) invt[(r & 1) * kTileRows + tid] = tile_reciprocal(N);
+      if (PB && tid < kTileRows) lds.invt[(r & 1) * kTileRows + tid] = tile_reciprocal(N);
     };
     set_inv(0, load_nb(0));
     uint32_t nbn = load_nb(1);
@@ -400,9 +460,9 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
     lds_barrier();
     int j = 0;
     Elem T0[4], T1[4];
-    // Stages 2 and 3 of sub-tile j; the reciprocals the sub-tile after next needs.
-    auto stages = [&](int lblk, int s, bool last_of_rows) __attribute__((always_inline)) {
-      if (tid < kTileUnits2) S::stage2(Vbuf + (j & 1) * kTileV, W, tid);
+    // Stages 2 and 3 of sub-tile j (column s); the reciprocals the sub-tile after next needs.
+    auto stages = [&](int s) __attribute__((always_inline)) {
+      if (tid < kTileUnits2) S::stage2(lds.V + (j & 1) * kTileV, W, tid);
       if (s == 0) {
         const int r = rho + (G::NS == 1 ? 2 : 1);
         set_inv(r, nbn);
@@ -413,13 +473,6 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
       if (s == G::NS - 1) ++rho;
       ++j;
     };
-    // The totals of the rows just finished, once the block's last tile of them is done.
-    auto flush = [&](int t, int lblk) __attribute__((always_inline)) {
-      if (t + 1 == nt || first_of_row(t + 1)) {
-        uint32_t* rp = rowpart + blockIdx.y * seg_row + (((t0 + t) >> lgT) + blockIdx.x) * G::NROWS + lblk * kTileRows;
-        if (tid < kTileRows) rp[tid] = rs_acc[lblk * kTileRows + tid];
-      }
-    };
     Acc i5S[4], i5D[4];          // identity letter of qubit 5 (LV 2: even and odd in outcome bit 6)
     Acc i6[4][4];                // LV 2: identity letter of qubit 6, per letter of qubit 5
 #pragma unroll
@@ -429,19 +482,23 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
       for (int q = 0; q < 4; ++q) i6[q][k] = Acc(0);
     }
     for (int t = 0; t < nt; ++t) {
-      const int64_t tile = t0 + t;
-      const int64_t first = (((tile >> lgT) << (n - G::Q)) + (tile & (((int64_t)1 << lgT) - 1))) << (2 * G::Q);
-      const auto o = tile_rsrc(out + blockIdx.y * seg_out + first, (1 << (2 * G::Q)) * (int)sizeof(Acc));
+      const auto o = tile_rsrc(tiles.out(t), (1 << (2 * G::Q)) * (int)sizeof(Acc));
+      // The totals of the rows just finished go out with the block's last tile of them.
+      const bool last = t + 1 == nt || tiles.first_of_row(t + 1);
+      uint32_t* const part = uniform_ptr(tiles.part(t));
+      auto flush = [&](int lblk) __attribute__((always_inline)) {
+        if (last && tid < kTileRows) part[lblk * kTileRows + tid] = lds.rs_acc[lblk * kTileRows + tid];
+      };
       if constexpr (LV == 1) {
         StaticFor<0, 3>::run([&](auto lc) __attribute__((always_inline)) {
           constexpr int l5 = decltype(lc)::value;
-          stages(l5, 0, false);
+          stages(0);
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
             tile_put<kNT>(o, tid, 1024 * (l5 + 1) + 256 * k, (Acc)(T0[k] - T1[k]));
             i5S[k] += (Acc)(T0[k] + T1[k]);
           }
-          flush(t, l5);
+          flush(l5);
           if constexpr (l5 == 2) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -456,14 +513,14 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
           StaticFor<0, 3>::run([&](auto lc) __attribute__((always_inline)) {
             constexpr int l5 = decltype(lc)::value;
             Acc hS[4], hD[4];                                  // outcome bit 6 = 0
-            stages(3 * l6 + l5, 0, false);
+            stages(0);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
               hS[k] = (Acc)(T0[k] + T1[k]);
               hD[k] = (Acc)(T0[k] - T1[k]);
             }
             lds_barrier();
-            stages(3 * l6 + l5, 1, false);
+            stages(1);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
               const Acc Sk = (Acc)(T0[k] + T1[k]), Dk = (Acc)(T0[k] - T1[k]);
@@ -472,7 +529,7 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
               i5D[k] += hS[k] - Sk;
               i6[l5 + 1][k] += hD[k] + Dk;
             }
-            flush(t, 3 * l6 + l5);
+            flush(3 * l6 + l5);
             if constexpr (l5 == 2) {
 #pragma unroll
               for (int k = 0; k < 4; ++k) {
@@ -498,9 +555,41 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
   }
 }
 
+// blockIdx.x: `per_block` consecutive tiles of an instance; blockIdx.y: segment, as for the
+// sub-tile kernel.  out: [3^(n-Q)][2^(n-Q)][4^Q]; rowpart: [b_hi + block][3^Q].
+template <int LV, bool PB, typename Acc>
+__global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
+    const uint16_t* __restrict__ counts, int n, int lrow, int64_t tiles, int64_t per_block,
+    const uint32_t* __restrict__ nb, Acc* __restrict__ out, uint32_t* __restrict__ rowpart, int64_t seg_counts,
+    int64_t seg_out, int64_t seg_row) {
+  __shared__ TileLds<LV, PB> lds;
+  InstanceTiles<LV, Acc> T;
+  T.counts_ = counts + blockIdx.y * seg_counts;
+  T.nb_ = nb;
+  T.out_ = out + blockIdx.y * seg_out;
+  T.rowpart_ = rowpart + blockIdx.y * seg_row;
+  T.t0 = blockIdx.x * per_block;
+  T.n = n;
+  T.lrow = lrow;
+  T.lgT = n - TileGeom<LV>::WB;
+  counts_tiles_block<LV, PB, Acc>(T, (int)(tiles - T.t0 < per_block ? tiles - T.t0 : per_block), lds);
+}
+
+// The same over a table of tiles; part of a block's row group: [group + block][3^Q].
+template <int LV, bool PB, typename Acc>
+__global__ __launch_bounds__(512, PB ? 2 : 4) void batch_tiles_kernel(const TileEntry* __restrict__ table, int tiles,
+                                                                      int per_block, char* __restrict__ ws,
+                                                                      uint32_t* __restrict__ rowpart) {
+  __shared__ TileLds<LV, PB> lds;
+  const int t0 = (int)blockIdx.x * per_block;
+  const BatchTiles<LV, Acc> T{(const __attribute__((address_space(4))) TileEntry*)(table + t0), ws, rowpart};
+  counts_tiles_block<LV, PB, Acc>(T, tiles - t0 < per_block ? tiles - t0 : per_block, lds);
+}
+
 // Row totals: where the parts of basis row group g = b / rows are.  per_block > 0: part
-// g + w for every block w of the counts pass that held one of the group's `runs` tiles;
-// else parts g * runs .. + runs - 1.  seg_row: words between the parts of the nseg segments.
+// group0 + g + w for every block w of the counts pass that held one of the group's `runs`
+// tiles (the instance's first tile is tile0); else parts g * runs .. + runs - 1.  seg_row:
+// words between the parts of the nseg segments.
 struct RowCheck {
   const uint32_t* rowpart;
   int64_t rows, runs, per_block, nbases;
@@ -509,15 +598,17 @@ struct RowCheck {
   uint32_t* flags;
   int nseg;
   int64_t seg_row;
+  int64_t group0, tile0;
 };
 
 __device__ __forceinline__ void check_row_total(const RowCheck& c, int64_t b) {
   const int64_t g = (uint32_t)b / (uint32_t)c.rows, j = (uint32_t)b % (uint32_t)c.rows;
   int64_t p0 = g * c.runs, p1 = p0 + c.runs;
   if (c.per_block > 0) {
-    const uint32_t w0 = (uint32_t)p0 / (uint32_t)c.per_block, w1 = (uint32_t)(p1 - 1) / (uint32_t)c.per_block;
-    p0 = g + w0;
-    p1 = g + w1 + 1;
+    const uint32_t w0 = (uint32_t)(c.tile0 + p0) / (uint32_t)c.per_block;
+    const uint32_t w1 = (uint32_t)(c.tile0 + p1 - 1) / (uint32_t)c.per_block;
+    p0 = c.group0 + g + w0;
+    p1 = c.group0 + g + w1 + 1;
   }
   uint64_t tot = 0;
   for (int s = 0; s < c.nseg; ++s)
@@ -545,23 +636,17 @@ struct FoldTailGeom {
   static constexpr int THREADS = COLS * SUB;
 };
 
+// Block `blk`; mid: LDS of SUB x 16 x COLS values (F > 2).  Every thread of the block calls
+// this (threads beyond THREADS only meet its barrier).
 template <int F, typename Tin, typename Acc, Out MODE>
-__global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
-    const Tin* __restrict__ in, void* __restrict__ out, int n, int h, int l, uint64_t shots, int64_t fold_blocks,
-    int64_t seg_in, int64_t seg_out, RowCheck chk) {
+__device__ __forceinline__ void fold_tail_block(const Tin* __restrict__ in, void* __restrict__ out, int n, int h, int l,
+                                                uint64_t shots, int64_t blk, int tid, Acc* __restrict__ mid) {
   using G = FoldTailGeom<F>;
   constexpr int COLS = G::COLS, F1 = F < 2 ? F : 2, N1 = 1 << (2 * F1);
-  const int tid = threadIdx.x;
-  if ((int64_t)blockIdx.x >= fold_blocks) {
-    const int64_t b = ((int64_t)blockIdx.x - fold_blocks) * G::THREADS + tid;
-    if (b < chk.nbases) check_row_total(chk, b);
-    return;
-  }
-  in += blockIdx.y * seg_in;
   const int64_t L = (int64_t)1 << (2 * l);
   const int64_t per_outer = L / COLS;
-  const int64_t bs = blockIdx.x / per_outer;
-  const int64_t a_l = (blockIdx.x % per_outer) * COLS + tid % COLS;
+  const int64_t bs = blk / per_outer;
+  const int64_t a_l = (blk % per_outer) * COLS + tid % COLS;
   const int q = tid / COLS;
   const int64_t rowstride = ((int64_t)1 << h) * L;
 
@@ -569,7 +654,7 @@ __global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
   const int wl = MODE == Out::Partial ? 0 : pauli_weight((uint64_t)a_l);
   auto put = [&](int a, Acc v) __attribute__((always_inline)) {
     if constexpr (MODE == Out::Partial) {
-      static_cast<Acc*>(out)[blockIdx.y * seg_out + ((bs << (2 * F)) + a) * L + a_l] = v;
+      static_cast<Acc*>(out)[((bs << (2 * F)) + a) * L + a_l] = v;
     } else {
       const int64_t i = (int64_t)a * L + a_l;
       const int w = wl + pauli_weight((uint64_t)a);
@@ -602,7 +687,6 @@ __global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
 #pragma unroll
     for (int a = 0; a < N1; ++a) put(a, o[a]);
   } else {
-    __shared__ Acc mid[G::SUB * 16 * COLS];
     const int col = tid % COLS;
 #pragma unroll
     for (int a = 0; a < 16; ++a) mid[(q * 16 + a) * COLS + col] = o[a];
@@ -632,16 +716,32 @@ __global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
   }
 }
 
+template <int F, typename Tin, typename Acc, Out MODE>
+__global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
+    const Tin* __restrict__ in, void* __restrict__ out, int n, int h, int l, uint64_t shots, int64_t fold_blocks,
+    int64_t seg_in, int64_t seg_out, RowCheck chk) {
+  using G = FoldTailGeom<F>;
+  __shared__ Acc mid[F > 2 ? G::SUB * 16 * G::COLS : 1];
+  if ((int64_t)blockIdx.x >= fold_blocks) {
+    const int64_t b = ((int64_t)blockIdx.x - fold_blocks) * G::THREADS + threadIdx.x;
+    if (b < chk.nbases) check_row_total(chk, b);
+    return;
+  }
+  constexpr int64_t kOutBytes = MODE == Out::Partial ? sizeof(Acc) : 8;
+  fold_tail_block<F, Tin, Acc, MODE>(in + blockIdx.y * seg_in, static_cast<char*>(out) + blockIdx.y * seg_out * kOutBytes,
+                                     n, h, l, shots, blockIdx.x, threadIdx.x, mid);
+}
+
 // ---------------------------------------------------------------------------------
 // Totals of `rows` consecutive rows of 2^lrow counts (lrow >= 3): 2^LR lanes per row, R
 // rows per lane group with all their loads issued before any is summed.
 template <int LR, int R>
-__global__ __launch_bounds__(256) void row_sums_kernel(const uint16_t* __restrict__ counts, int lrow, int64_t rows,
-                                                       uint32_t* __restrict__ nb) {
+__device__ __forceinline__ void row_sums_block(const uint16_t* __restrict__ counts, int lrow, int64_t rows,
+                                               uint32_t* __restrict__ nb, int64_t blk) {
   constexpr int LPR = 1 << LR, GROUPS = 256 / LPR;
   const int lane = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const int per = 1 << (lrow - 3 - LR);                       // 16-byte loads per lane and row
-  const int64_t b0 = ((int64_t)blockIdx.x * GROUPS + grp) * R;
+  const int64_t b0 = (blk * GROUPS + grp) * R;
   const tile_u32x4* __restrict__ base = reinterpret_cast<const tile_u32x4*>(counts);
   uint32_t sum[R];
 #pragma unroll
@@ -670,6 +770,12 @@ __global__ __launch_bounds__(256) void row_sums_kernel(const uint16_t* __restric
   }
 }
 
+template <int LR, int R>
+__global__ __launch_bounds__(256) void row_sums_kernel(const uint16_t* __restrict__ counts, int lrow, int64_t rows,
+                                                       uint32_t* __restrict__ nb) {
+  row_sums_block<LR, R>(counts, lrow, rows, nb, blockIdx.x);
+}
+
 // ---------------------------------------------------------------------------------
 // An instance of N <= 5 qubits in one workgroup and one launch: a thread per basis row
 // sums, checks and transforms its row (2^N counts in registers), the identity letters are
@@ -677,17 +783,21 @@ __global__ __launch_bounds__(256) void row_sums_kernel(const uint16_t* __restric
 // step (ii).  Sums are held in binary64; with uniform shots they are integers below 2^53,
 // so the coefficients are the same correctly rounded quotients as on the other paths.
 // MODE: what `out` receives (PauliT: no rho).
-template <int N, bool PB, Out MODE, bool RHO, typename OutT>
-__global__ __launch_bounds__(256) void small_estimate_kernel(const uint16_t* __restrict__ counts, uint64_t shots,
-                                                             const uint32_t* __restrict__ nb_in,
-                                                             void* __restrict__ out, void* __restrict__ rho,
-                                                             uint32_t* __restrict__ flags) {
-  constexpr int B = (int)ipow3(N), D = 1 << N, NA = 1 << (2 * N), DP = D + 1;
+// S, E: LDS of SmallLds<N>.
+template <int N>
+struct SmallLds {
+  static constexpr int B = (int)ipow3(N), D = 1 << N, DP = D + 1, NA = 1 << (2 * N);
   // the rows' sums, then step (ii)'s two planes
-  constexpr int NSUM = B * DP > 2 * RhoLowLds<N>::SIZE ? B * DP : 2 * RhoLowLds<N>::SIZE;
-  __shared__ double S[NSUM];
-  __shared__ double E[RHO ? NA : 1];
-  const int tid = threadIdx.x;
+  static constexpr int S = B * DP > 2 * RhoLowLds<N>::SIZE ? B * DP : 2 * RhoLowLds<N>::SIZE;
+  static constexpr int E = NA;
+};
+
+template <int N, bool PB, Out MODE, bool RHO, typename OutT>
+__device__ __forceinline__ void small_estimate_block(const uint16_t* __restrict__ counts, uint64_t shots,
+                                                     const uint32_t* __restrict__ nb_in, void* __restrict__ out,
+                                                     void* __restrict__ rho, uint32_t* __restrict__ flags, int tid,
+                                                     double* __restrict__ S, double* __restrict__ E) {
+  constexpr int B = SmallLds<N>::B, D = SmallLds<N>::D, NA = SmallLds<N>::NA, DP = SmallLds<N>::DP;
   if (tid < B) {
     int32_t x[D];
     const uint32_t* __restrict__ p = reinterpret_cast<const uint32_t*>(counts) + tid * (D / 2);
@@ -757,6 +867,16 @@ __global__ __launch_bounds__(256) void small_estimate_kernel(const uint16_t* __r
     __syncthreads();                       // S is dead, E complete
     rho_low_block<N, true, OutT, 256>(E, rho, N, 0, tid, S, S + RhoLowLds<N>::SIZE);
   }
+}
+
+template <int N, bool PB, Out MODE, bool RHO, typename OutT>
+__global__ __launch_bounds__(256) void small_estimate_kernel(const uint16_t* __restrict__ counts, uint64_t shots,
+                                                             const uint32_t* __restrict__ nb_in,
+                                                             void* __restrict__ out, void* __restrict__ rho,
+                                                             uint32_t* __restrict__ flags) {
+  __shared__ double S[SmallLds<N>::S];
+  __shared__ double E[RHO ? SmallLds<N>::E : 1];
+  small_estimate_block<N, PB, MODE, RHO, OutT>(counts, shots, nb_in, out, rho, flags, threadIdx.x, S, E);
 }
 
 }  // namespace lre

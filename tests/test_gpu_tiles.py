@@ -124,3 +124,48 @@ def test_stream_segments_together(n, h, shots):
         assert torch.equal(coef, want)
     else:
         assert (coef - want).abs().max().item() <= TOL
+
+
+@pytest.mark.parametrize("ns,per_basis", [([9], False), ([9, 8, 7, 6, 5], True), ([9] * 14, False), ([9] * 14 + [7, 6, 6, 1], True),
+                                          ([6], False), ([6, 6], True), ([2, 4], True), ([8] * 3, False)])
+def test_batch_forms(ns, per_basis):
+    """A new plan (one launch per stage) against the single instances: 6-qubit tiles with up
+    to 3 qubits left (few instances), 7-qubit tiles (14 of 9 qubits), instances of one tile,
+    none at all; per-basis totals, given and from the rows, beside uniform shots."""
+    print(f"[tiles batch {ns} per-basis={per_basis}]", flush=True)
+    counts, shots, nbs = [], [], []
+    for j, n in enumerate(ns):
+        c, total = uniform_counts(n, 3, 31 * j + n)
+        pb = per_basis and j % 3 != 1
+        if pb:
+            c[:, 0] += 1 + torch.arange(3 ** n, device=DEV) % 5
+        counts.append(as_uint16(c))
+        shots.append(0 if pb else total)
+        nbs.append(c.sum(1).to(torch.int32) if pb and j % 2 else None)
+    b = L.Batch(counts, shots, n_per_basis=nbs)
+    assert b.tiles["staged"] == 1
+    for tiles_per_block in (16, 1, 3):
+        b.set_tiles(1, tiles_per_block, 432, 1, 0, 1)
+        for c, r in zip(b.coefs, b.rhos):
+            c.fill_(7.0)
+            r.fill_(7.0)
+        b.run(check=True)
+        for j in range(len(ns)):
+            coef, rho = L.estimate(counts[j], shots[j], n_per_basis=nbs[j])
+            if shots[j]:
+                assert torch.equal(b.coefs[j], coef) and torch.equal(b.rhos[j], rho)
+            else:
+                assert (b.coefs[j] - coef).abs().max().item() <= TOL
+                assert (b.rhos[j] - rho).abs().max().item() <= TOL
+    # a wrong total is reported, in the first and the last instance
+    for j in (0, len(ns) - 1):
+        v = counts[j].view(torch.int16)
+        v[3 ** ns[j] // 2] += 1
+        if shots[j] or nbs[j] is not None:
+            b.run()
+            with pytest.raises(L.LreError) as e:
+                L.check_flags(DEV)
+            assert e.value.status == L.LRE_E_SHOTS
+        v[3 ** ns[j] // 2] -= 1
+    b.run(check=True)
+    b.close()
