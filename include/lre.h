@@ -72,7 +72,7 @@ typedef enum {
 typedef struct lre_ctx lre_ctx;
 
 /* Create a context on HIP device `hip_device`: allocates the 64-byte device flag
- * word.  *out receives the context.  Errors: LRE_E_ARG (out == NULL), LRE_E_HIP. */
+ * word and its 64-byte mirror in pinned host memory.  *out receives the context.  Errors: LRE_E_ARG (out == NULL), LRE_E_HIP. */
 lre_status lre_create(lre_ctx** out, int hip_device);
 
 /* Destroy a context created by lre_create (NULL is ignored). */

@@ -641,7 +641,23 @@ lre_status lre_create(lre_ctx** out, int hip_device) {
   c->n_stage_events = 0;
   for (auto& e : c->stage_events) e = nullptr;
   if (hipMalloc(&c->flags, 64) != hipSuccess) { delete c; return LRE_E_HIP; }
-  if (hipMemset(c->flags, 0, 64) != hipSuccess) { (void)hipFree(c->flags); delete c; return LRE_E_HIP; }
+  void* mirror = nullptr;
+  if (hipHostMalloc(&mirror, 64, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+    (void)hipFree(c->flags);
+    delete c;
+    return LRE_E_HIP;
+  }
+  std::memset(mirror, 0, 64);
+  c->host_flags = static_cast<volatile uint32_t*>(mirror);
+  void* mirror_dev = nullptr;
+  uint64_t block[8] = {0};
+  if (hipHostGetDevicePointer(&mirror_dev, mirror, 0) == hipSuccess) block[1] = reinterpret_cast<uint64_t>(mirror_dev);
+  if (!mirror_dev || hipMemcpy(c->flags, block, sizeof block, hipMemcpyHostToDevice) != hipSuccess) {
+    (void)hipFree(c->flags);
+    (void)hipHostFree(mirror);
+    delete c;
+    return LRE_E_HIP;
+  }
   // This device's copy of the static scratch array (device `hip_device` is current).
   void* sp = nullptr;
   const hipError_t se = hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch));
@@ -655,6 +671,7 @@ void lre_destroy(lre_ctx* ctx) {
   if (!ctx) return;
   DeviceGuard g(ctx->device);
   (void)hipFree(ctx->flags);
+  (void)hipHostFree(const_cast<uint32_t*>(ctx->host_flags));
   lre_detail::destroy_blas(ctx->blas);
   delete ctx;
 }
@@ -696,6 +713,11 @@ lre_status lre_check(lre_ctx* ctx, void* stream) {
   if (!g.ok) return LRE_E_HIP;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (hipStreamSynchronize(st) != hipSuccess) return LRE_E_HIP;
+  uint32_t raised = 0;
+  for (int k = 0; k < 16; ++k) raised |= ctx->host_flags[k];
+  if (!raised) return LRE_OK;
+  // Mirror first: a bit raised meanwhile then leaves at worst a mirror word without its bit.
+  for (int k = 0; k < 16; ++k) ctx->host_flags[k] = 0;
   uint32_t f = 0;
   if (hipMemcpy(&f, ctx->flags, sizeof f, hipMemcpyDeviceToHost) != hipSuccess) return LRE_E_HIP;
   if (f) {

@@ -172,7 +172,7 @@ __device__ __noinline__ void run_totals(const BInstG& I, const BInstPB& X, int64
     if (lam == 0) {
       nb[b] = N;
       inv[b] = N ? 1.0 / (double)N : 0.0;
-      if (!N) atomicOr(flags, (uint32_t)FLAG_EMPTY);
+      if (!N) raise_flag(flags, FLAG_EMPTY);
     }
   };
   if (X.nb_in) {
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kBT, WORKERS == 2 ? 4 : 1) void batch_kernel(
         uint32_t spins = 0;
         while (__hip_atomic_load(&ctl[W.wait_ctr], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < W.wait_target) {
           if (++spins > kWaitLimit) {
-            atomicOr(flags, (uint32_t)FLAG_WAIT);
+            raise_flag(flags, FLAG_WAIT);
             skip = 1;
             break;
           }

@@ -6,7 +6,8 @@
 
 struct lre_ctx {
   int device;
-  uint32_t* flags;              // device word: FLAG_* bits raised by the kernels
+  uint32_t* flags;              // device block: FLAG_* bits raised by the kernels (raise_flag)
+  volatile uint32_t* host_flags = nullptr;  // its mirror in pinned host memory, a word per bit
   hipEvent_t stage_events[4];   // optional profiling events (lre_set_stage_events)
   int n_stage_events;
   void* blas = nullptr;         // rocBLAS handle of lre_project, created on first use

@@ -55,6 +55,16 @@ __host__ __device__ constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c
 
 enum : uint32_t { FLAG_SHOTS = 1u, FLAG_EMPTY = 2u, FLAG_ARG = 4u, FLAG_WAIT = 8u, FLAG_EIG = 16u };
 
+// The context's flag block on the device: [0] the raised bits, [2..3] the address of its
+// mirror in pinned host memory, a word per bit.  The thread that raises a bit first sets its
+// word, so that a check that finds nothing raised reads host memory only (a device-to-host
+// copy of the word took 18 of the 23 us of a check).
+__device__ __forceinline__ void raise_flag(uint32_t* flags, uint32_t bit) {
+  if (atomicOr(flags, bit) & bit) return;
+  uint32_t* const host = *reinterpret_cast<uint32_t* const*>(flags + 2);
+  __hip_atomic_store(host + (__ffs((int)bit) - 1), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // What the final pass writes.
 enum class Out : int { Partial = 0, CoefUniform = 1, CoefPerBasis = 2, PauliT = 3 };
 
@@ -723,7 +733,7 @@ __device__ __forceinline__ void counts_block(const uint16_t* __restrict__ counts
     // uniform shots or (check_nb) the per-basis totals.
     for (int i = tid; i < G::NROWS; i += THREADS) {
       const uint32_t want = check_nb ? check_nb[row0 + i] : (uint32_t)shots;
-      if (rs_acc[i] != want) atomicOr(check_flags, (uint32_t)FLAG_SHOTS);
+      if (rs_acc[i] != want) raise_flag(check_flags, FLAG_SHOTS);
     }
   } else {
     uint32_t* __restrict__ rp = rowpart + blk * G::NROWS;
@@ -1262,7 +1272,7 @@ __global__ __launch_bounds__(256) void signed_sums_kernel(const uint16_t* __rest
   const int64_t d = (int64_t)1 << n;
   const int64_t b = bases[blockIdx.x];
   const bool ok = b >= 0 && b < ipow3(n);
-  if (!ok && threadIdx.x == 0) atomicOr(flags, (uint32_t)FLAG_ARG);
+  if (!ok && threadIdx.x == 0) raise_flag(flags, FLAG_ARG);
   const int tid = threadIdx.x;
   const int grp = tid / G::LPC, lam = tid % G::LPC;
   constexpr int GROUPS = 256 / G::LPC;
@@ -1301,7 +1311,7 @@ static __global__ __launch_bounds__(256) void signed_sums_mfma_kernel(const uint
   const int64_t d = (int64_t)1 << n;
   const int64_t b = bases[blockIdx.x];
   const bool ok = b >= 0 && b < ipow3(n);
-  if (!ok && threadIdx.x == 0) atomicOr(flags, (uint32_t)FLAG_ARG);
+  if (!ok && threadIdx.x == 0) raise_flag(flags, FLAG_ARG);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 15, g = lane >> 4;
   lre_v4i hA[4];

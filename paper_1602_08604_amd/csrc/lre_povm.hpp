@@ -60,13 +60,13 @@ static __global__ void povm_setup_kernel(const double* __restrict__ G, double* _
         for (int c = 0; c < 4; ++c) s += a[r][c + 4] * g[j][c];   // (G^T G)^{-1} G^T
       M[4 * r + j] = 2.0 * s;
     }
-  if (!ok) atomicOr(flags, (uint32_t)FLAG_ARG);
+  if (!ok) raise_flag(flags, FLAG_ARG);
 }
 
 // Empty data (N = 0) is an error, as an empty basis is for the Pauli measurements
 // (checked after the first pass has summed the counts).
 static __global__ void povm_check_kernel(const unsigned long long* __restrict__ total, uint32_t* __restrict__ flags) {
-  if (threadIdx.x == 0 && blockIdx.x == 0 && *total == 0ull) atomicOr(flags, (uint32_t)FLAG_EMPTY);
+  if (threadIdx.x == 0 && blockIdx.x == 0 && *total == 0ull) raise_flag(flags, FLAG_EMPTY);
 }
 
 // y <- M y on one digit: 4 values.
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void povm_low_kernel(const uint16_t* __restric
   __syncthreads();
   const uint64_t bsum = part[0] + part[1] + part[2] + part[3];
   if (!FINAL && threadIdx.x == 0) atomicAdd(total, (unsigned long long)bsum);
-  if (FINAL && threadIdx.x == 0 && bsum == 0) atomicOr(flags, (uint32_t)FLAG_EMPTY);
+  if (FINAL && threadIdx.x == 0 && bsum == 0) raise_flag(flags, FLAG_EMPTY);
 #pragma unroll
   for (int d = 0; d < J; d += 2) {
     const int nd = (J - d) >= 2 ? 2 : 1;          // digits in this stage

@@ -54,7 +54,7 @@ __global__ void spectrum_kernel(const double* __restrict__ w, double* __restrict
                                 double* __restrict__ eig_out) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   if (*info != 0) {
-    atomicOr(flags, (uint32_t)lre::FLAG_EIG);
+    lre::raise_flag(flags, lre::FLAG_EIG);
     for (int j = 0; j < d; ++j) lam[j] = 0.0;
     return;
   }

@@ -614,8 +614,8 @@ __device__ __forceinline__ void check_row_total(const RowCheck& c, int64_t b) {
   for (int s = 0; s < c.nseg; ++s)
     for (int64_t p = p0; p < p1; ++p) tot += c.rowpart[s * c.seg_row + p * c.rows + j];
   const uint64_t want = c.shots ? c.shots : (uint64_t)c.nb[b];
-  if (tot != want) atomicOr(c.flags, (uint32_t)FLAG_SHOTS);
-  if (!c.shots && want == 0) atomicOr(c.flags, (uint32_t)FLAG_EMPTY);
+  if (tot != want) raise_flag(c.flags, FLAG_SHOTS);
+  if (!c.shots && want == 0) raise_flag(c.flags, FLAG_EMPTY);
 }
 
 static __global__ __launch_bounds__(256) void check_rows_kernel(RowCheck c) {
@@ -821,11 +821,11 @@ __device__ __forceinline__ void small_estimate_block(const uint16_t* __restrict_
     double inv = 1.0;
     if constexpr (PB) {
       const uint32_t want = nb_in ? nb_in[tid] : tot;
-      if (tot != want) atomicOr(flags, (uint32_t)FLAG_SHOTS);
-      if (want == 0) atomicOr(flags, (uint32_t)FLAG_EMPTY);
+      if (tot != want) raise_flag(flags, FLAG_SHOTS);
+      if (want == 0) raise_flag(flags, FLAG_EMPTY);
       inv = want ? 1.0 / (double)want : 0.0;
     } else {
-      if ((uint64_t)tot != shots) atomicOr(flags, (uint32_t)FLAG_SHOTS);
+      if ((uint64_t)tot != shots) raise_flag(flags, FLAG_SHOTS);
     }
 #pragma unroll
     for (int m = 0; m < D; ++m) S[tid * DP + m] = PB ? (double)x[m] * inv : (double)x[m];

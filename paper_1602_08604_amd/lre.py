@@ -165,7 +165,8 @@ def context(device: int | None = None) -> int:
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    index = torch.cuda.current_device() if device is None or device.index is None else device.index
+    return torch._C._cuda_getCurrentRawStream(index)
 
 
 def _num_qubits(counts: torch.Tensor) -> int:
@@ -211,11 +212,9 @@ def estimate(counts: torch.Tensor, shots: int, n_per_basis: torch.Tensor | None 
     if workspace is None:
         workspace = torch.empty(max(wsb, 1), dtype=torch.uint8, device=dev)
     st = lib().lre_estimate(
-        ctypes.c_void_p(context(dev.index)), n, ctypes.c_void_p(counts.data_ptr()), int(shots),
-        ctypes.c_void_p(n_per_basis.data_ptr() if n_per_basis is not None else None),
-        ctypes.c_void_p(coef.data_ptr()), ctypes.c_void_p(rho.data_ptr() if want_rho else None),
-        ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), int(flags),
-        ctypes.c_void_p(_stream(dev)))
+        context(dev.index), n, counts.data_ptr(), int(shots), n_per_basis.data_ptr() if n_per_basis is not None else None,
+        coef.data_ptr(), rho.data_ptr() if want_rho else None, workspace.data_ptr(), workspace.numel(), int(flags),
+        _stream(dev))
     _ok(st, "lre_estimate")
     if check:
         check_flags(dev)
@@ -237,10 +236,8 @@ def estimate_noalloc(counts: torch.Tensor, shots: int, coef: torch.Tensor, rho: 
                                     or n_per_basis.numel() != 3 ** n or not n_per_basis.is_contiguous()):
         raise ValueError("n_per_basis must be a contiguous 32-bit device tensor of length 3^n")
     st = lib().lre_estimate_noalloc(
-        ctypes.c_void_p(context(dev.index)), n, ctypes.c_void_p(counts.data_ptr()), int(shots),
-        ctypes.c_void_p(n_per_basis.data_ptr() if n_per_basis is not None else None),
-        ctypes.c_void_p(coef.data_ptr()), ctypes.c_void_p(rho.data_ptr() if want_rho else None),
-        int(flags), ctypes.c_void_p(_stream(dev)))
+        context(dev.index), n, counts.data_ptr(), int(shots), n_per_basis.data_ptr() if n_per_basis is not None else None,
+        coef.data_ptr(), rho.data_ptr() if want_rho else None, int(flags), _stream(dev))
     _ok(st, "lre_estimate_noalloc")
     if check:
         check_flags(dev)
