@@ -1053,6 +1053,42 @@ size_t lre_povm_workspace_bytes(int n, uint32_t flags) {
   return head + align256(tmp);
 }
 
+}  // extern "C"
+
+namespace {
+
+// Digits of the first pass and of the next one.  Up to 7 in the first: all of n <= 7; 6 for
+// n = 8 .. 10, whose tiles of 7 would leave most CUs idle (n = 10: 23.6 us against 17.8, all
+// passes), 7 from there on, which saves a pass or thins the last one (n = 11: 34.5 us against 36.8;
+// n = 12: 94 as 7 + 5, 117 as 6 + 4 + 2; n = 14: 2.18 ms as 7 + 4 + 3, 2.27 as 6 + 4 + 4).
+int povm_first_digits(int n) { return n <= 7 ? n : (n <= 10 ? 6 : 7); }
+
+// (32-bit offsets in povm_high5_kernel: lo <= 9; 5 digits are left for n = 12, lo = 7, only.)
+int povm_next_digits(int left, int lo) { return left == 5 && lo <= 9 ? 5 : (left >= 4 ? 4 : left); }
+
+template <int J, bool FINAL>
+void launch_povm_tiles(const uint16_t* counts, double* coef, const double* M, unsigned long long* total,
+                       uint32_t* flags, int tiles, hipStream_t st) {
+  using G = PovmTileGeom<J>;
+  const int blocks = (int)std::min<int64_t>(
+      tiles, resident_blocks(povm_tile_kernel<J, FINAL>, G::TH, (G::T + G::T / 16) * 8 + G::TH / 8));
+  hipLaunchKernelGGL((povm_tile_kernel<J, FINAL>), dim3((unsigned)blocks), dim3(G::TH), 0, st, counts, coef, M, total,
+                     flags, tiles);
+}
+
+template <bool FINAL>
+void launch_povm_high5(double* coef, int lo, const double* M, const unsigned long long* total, uint32_t* flags,
+                       int64_t tiles, hipStream_t st) {
+  const int64_t blocks =
+      std::min<int64_t>(tiles, resident_blocks(povm_high5_kernel<FINAL>, 1024, 1024LL * kPovmWideCols * 8));
+  hipLaunchKernelGGL((povm_high5_kernel<FINAL>), dim3((unsigned)blocks), dim3(1024), 0, st, coef, lo, M, total, flags,
+                     tiles);
+}
+
+}  // namespace
+
+extern "C" {
+
 lre_status lre_povm_estimate(lre_ctx* ctx, int n, const uint16_t* counts, const double* G, double* coef, void* rho,
                              void* workspace, size_t workspace_bytes, uint32_t flags, void* stream) {
   if (!ctx || !counts || !G || !coef || n < 1 || n > LRE_MAX_QUBITS) return LRE_E_ARG;
@@ -1075,48 +1111,51 @@ lre_status lre_povm_estimate(lre_ctx* ctx, int n, const uint16_t* counts, const 
   hipLaunchKernelGGL(povm_setup_kernel, dim3(1), dim3(64), 0, st, G, M, total, ctx->flags);
   record_stage(ctx, 1, st);
 
-  // passes: the lowest min(n, 6) digits in one LDS tile (which also sums the counts into
-  // N), then 4 digits at a time in LDS, then the remaining 1..3 in registers; the last
-  // pass divides by N
-  const int J = n < 6 ? n : 6;
-  const int64_t tiles = count >> (2 * J);
+  // Passes over the digits, lowest first; the first also sums the counts into N, the last
+  // divides by N.
+  const int J = povm_first_digits(n);
+  const int tiles = (int)(count >> (2 * J));
   const bool only = J == n;
   switch (J) {
-#define LRE_POVM_LOW(JJ)                                                                                   \
-  case JJ:                                                                                                 \
-    if (only)                                                                                              \
-      hipLaunchKernelGGL((povm_low_kernel<JJ, true>), dim3((unsigned)tiles), dim3(256), 0, st, counts, coef, \
-                         (const double*)M, total, ctx->flags);                                              \
-    else                                                                                                   \
-      hipLaunchKernelGGL((povm_low_kernel<JJ, false>), dim3((unsigned)tiles), dim3(256), 0, st, counts, coef, \
-                         (const double*)M, total, ctx->flags);                                              \
+#define LRE_POVM_LOW(JJ)                                                                                          \
+  case JJ:                                                                                                        \
+    hipLaunchKernelGGL((povm_low_kernel<JJ>), dim3(1), dim3(256), 0, st, counts, coef, (const double*)M, ctx->flags); \
     break;
-    LRE_POVM_LOW(1) LRE_POVM_LOW(2) LRE_POVM_LOW(3) LRE_POVM_LOW(4) LRE_POVM_LOW(5) LRE_POVM_LOW(6)
+    LRE_POVM_LOW(1) LRE_POVM_LOW(2) LRE_POVM_LOW(3) LRE_POVM_LOW(4) LRE_POVM_LOW(5)
 #undef LRE_POVM_LOW
+    case 6:
+      if (only) launch_povm_tiles<6, true>(counts, coef, M, total, ctx->flags, tiles, st);
+      else launch_povm_tiles<6, false>(counts, coef, M, total, ctx->flags, tiles, st);
+      break;
+    default:
+      if (only) launch_povm_tiles<7, true>(counts, coef, M, total, ctx->flags, tiles, st);
+      else launch_povm_tiles<7, false>(counts, coef, M, total, ctx->flags, tiles, st);
   }
-  if (!only)
-    hipLaunchKernelGGL(povm_check_kernel, dim3(1), dim3(64), 0, st, (const unsigned long long*)total, ctx->flags);
-  int lo = J;
-  while (n - lo >= 4) {
-    const bool last = n - lo == 4;
-    const int64_t blocks = (count >> 8) / kPovmCols;
-    if (last)
-      hipLaunchKernelGGL((povm_high4_kernel<true>), dim3((unsigned)blocks), dim3(kPovmHighThreads), 0, st, coef, n,
-                         lo, (const double*)M, (const unsigned long long*)total);
-    else
-      hipLaunchKernelGGL((povm_high4_kernel<false>), dim3((unsigned)blocks), dim3(kPovmHighThreads), 0, st, coef, n,
-                         lo, (const double*)M, (const unsigned long long*)total);
-    lo += 4;
-  }
-  if (n > lo) {
-    const int F = n - lo;
+  for (int lo = J; lo < n;) {
+    const int F = povm_next_digits(n - lo, lo);
+    const bool last = n - lo == F;
+    const double* Mc = M;
+    const unsigned long long* tot = total;
     const int64_t cols = count >> (2 * F);
     const dim3 grid((unsigned)((cols + 255) / 256));
     switch (F) {
-      case 1: hipLaunchKernelGGL((povm_reg_kernel<1, true>), grid, dim3(256), 0, st, coef, n, lo, (const double*)M, (const unsigned long long*)total); break;
-      case 2: hipLaunchKernelGGL((povm_reg_kernel<2, true>), grid, dim3(256), 0, st, coef, n, lo, (const double*)M, (const unsigned long long*)total); break;
-      default: hipLaunchKernelGGL((povm_reg_kernel<3, true>), grid, dim3(256), 0, st, coef, n, lo, (const double*)M, (const unsigned long long*)total); break;
+      case 5:
+        if (last) launch_povm_high5<true>(coef, lo, Mc, tot, ctx->flags, cols / kPovmWideCols, st);
+        else launch_povm_high5<false>(coef, lo, Mc, tot, ctx->flags, cols / kPovmWideCols, st);
+        break;
+      case 4:
+        if (last)
+          hipLaunchKernelGGL((povm_high4_kernel<true>), dim3((unsigned)(cols / kPovmCols)), dim3(kPovmHighThreads), 0,
+                             st, coef, n, lo, Mc, tot, ctx->flags);
+        else
+          hipLaunchKernelGGL((povm_high4_kernel<false>), dim3((unsigned)(cols / kPovmCols)), dim3(kPovmHighThreads), 0,
+                             st, coef, n, lo, Mc, tot, ctx->flags);
+        break;
+      case 3: hipLaunchKernelGGL((povm_reg_kernel<3, true>), grid, dim3(256), 0, st, coef, n, lo, Mc, tot, ctx->flags); break;
+      case 2: hipLaunchKernelGGL((povm_reg_kernel<2, true>), grid, dim3(256), 0, st, coef, n, lo, Mc, tot, ctx->flags); break;
+      default: hipLaunchKernelGGL((povm_reg_kernel<1, true>), grid, dim3(256), 0, st, coef, n, lo, Mc, tot, ctx->flags); break;
     }
+    lo += F;
   }
   if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
   record_stage(ctx, 2, st);
