@@ -854,6 +854,11 @@ lre_status stream_slab(lre_stream* S, int64_t slab, const uint16_t* counts, cons
   io.seg_row = (int64_t)(S->seg_rowpart / 4);
   io.seg_final = ipow4(np);
   const size_t vbytes = (size_t)ipow4(np) * ty_size(S->tV);
+  const RowCheck chk{reinterpret_cast<const uint32_t*>(ws + S->off_rowpart), ipow3(P.q1), P.runs, P.per_block, nbases,
+                     io.nb, P.per_basis ? (uint64_t)0 : S->shots, S->ctx->flags, 1 << h, io.seg_row, 0, 0};
+  // With all segments in one launch the last pass can check the slab's rows (n = 12, h = 2:
+  // 10 us a slab by itself).
+  if (S->par == 1 << h) io.chk = chk;
   for (int sg = 0; sg < (1 << h); sg += S->par) {
     io.counts = counts + ((int64_t)sg << np);
     io.rowpart = reinterpret_cast<uint32_t*>(ws + S->off_rowpart + (size_t)sg * S->seg_rowpart);
@@ -861,9 +866,8 @@ lre_status stream_slab(lre_stream* S, int64_t slab, const uint16_t* counts, cons
     const lre_status s = run_passes(S->ctx, P, io, S->shots, Out::Partial, st);
     if (s != LRE_OK) return s;
   }
-  const RowCheck chk{reinterpret_cast<const uint32_t*>(ws + S->off_rowpart), ipow3(P.q1), P.runs, P.per_block, nbases,
-                     io.nb, P.per_basis ? (uint64_t)0 : S->shots, S->ctx->flags, 1 << h, io.seg_row, 0, 0};
-  hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)((nbases + 255) / 256)), dim3(256), 0, st, chk);
+  if (S->par != 1 << h)
+    hipLaunchKernelGGL(check_rows_kernel, dim3((unsigned)((nbases + 255) / 256)), dim3(256), 0, st, chk);
   // Letters of the top qubits: digit p of the slab index (base 3) is qubit h - p.
   uint32_t atop = 0;
   int64_t t = slab;
@@ -964,9 +968,9 @@ lre_status lre_stream_begin(lre_stream* S, double* coef, void* workspace, size_t
   std::fill(S->pushed.begin(), S->pushed.end(), 0);
   S->npushed = 0;
   // the accumulator starts at zero (a fill kernel: capturable, no memset node)
-  const int64_t words = ipow4(S->n) * 2;
-  hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), reinterpret_cast<uint32_t*>(coef), words, 0u);
+  const int64_t count = ipow4(S->n);             // >= 4^9
+  hipLaunchKernelGGL(stream_clear_kernel, dim3((unsigned)(count / kClearBlock)), dim3(256), 0,
+                     static_cast<hipStream_t>(stream), coef);
   return hipGetLastError() == hipSuccess ? LRE_OK : LRE_E_HIP;
 }
 

@@ -724,7 +724,7 @@ __global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
   __shared__ Acc mid[F > 2 ? G::SUB * 16 * G::COLS : 1];
   if ((int64_t)blockIdx.x >= fold_blocks) {
     const int64_t b = ((int64_t)blockIdx.x - fold_blocks) * G::THREADS + threadIdx.x;
-    if (b < chk.nbases) check_row_total(chk, b);
+    if (blockIdx.y == 0 && b < chk.nbases) check_row_total(chk, b);   // all segments' parts
     return;
   }
   constexpr int64_t kOutBytes = MODE == Out::Partial ? sizeof(Acc) : 8;
