@@ -187,7 +187,8 @@ struct Fold1Args {
   const uint16_t* counts;
   int n, chunks;
   int lrow;             // log2 of the row stride of counts (n for a whole instance)
-  const uint32_t* nb;   // per-basis totals
+  const uint32_t* nb;   // per-basis totals (NULL: formed in the pass, kept in nb_own)
+  uint32_t* nb_own;
   void* out;
   uint32_t* rowpart;
   uint64_t shots;
@@ -202,7 +203,7 @@ void launch_tile(const Fold1Args& a) {
   const dim3 grid((unsigned)a.blocks, (unsigned)a.nseg);
   if constexpr (LV == 0)
     hipLaunchKernelGGL((counts_subtile_kernel<PB, Acc>), grid, dim3(256), 0, a.st, a.counts, a.n, a.lrow, a.nb,
-                       static_cast<Acc*>(a.out), a.rowpart, a.seg_counts, a.seg_out, a.seg_row);
+                       a.nb_own, static_cast<Acc*>(a.out), a.rowpart, a.seg_counts, a.seg_out, a.seg_row);
   else
     hipLaunchKernelGGL((counts_tile_kernel<LV, PB, Acc>), grid, dim3(512), 0, a.st, a.counts, a.n, a.lrow, a.tiles,
                        a.per_block, a.nb, static_cast<Acc*>(a.out), a.rowpart, a.seg_counts, a.seg_out, a.seg_row);
@@ -454,6 +455,7 @@ struct PassIO {
   const uint16_t* counts;
   int lrow;                // log2 of the row stride of counts
   const uint32_t* nb;      // per-basis totals
+  uint32_t* nb_own = nullptr;   // the counts pass is to form them (= nb)
   uint32_t* rowpart;
   void* final_out;
   void* bufA;
@@ -473,7 +475,8 @@ lre_status run_passes(lre_ctx* ctx, const Plan& P, const PassIO& io, uint64_t sh
   a1.n = n;
   a1.chunks = P.chunks;
   a1.lrow = io.lrow;
-  a1.nb = io.nb;
+  a1.nb = io.nb_own ? nullptr : io.nb;
+  a1.nb_own = io.nb_own;
   a1.out = single ? io.final_out : io.bufA;
   a1.rowpart = io.rowpart;
   a1.shots = shots;
@@ -567,7 +570,8 @@ lre_status run_step1(lre_ctx* ctx, const Plan& P, const uint16_t* counts, uint64
   io.nb = P.per_basis ? nb_in : nullptr;
   if (P.per_basis && !nb_in) {
     uint32_t* nb = reinterpret_cast<uint32_t*>(ws + P.off_nb);
-    launch_row_sums(nbases, P.n, counts, nb, st);
+    if (!P.mfma && P.q1 == 5) io.nb_own = nb;                // summed by the counts pass
+    else launch_row_sums(nbases, P.n, counts, nb, st);
     io.nb = nb;
   }
   io.rowpart = reinterpret_cast<uint32_t*>(ws + P.off_rowpart);

@@ -241,10 +241,14 @@ __device__ __forceinline__ void tile_put(__amdgpu_buffer_rsrc_t rsrc, int t, int
 // streamed slab's outcome segment; counts advance by seg_counts, out and rowpart by seg_out
 // elements and seg_row words).
 // out: [3^(n-5)][2^(n-5)][4^5] partial sums; rowpart: [block][243] row sums of the block.
-// nb: per-basis totals (PB), of which every row's reciprocal is formed here.
+// nb: per-basis totals (PB), of which every row's reciprocal is formed here; NULL (one
+// segment, lrow = n): every workgroup sums its rows over all their outcomes, which its 2^(n-6)
+// neighbours also read, and column 0 writes the sums to nb_own for the row check.  (By a
+// launch of its own: n = 7 3.3 us of 17.)
 template <bool PB, typename Acc>
 __global__ __launch_bounds__(256) void counts_subtile_kernel(const uint16_t* __restrict__ counts, int n, int lrow,
-                                                             const uint32_t* __restrict__ nb, Acc* __restrict__ out,
+                                                             const uint32_t* __restrict__ nb,
+                                                             uint32_t* __restrict__ nb_own, Acc* __restrict__ out,
                                                              uint32_t* __restrict__ rowpart, int64_t seg_counts,
                                                              int64_t seg_out, int64_t seg_row) {
   using S = TileStages<PB>;
@@ -263,7 +267,32 @@ __global__ __launch_bounds__(256) void counts_subtile_kernel(const uint16_t* __r
   const auto none = tile_rsrc(counts, 0);
   S::load_rows(R, src, voff, rowbytes);
   if constexpr (PB) {
-    if (tid < kTileRows) invt[tid] = tile_reciprocal(nb[b_hi * kTileRows + tid]);
+    if (nb) {
+      if (tid < kTileRows) invt[tid] = tile_reciprocal(nb[b_hi * kTileRows + tid]);
+    } else {
+      const auto rows = tile_rsrc(counts + ((b_hi * kTileRows) << lrow), kTileRows * rowbytes);
+      uint32_t sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};              // rows (tid >> 3) + 32 k, from 243 on zeros
+      for (int c = 0; c < (1 << (n - 6)); ++c) {
+        tile_u32x4 u[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          u[k] = __builtin_amdgcn_raw_buffer_load_b128(
+              rows, (tid >> 3) * rowbytes + lam * 16, __builtin_amdgcn_readfirstlane(32 * k * rowbytes + c * 128), 0);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[k] += (u[k][e] & 0xFFFFu) + (u[k][e] >> 16);
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t tot = lane_sum<3>(sum[k]);
+        const int r = (tid >> 3) + 32 * k;
+        if (lam == 0 && r < kTileRows) {
+          invt[r] = tile_reciprocal(tot);
+          if (col == 0) nb_own[b_hi * kTileRows + r] = tot;
+        }
+      }
+    }
     lds_barrier();
   }
   {
@@ -636,6 +665,35 @@ struct FoldTailGeom {
   static constexpr int THREADS = COLS * SUB;
 };
 
+// x / den, correctly rounded, by the reciprocal rc = 1 / den (correctly rounded too): x rc is
+// off by less than two units, one correction by the exact remainder makes it faithful, and
+// the second rounds it correctly (Markstein).  Finite x and positive den away from the
+// limits of the type's range, as sums of counts and 3^k N are.
+__device__ __forceinline__ double tail_quotient(double x, double den, double rc) {
+  double q = x * rc;
+  q = fma(fma(-q, den, x), rc, q);
+  return fma(fma(-q, den, x), rc, q);
+}
+
+// The divisors 3^(n - w) (times the shots) of the weights w = wl + k, k <= K: powers and
+// reciprocals once a thread instead of a loop and a division an output (small plans' last pass:
+// n = 7 5.6 -> 3.8 us, n = 8 5.7 -> 4.0, n = 10 10.9 -> 9.7; the larger ones are bound by memory).
+template <int K, Out MODE>
+struct TailDivisors {
+  double den[K + 1], rc[K + 1];
+  __device__ __forceinline__ TailDivisors(int n, int wl, uint64_t shots) {
+    if constexpr (MODE == Out::CoefUniform || MODE == Out::CoefPerBasis) {
+      double p = pow3d(n - wl - K);
+#pragma unroll
+      for (int k = K; k >= 0; --k) {
+        den[k] = MODE == Out::CoefUniform ? p * (double)shots : p;
+        rc[k] = 1.0 / den[k];
+        p *= 3.0;
+      }
+    }
+  }
+};
+
 // Block `blk`; mid: LDS of SUB x 16 x COLS values (F > 2).  Every thread of the block calls
 // this (threads beyond THREADS only meet its barrier).
 template <int F, typename Tin, typename Acc, Out MODE>
@@ -650,19 +708,13 @@ __device__ __forceinline__ void fold_tail_block(const Tin* __restrict__ in, void
   const int q = tid / COLS;
   const int64_t rowstride = ((int64_t)1 << h) * L;
 
-  // Final value of folded code a: divided by 3^(n-w) (and the shots) unless partial.
-  const int wl = MODE == Out::Partial ? 0 : pauli_weight((uint64_t)a_l);
-  auto put = [&](int a, Acc v) __attribute__((always_inline)) {
-    if constexpr (MODE == Out::Partial) {
-      static_cast<Acc*>(out)[((bs << (2 * F)) + a) * L + a_l] = v;
-    } else {
-      const int64_t i = (int64_t)a * L + a_l;
-      const int w = wl + pauli_weight((uint64_t)a);
-      if constexpr (MODE == Out::CoefUniform)
-        static_cast<double*>(out)[i] = acc_to_double(v) / (pow3d(n - w) * (double)shots);
-      else if constexpr (MODE == Out::CoefPerBasis) static_cast<double*>(out)[i] = acc_to_double(v) / pow3d(n - w);
-      else static_cast<int64_t*>(out)[i] = acc_to_i64(v);
-    }
+  // Final value of folded code a, k of whose letters are not the identity: divided by
+  // 3^(n-w) (and the shots) unless partial.
+  const TailDivisors<F, MODE> div(n, MODE == Out::Partial ? 0 : pauli_weight((uint64_t)a_l), shots);
+  auto put = [&](int a, double den, double rc, Acc v) __attribute__((always_inline)) {
+    if constexpr (MODE == Out::Partial) static_cast<Acc*>(out)[((bs << (2 * F)) + a) * L + a_l] = v;
+    else if constexpr (MODE == Out::PauliT) static_cast<int64_t*>(out)[(int64_t)a * L + a_l] = acc_to_i64(v);
+    else static_cast<double*>(out)[(int64_t)a * L + a_l] = tail_quotient(acc_to_double(v), den, rc);
   };
 
   const int dq = q >> (F > 2 ? F - 2 : 0), sq = q & ((1 << (F > 2 ? F - 2 : 0)) - 1);
@@ -685,7 +737,10 @@ __device__ __forceinline__ void fold_tail_block(const Tin* __restrict__ in, void
   });
   if constexpr (F <= 2) {
 #pragma unroll
-    for (int a = 0; a < N1; ++a) put(a, o[a]);
+    for (int a = 0; a < N1; ++a) {
+      const int k = __builtin_popcount((a | (a >> 1)) & 0x5);
+      put(a, div.den[k], div.rc[k], o[a]);
+    }
   } else {
     const int col = tid % COLS;
 #pragma unroll
@@ -710,8 +765,14 @@ __device__ __forceinline__ void fold_tail_block(const Tin* __restrict__ in, void
           r[a] += x[m];
         });
       });
+      // of the code's two letters
+      const int kc = __popc((uint32_t)(code | (code >> 1)) & 0x5u);
 #pragma unroll
-      for (int a = 0; a < N2; ++a) put(code + 16 * a, r[a]);
+      for (int a = 0; a < N2; ++a) {
+        const int k = __builtin_popcount((a | (a >> 1)) & 0x5);
+        put(code + 16 * a, kc == 0 ? div.den[k] : (kc == 1 ? div.den[k + 1] : div.den[k + 2]),
+            kc == 0 ? div.rc[k] : (kc == 1 ? div.rc[k + 1] : div.rc[k + 2]), r[a]);
+      }
     }
   }
 }

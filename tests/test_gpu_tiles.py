@@ -169,3 +169,19 @@ def test_batch_forms(ns, per_basis):
         v[3 ** ns[j] // 2] -= 1
     b.run(check=True)
     b.close()
+
+
+@pytest.mark.parametrize("n", [5, 6, 7, 8, 9])
+def test_empty_row_is_reported(n):
+    """Totals formed from the rows: an empty row anywhere (the first, one in the middle, the
+    last) is reported, a row with a single count is not."""
+    for row in (0, 3 ** n // 2, 3 ** n - 1):
+        print(f"[tiles empty row n={n} row={row}]", flush=True)
+        c = torch.ones((3 ** n, 2 ** n), dtype=torch.int64, device=DEV)
+        c[row] = 0
+        with pytest.raises(L.LreError) as e:
+            L.estimate(as_uint16(c), 0, flags=L.LRE_NO_RHO)
+        assert e.value.status == L.LRE_E_EMPTY_BASIS
+        c[row, -1] = 1
+        coef, _ = L.estimate(as_uint16(c), 0, flags=L.LRE_NO_RHO)
+        assert abs(coef[0].item() - 1.0) <= TOL
