@@ -491,7 +491,7 @@ def bench_povm(args, torch, lre):
                    "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": algo_i / (t_i / 1e3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": algo_i / (t_i / 1e3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "step (i) mode-product passes (povm_low_kernel, povm_high4_kernel x2)",
+                     "kernel": "step (i) mode-product passes (povm_tile_kernel, povm_high4_kernel, povm_reg_kernel)",
                      "algorithmic_bytes_per_launch": algo_i},
         "step_ms": {"step_i": t_i, "step_ii": t_ii},
         "whole_step_hbm_frac": (algo_i + 16.0 * m) / (ms / 1e3) / (HBM_PEAK_GBS * 1e9),
@@ -592,8 +592,8 @@ def bench_batch(args, torch, lre):
         "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "int32+f64", "data": "synthetic",
         "config": {"workload": "batched: 512 instances, n uniform in {3..9} (default_rng(16042)), Haar pure "
-                               "states, shots uniform in [100, 10^4], uint16 counts; one captured launch "
-                               "(counter fill + persistent kernel) per step"
+                               "states, shots uniform in [100, 10^4], uint16 counts; one captured batch run "
+                               "per step"
                                + ("; coefficients only (no rho)" if args.no_rho else ""),
                    "instances": 512, "n_histogram": hist, "total_counts": n_counts, "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": 2.0 * n_counts / (ms_dev / 1e3) / 1e9, "peak": HBM_PEAK_GBS,
@@ -601,8 +601,8 @@ def bench_batch(args, torch, lre):
                      "traffic": None if args.no_rho else measured_traffic(
                          "batch", ",".join(str(tiles[k]) for k in
                                            ("workers_per_cu", "counts_tiles", "fold_cols", "rho_blocks", "interleave", "staged"))),
-                     "kernel": ("batch launch: persistent batch_kernel (counts pass, instances of n <= 7), "
-                                "batch_fold_kernel, batch_rho_kernel" if tiles.get("staged") else
+                     "kernel": ("batch launches, one per stage: batch_tiles_kernel (counts pass), batch_small_kernel, "
+                                "batch_tail_kernel, batch_rho_kernel" if tiles.get("staged") else
                                 "batch_kernel (persistent, all stages of all instances)"),
                      "algorithmic_bytes_per_launch": 2.0 * n_counts},
         "whole_step_hbm_frac": algo / (ms_dev / 1e3) / (HBM_PEAK_GBS * 1e9),
@@ -819,7 +819,7 @@ def bench_estimate(workload, args, torch, lre, extras):
                    "wht": "int8-mfma" if head_flags else "plain-int32", "parallelism": "single GPU"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "fold_counts_stream_kernel (counts pass of step (i))",
+                     "kernel": "counts pass of step (i): counts_subtile_kernel (n <= 8), counts_tile_kernel",
                      "algorithmic_bytes_per_launch": 2.0 * n_counts},
         "end_to_end_s": ms_step / 1e3,
         "step_ms": {"counts_pass": t_pass1 * 1e3, "step_i": sum(step_i) / len(step_i),

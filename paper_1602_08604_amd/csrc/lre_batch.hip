@@ -3,7 +3,7 @@
 // (lre_kernels.hpp, lre_tile.hpp), in one of two forms.
 //
 // Staged (a new plan's form, batch_tiles_kernel and its neighbours below): one launch per stage
-// over all instances.  512 uniform-shot instances of 3 to 9 qubits take 0.63 ms (the work list
+// over all instances.  512 uniform-shot instances of 3 to 9 qubits take 0.62 ms (the work list
 // 0.79 at its best shape, 0.94 at its first), 40 of 5 to 9 qubits with totals from the rows
 // 0.13 (0.71).
 //

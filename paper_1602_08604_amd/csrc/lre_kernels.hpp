@@ -18,20 +18,23 @@
 // Pauli letters.  Qubit positions count from the least significant (position p has
 // weight 3^p in b, 2^p in s, 4^p in the Pauli index), so the lowest qubits fold first.
 //
-// Pass 1 (counts_block / fold_counts_stream_kernel) streams the uint16 counts once and
-// folds the lowest Q <= 7 qubits: a tile is 3^Q rows x 2^Q consecutive outcomes; a lane
-// owns 8 outcomes of a row, a group of 16 lanes walks 27 rows, folds the 3 register
-// qubits with an accumulator cascade, applies the lane butterflies to the values that
-// leave the cascade and adds them into a 4^Q LDS accumulator.  Later passes
-// (fold_partial_col / fold_partial_kernel) fold up to 3 more qubits per pass, one
-// thread per column of the fastest-varying a_lo index, entirely in registers, or 4
+// The counts pass of single instances, slabs and the staged batch folds its qubits through LDS
+// sub-tiles (lre_tile.hpp, which also has the last pass of small plans and the one-launch path
+// of up to 5 qubits).  Here: counts_block, the counts pass of the batch's persistent kernel,
+// which folds the lowest Q <= 7 qubits of a tile of 3^Q rows x 2^Q consecutive outcomes (a
+// lane owns 8 outcomes of a row, a group of 16 lanes walks 27 rows, folds the 3 register
+// qubits with an accumulator cascade, applies the lane butterflies to the values that leave
+// the cascade and adds them into a 4^Q LDS accumulator); its int8-MFMA form
+// (fold_counts_mfma_kernel); and the later passes of n >= 12 and of the persistent kernel:
+// fold_partial_col / fold_partial_kernel fold up to 3 more qubits per pass, one thread per
+// column of the fastest-varying a_lo index, entirely in registers, or 4
 // (fold_partial4_kernel) with the letter codes of 64 columns accumulated in LDS.
 //
 // Step (ii) (Sec. II eq. 4): with x = r XOR c, the entry mu[r][r^x] is a Walsh-Hadamard
 // transform over z in {0,1}^n of e_{a(x,z)} (-i)^{|x&z|}, where per qubit the pair
 // (x_k, z_k) = (0,0),(1,0),(1,1),(0,1) is the letter I, X, Y, Z (the paper's grouping of
-// the Omega_i by nonzero pattern, Sec. IV).  n <= 6: rho_low_kernel does all of it in
-// LDS.  7 <= n <= 10: rho_tile_kernel, units of one high pattern and 8 low patterns
+// the Omega_i by nonzero pattern, Sec. IV).  n <= 5: rho_low_block does all of it in
+// LDS.  6 <= n <= 10: rho_tile_kernel, units of one high pattern and 8 low patterns
 // from coefficients to mu in LDS (a real low transform, the complex one rebuilt from
 // pairs of its outputs, the high transform in registers).  n = 11, 12:
 // rho_real_tile_kernel, the whole n-qubit transform real (the sign (-1)^{floor(|x&z|/2)}
@@ -1671,7 +1674,7 @@ __device__ __forceinline__ void rho_tiles(const double* __restrict__ coef, void*
   }
 }
 
-// Step (ii) for a single instance with n = 6 + H in [7, 10]: one unit per block.
+// Step (ii) for a single instance with n = 6 + H in [6, 10]: one unit per block.
 template <int H, typename OutT>
 __global__ __launch_bounds__(512) void rho_tile_kernel(const double* __restrict__ coef, void* __restrict__ rho) {
   __shared__ double V[RhoTileGeom<H>::NV];

@@ -15,8 +15,8 @@
 //      formed and only the identity letter is kept.
 // Every value passes LDS twice, each time as a plain store and load (no atomics), and no
 // stage has a chain longer than one thread's fold, so a small instance is not one workgroup's
-// serial walk: n = 7 (per-basis totals from the rows) 49.8 -> 16.5 us a call, n = 8 33 -> 14.9,
-// n = 10 66 -> 52.  At n >= 12 the pass is bound by memory: with 10 % (n = 12) to 19 % (n = 13,
+// serial walk: n = 7 (per-basis totals from the rows) 49.8 -> 12.6 us a call, n = 8 33 -> 12.6,
+// n = 10 66 -> 52.7.  At n >= 12 the pass is bound by memory: with 10 % (n = 12) to 19 % (n = 13,
 // binary64) of its traffic being writes the device moves 5.2 TB/s (loads alone: 7.0 and 6.4),
 // n = 12 927 -> 904 us, n = 13 6.40 -> 6.13 ms.
 #pragma once
