@@ -463,7 +463,47 @@ struct PassIO {
   int nseg = 1;
   int64_t seg_counts = 0, seg_row = 0, seg_final = 0;
   RowCheck chk{};          // checked with the last pass (nbases 0: not)
+  void* rho = nullptr;     // not NULL (fuses_rho): step (ii) with the last pass, into rho
+  bool fp32 = false;
 };
+
+template <int H, typename Tin, typename Acc, Out M>
+void launch_tail_rho(const FoldArgs& a, void* rho, bool fp32) {
+  const dim3 grid((unsigned)((8 << H) + (a.chk.nbases + 511) / 512));
+  const Tin* in = static_cast<const Tin*>(a.in);
+  double* coef = static_cast<double*>(a.out);
+  if (fp32)
+    hipLaunchKernelGGL((tail_rho_kernel<H, Tin, Acc, M, float>), grid, dim3(512), 0, a.st, in, coef, rho, a.shots, a.chk);
+  else
+    hipLaunchKernelGGL((tail_rho_kernel<H, Tin, Acc, M, double>), grid, dim3(512), 0, a.st, in, coef, rho, a.shots, a.chk);
+}
+
+// The last pass and step (ii) of n = 6 .. 8 qubits in one launch or two: a unit of 8 qubits reads up to
+// 216 partials a thread, which takes 7.6 us from integers (two launches: 4.0 + 4.0 and a
+// gap, 12.1 -> 11.1 us a call) but 11.8 from binary64 (13.1 -> 17.4 a call); up to 7 qubits
+// at most 36 (n = 7 12.1 -> 8.3 us a call, binary64 12.3 -> 9.2).
+bool fuses_rho(const Plan& P) {
+  return !P.mfma && P.q1 == 5 && (P.n <= 7 || (P.n == 8 && P.t1 == Ty::U32));
+}
+
+template <int H>
+void tail_rho_h(Ty tin, Ty tout, Out m, const FoldArgs& a, void* rho, bool fp32) {
+  if constexpr (H < 2) {
+    if (m == Out::CoefPerBasis) return launch_tail_rho<H, double, double, Out::CoefPerBasis>(a, rho, fp32);
+    if (tin == Ty::F64) return launch_tail_rho<H, double, double, Out::CoefUniform>(a, rho, fp32);
+  }
+  if (tout == Ty::F64) launch_tail_rho<H, uint32_t, double, Out::CoefUniform>(a, rho, fp32);
+  else launch_tail_rho<H, uint32_t, uint32_t, Out::CoefUniform>(a, rho, fp32);
+}
+
+bool tail_rho(Ty tin, Ty tout, Out m, const FoldArgs& a, void* rho, bool fp32) {
+  switch (a.n) {
+    case 6: tail_rho_h<0>(tin, tout, m, a, rho, fp32); return true;
+    case 7: tail_rho_h<1>(tin, tout, m, a, rho, fp32); return true;
+    case 8: tail_rho_h<2>(tin, tout, m, a, rho, fp32); return true;
+  }
+  return false;
+}
 
 // The counts pass (n > kSmallN) and the later passes, into final_out with final mode `fm`.
 lre_status run_passes(lre_ctx* ctx, const Plan& P, const PassIO& io, uint64_t shots, Out fm, hipStream_t st) {
@@ -511,7 +551,8 @@ lre_status run_passes(lre_ctx* ctx, const Plan& P, const PassIO& io, uint64_t sh
     a.seg_out = last ? io.seg_final : (ipow3(h) << h) * ipow4(l);
     if (P.npass == 1) a.chk = io.chk;
     a.st = st;
-    const bool done = P.npass == 1 ? fold_tail(P.F[k], tin, P.tout[k], fm, a)
+    const bool done = io.rho ? tail_rho(tin, P.tout[k], fm, a, io.rho, io.fp32)
+                      : P.npass == 1 ? fold_tail(P.F[k], tin, P.tout[k], fm, a)
                                    : two_pass(P.F[k], last, tin, P.tout[k], fm, a);
     if (!done) return LRE_E_UNSUPPORTED;
     if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
@@ -562,9 +603,12 @@ lre_status run_small(lre_ctx* ctx, int n, Out fm, const uint16_t* counts, uint64
 // Step (i) of an instance of n > kSmallN qubits into `final_out` (coef or T) with final
 // mode `fm`.
 lre_status run_step1(lre_ctx* ctx, const Plan& P, const uint16_t* counts, uint64_t shots,
-                     const uint32_t* nb_in, void* final_out, Out fm, char* ws, hipStream_t st) {
+                     const uint32_t* nb_in, void* final_out, Out fm, char* ws, hipStream_t st, void* rho = nullptr,
+                     bool fp32 = false) {
   const int64_t nbases = ipow3(P.n);
   PassIO io{};
+  io.rho = rho;
+  io.fp32 = fp32;
   io.counts = counts;
   io.lrow = P.n;
   io.nb = P.per_basis ? nb_in : nullptr;
@@ -609,10 +653,12 @@ lre_status estimate_impl(lre_ctx* ctx, int n, const uint16_t* counts, uint64_t s
     for (int k = 1; k < 4; ++k) record_stage(ctx, k, st);
     return s;
   }
-  const lre_status s = run_step1(ctx, P, counts, shots, n_per_basis, coef, fm, ws, st);
+  const bool fused = want_rho && fuses_rho(P);
+  const lre_status s = run_step1(ctx, P, counts, shots, n_per_basis, coef, fm, ws, st, fused ? rho : nullptr,
+                                 (flags & LRE_RHO_FP32) != 0);
   if (s != LRE_OK) return s;
   record_stage(ctx, 2, st);
-  if (want_rho) {
+  if (want_rho && !fused) {
     if (flags & LRE_RHO_FP32) launch_rho<float>(P, coef, rho, ws, st);
     else launch_rho<double>(P, coef, rho, ws, st);
     if (hipGetLastError() != hipSuccess) return LRE_E_HIP;

@@ -1596,15 +1596,66 @@ __device__ __forceinline__ int rho_tile_slot(uint32_t j, uint32_t w6) {
   return (int)(((w6 >> 3) << 6) | letters_of<3>(j, w6 & 7u));
 }
 
+// Unit u from its staged inputs V to mu.  Every thread of the block calls this.
+template <int H, typename OutT, int THREADS>
+__device__ __forceinline__ void rho_tile_unit(void* __restrict__ rho, int64_t u, int t, double* __restrict__ V) {
+  using G = RhoTileGeom<H>;
+  constexpr int n = 6 + H;
+  static_assert(THREADS >= G::NZ * 32, "one lane quad per (z_hi, j) low transform");
+  const double scale = ldexp(1.0, -n - 1);
+  const uint32_t x_hi = (uint32_t)(u >> 3), xb = (uint32_t)(u & 7);
+  if (t < G::NZ * 32) {  // low transform: lane quad (z_hi, j), lane zl holds z_lo = zl + 4k
+    const uint32_t q = (uint32_t)t >> 2, zl = (uint32_t)t & 3u;
+    const uint32_t z_hi = q >> 3, j = q & 7u, x_lo = (xb << 3) | j;
+    double* __restrict__ Vz = V + z_hi * 512;
+    double v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const uint32_t z = zl + 4u * (uint32_t)k;
+      const double a = Vz[rho_tile_slot(j, z)];
+      v[k] = (__popc(x_lo & z) & 2) ? -a : a;
+    }
+    wht_regs<4>(v);
+    int32_t sg[2] = {(t & 1) ? -1 : 1, (t & 2) ? -1 : 1};
+    asm volatile("" : "+v"(sg[0]), "+v"(sg[1]));
+#pragma unroll
+    for (int k = 0; k < 16; ++k) lane_bfly<kDppQuadXor1, false>(v[k], sg[0]);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) lane_bfly<kDppQuadXor2, false>(v[k], sg[1]);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) Vz[rho_tile_slot(j, zl + 4u * (uint32_t)k)] = v[k];
+  }
+  lds_barrier();
+  for (int w = t; w < 512; w += THREADS) {  // high transform: (r_lo, j), j fastest
+    const uint32_t r_lo = (uint32_t)w >> 3, j = (uint32_t)w & 7u;
+    const uint32_t rb = r_lo ^ ((xb << 3) | j);
+    const int sa = rho_tile_slot(j, r_lo), sb = rho_tile_slot(j, rb);
+    double re[G::NZ], im[G::NZ];
+#pragma unroll
+    for (int z = 0; z < G::NZ; ++z) {
+      const double ta = V[z * 512 + sa], tb = V[z * 512 + sb];
+      re[z] = ta + tb;
+      im[z] = tb - ta;
+      mul_neg_i_pow(__popc(x_hi & (uint32_t)z), re[z], im[z]);
+    }
+    wht_regs<H>(re);
+    wht_regs<H>(im);
+#pragma unroll
+    for (int r_hi = 0; r_hi < G::NZ; ++r_hi) {
+      const int64_t row = ((int64_t)r_hi << 6) | r_lo;
+      const int64_t col = ((int64_t)(r_hi ^ x_hi) << 6) | rb;
+      store_complex<OutT>(rho, (row << n) + col, re[r_hi] * scale, im[r_hi] * scale);
+    }
+  }
+}
+
 // Units [u0, u1) of one instance, in sequence; the next unit's inputs are loaded into
 // registers while the current one is transformed.  Every thread of the block calls this.
 template <int H, typename OutT, int THREADS>
 __device__ __forceinline__ void rho_tiles(const double* __restrict__ coef, void* __restrict__ rho, int64_t u0,
                                           int64_t u1, int t, double* __restrict__ V) {
   using G = RhoTileGeom<H>;
-  constexpr int n = 6 + H;
   constexpr int PER = (G::NV + THREADS - 1) / THREADS;
-  static_assert(THREADS >= G::NZ * 32, "one lane quad per (z_hi, j) low transform");
   double pre[PER];
   auto load = [&](int64_t u) __attribute__((always_inline)) {
     const uint32_t x_hi = (uint32_t)(u >> 3), xb = (uint32_t)(u & 7);
@@ -1618,7 +1669,6 @@ __device__ __forceinline__ void rho_tiles(const double* __restrict__ coef, void*
       }
     }
   };
-  const double scale = ldexp(1.0, -n - 1);
   if (u0 < u1) load(u0);
   for (int64_t u = u0; u < u1; ++u) {
     lds_barrier();  // the previous unit's high transform has read V
@@ -1627,50 +1677,7 @@ __device__ __forceinline__ void rho_tiles(const double* __restrict__ coef, void*
       if (t + THREADS * i < G::NV) V[t + THREADS * i] = pre[i];
     lds_barrier();
     if (u + 1 < u1) load(u + 1);
-    const uint32_t x_hi = (uint32_t)(u >> 3), xb = (uint32_t)(u & 7);
-    if (t < G::NZ * 32) {  // low transform: lane quad (z_hi, j), lane zl holds z_lo = zl + 4k
-      const uint32_t q = (uint32_t)t >> 2, zl = (uint32_t)t & 3u;
-      const uint32_t z_hi = q >> 3, j = q & 7u, x_lo = (xb << 3) | j;
-      double* __restrict__ Vz = V + z_hi * 512;
-      double v[16];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const uint32_t z = zl + 4u * (uint32_t)k;
-        const double a = Vz[rho_tile_slot(j, z)];
-        v[k] = (__popc(x_lo & z) & 2) ? -a : a;
-      }
-      wht_regs<4>(v);
-      int32_t sg[2] = {(t & 1) ? -1 : 1, (t & 2) ? -1 : 1};
-      asm volatile("" : "+v"(sg[0]), "+v"(sg[1]));
-#pragma unroll
-      for (int k = 0; k < 16; ++k) lane_bfly<kDppQuadXor1, false>(v[k], sg[0]);
-#pragma unroll
-      for (int k = 0; k < 16; ++k) lane_bfly<kDppQuadXor2, false>(v[k], sg[1]);
-#pragma unroll
-      for (int k = 0; k < 16; ++k) Vz[rho_tile_slot(j, zl + 4u * (uint32_t)k)] = v[k];
-    }
-    lds_barrier();
-    for (int w = t; w < 512; w += THREADS) {  // high transform: (r_lo, j), j fastest
-      const uint32_t r_lo = (uint32_t)w >> 3, j = (uint32_t)w & 7u;
-      const uint32_t rb = r_lo ^ ((xb << 3) | j);
-      const int sa = rho_tile_slot(j, r_lo), sb = rho_tile_slot(j, rb);
-      double re[G::NZ], im[G::NZ];
-#pragma unroll
-      for (int z = 0; z < G::NZ; ++z) {
-        const double ta = V[z * 512 + sa], tb = V[z * 512 + sb];
-        re[z] = ta + tb;
-        im[z] = tb - ta;
-        mul_neg_i_pow(__popc(x_hi & (uint32_t)z), re[z], im[z]);
-      }
-      wht_regs<H>(re);
-      wht_regs<H>(im);
-#pragma unroll
-      for (int r_hi = 0; r_hi < G::NZ; ++r_hi) {
-        const int64_t row = ((int64_t)r_hi << 6) | r_lo;
-        const int64_t col = ((int64_t)(r_hi ^ x_hi) << 6) | rb;
-        store_complex<OutT>(rho, (row << n) + col, re[r_hi] * scale, im[r_hi] * scale);
-      }
-    }
+    rho_tile_unit<H, OutT, THREADS>(rho, u, t, V);
   }
 }
 

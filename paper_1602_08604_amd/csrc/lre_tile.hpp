@@ -15,7 +15,7 @@
 //      formed and only the identity letter is kept.
 // Every value passes LDS twice, each time as a plain store and load (no atomics), and no
 // stage has a chain longer than one thread's fold, so a small instance is not one workgroup's
-// serial walk: n = 7 (per-basis totals from the rows) 49.8 -> 12.6 us a call, n = 8 33 -> 12.6,
+// serial walk: n = 7 (per-basis totals from the rows) 49.8 -> 10.6 us a call, n = 8 33 -> 11.3,
 // n = 10 66 -> 52.7.  At n >= 12 the pass is bound by memory: with 10 % (n = 12) to 19 % (n = 13,
 // binary64) of its traffic being writes the device moves 5.2 TB/s (loads alone: 7.0 and 6.4),
 // n = 12 927 -> 904 us, n = 13 6.40 -> 6.13 ms.
@@ -791,6 +791,99 @@ __global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
   constexpr int64_t kOutBytes = MODE == Out::Partial ? sizeof(Acc) : 8;
   fold_tail_block<F, Tin, Acc, MODE>(in + blockIdx.y * seg_in, static_cast<char*>(out) + blockIdx.y * seg_out * kOutBytes,
                                      n, h, l, shots, blockIdx.x, threadIdx.x, mid);
+}
+
+// ---------------------------------------------------------------------------------
+// The last pass and step (ii) of n = 6 + H <= 8 qubits in one launch, a unit of rho_tiles per
+// workgroup: every coefficient belongs to exactly one unit (its x pattern), so a unit folds
+// its own coefficients from the counts pass's partials [3^(H+1)][2^(H+1)][4^5], writes them
+// to coef and, through V, to mu.  Thread t takes letters t & 63 of qubits 0..2 and
+// z bits t >> 6 of qubits 3..5 (one wave), all 2^H z patterns of the qubits above, whose x
+// pattern X says which of their 6 inputs matter: all for I and Z, those of X and Y otherwise.
+// Bound by the loads' latency, once per letter of qubit 5 (the sched_barrier keeps a letter's
+// loads together: n = 7 9.2 -> 8.3 us a call); n = 7 4.9 us where the two launches took 3.8 + 3.3
+// and the gap between them, n = 8 (integers) 7.6 against 4.0 + 4.0.
+template <int H, int X, typename Tin, typename Acc>
+__device__ __forceinline__ void tail_unit_fold(const Tin* __restrict__ p, int letter5, Acc (&out)[1 << H]) {
+  constexpr int h = H + 1, ND = (int)ipow3(H), NS = 1 << H;
+#pragma unroll
+  for (int z = 0; z < NS; ++z) out[z] = Acc(0);
+  const int first = letter5 ? letter5 - 1 : 0, last = letter5 ? letter5 : 3;
+  for (int d5 = first; d5 < last; ++d5) {
+    Tin y[ND][NS][2];
+    StaticFor<0, ND>::run([&](auto dc) __attribute__((always_inline)) {
+      constexpr int d = decltype(dc)::value;
+      constexpr bool used = !((X & 1) && d % 3 == 2) && !((X & 2) && d / 3 == 2);
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int s5 = 0; s5 < 2; ++s5)
+          y[d][s][s5] = used ? p[((((d * 3 + d5) << h) | (2 * s + s5)) << 10)] : Tin(0);
+    });
+    __builtin_amdgcn_sched_barrier(0);                         // every load in flight at once
+    StaticFor<0, ND>::run([&](auto dc) __attribute__((always_inline)) {
+      constexpr int d = decltype(dc)::value;
+      Acc v[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const Acc a = in_to_acc<Tin, Acc>(y[d][s][0]), b = in_to_acc<Tin, Acc>(y[d][s][1]);
+        v[s] = letter5 ? a - b : a + b;
+      }
+      wht_regs<H>(v);
+      StaticFor<0, NS>::run([&](auto zc) __attribute__((always_inline)) {
+        constexpr int z = decltype(zc)::value;
+        constexpr int a0 = (X & 1) ? ((z & 1) ? 2 : 1) : ((z & 1) ? 3 : 0);
+        constexpr int a1 = (X & 2) ? ((z & 2) ? 2 : 1) : ((z & 2) ? 3 : 0);
+        if constexpr ((a0 == 0 || a0 == d % 3 + 1) && (H < 2 || a1 == 0 || a1 == d / 3 + 1)) out[z] += v[(X | z) & (NS - 1)];
+      });
+    });
+  }
+}
+
+template <int H, typename Tin, typename Acc, Out MODE, typename OutT>
+__global__ __launch_bounds__(512, 2) void tail_rho_kernel(const Tin* __restrict__ in, double* __restrict__ coef,
+                                                       void* __restrict__ rho, uint64_t shots, RowCheck chk) {
+  static_assert(H <= 2, "n <= 8");
+  constexpr int n = 6 + H, NZ = 1 << H, UNITS = 8 << H;
+  __shared__ double V[RhoTileGeom<H>::NV];
+  const int t = threadIdx.x;
+  if (blockIdx.x >= UNITS) {
+    const int64_t b = ((int64_t)blockIdx.x - UNITS) * 512 + t;
+    if (b < chk.nbases) check_row_total(chk, b);
+    return;
+  }
+  const uint32_t x_hi = blockIdx.x >> 3, xb = blockIdx.x & 7u;
+  const uint32_t zh3 = (uint32_t)__builtin_amdgcn_readfirstlane(t >> 6);
+  const uint32_t a5 = letters_of<3>(xb, zh3);                  // letters of qubits 3..5
+  const uint32_t low = ((a5 & 15u) << 6) | (uint32_t)(t & 63);
+  const int letter5 = (int)(a5 >> 4);
+  Acc out[NZ];
+  const Tin* __restrict__ p = in + low;
+  if constexpr (H == 0) tail_unit_fold<H, 0>(p, letter5, out);
+  if constexpr (H == 1) {
+    if (x_hi == 0) tail_unit_fold<H, 0>(p, letter5, out);
+    else tail_unit_fold<H, 1>(p, letter5, out);
+  }
+  if constexpr (H == 2) {
+    if (x_hi == 0) tail_unit_fold<H, 0>(p, letter5, out);
+    else if (x_hi == 1) tail_unit_fold<H, 1>(p, letter5, out);
+    else if (x_hi == 2) tail_unit_fold<H, 2>(p, letter5, out);
+    else tail_unit_fold<H, 3>(p, letter5, out);
+  }
+  const TailDivisors<H, MODE> div(n, pauli_weight((uint64_t)low) + (letter5 ? 1 : 0), shots);
+#pragma unroll
+  for (int z = 0; z < NZ; ++z) {
+    const int k = __popc(x_hi | (uint32_t)z);                  // letters of the qubits above that are not I
+    double den = div.den[0], rc = div.rc[0];
+#pragma unroll
+    for (int q = 1; q <= H; ++q)
+      if (k == q) { den = div.den[q]; rc = div.rc[q]; }
+    const double e = tail_quotient(acc_to_double(out[z]), den, rc);
+    coef[((int64_t)letters_of<H>(x_hi, (uint32_t)z) << 12) | (a5 << 6) | (uint32_t)(t & 63)] = e;
+    V[z * 512 + t] = e;
+  }
+  lds_barrier();
+  rho_tile_unit<H, OutT, 512>(rho, blockIdx.x, t, V);
 }
 
 // ---------------------------------------------------------------------------------
