@@ -136,6 +136,8 @@ lre_status lre_check(lre_ctx* ctx, void* stream);
  * disable.  While set, lre_estimate records them on its stream at stage boundaries:
  *   events[0] before its first kernel,        events[1] after the counts pass,
  *   events[2] after the rest of step (i),     events[3] after step (ii).
+ * Where one launch holds several stages (n <= 5: all of them; n = 6 .. 8 with a matrix: the
+ * rest of step (i) and step (ii)), their events follow that launch.
  * The caller owns the events and must keep them alive while they are set. */
 lre_status lre_set_stage_events(lre_ctx* ctx, void* const* events, int count);
 
