@@ -695,7 +695,8 @@ struct TailDivisors {
 };
 
 // Block `blk`; mid: LDS of SUB x 16 x COLS values (F > 2).  Every thread of the block calls
-// this (threads beyond THREADS only meet its barrier).
+// this.  The batch's tail stage runs F = 3 in workgroups of 256: threads from THREADS on have no
+// (letters, outcomes) of their own and only meet the barrier.
 template <int F, typename Tin, typename Acc, Out MODE>
 __device__ __forceinline__ void fold_tail_block(const Tin* __restrict__ in, void* __restrict__ out, int n, int h, int l,
                                                 uint64_t shots, int64_t blk, int tid, Acc* __restrict__ mid) {
@@ -717,36 +718,41 @@ __device__ __forceinline__ void fold_tail_block(const Tin* __restrict__ in, void
     else static_cast<double*>(out)[(int64_t)a * L + a_l] = tail_quotient(acc_to_double(v), den, rc);
   };
 
-  const int dq = q >> (F > 2 ? F - 2 : 0), sq = q & ((1 << (F > 2 ? F - 2 : 0)) - 1);
-  const Tin* __restrict__ p =
-      in + fold_in_offset<F>(h, l, (bs << (2 * l)) + a_l, dq * (int)ipow3(F1), sq << F1);
-  Acc o[N1];
+  if (tid < G::THREADS) {
+    const int dq = q >> (F > 2 ? F - 2 : 0), sq = q & ((1 << (F > 2 ? F - 2 : 0)) - 1);
+    const Tin* __restrict__ p =
+        in + fold_in_offset<F>(h, l, (bs << (2 * l)) + a_l, dq * (int)ipow3(F1), sq << F1);
+    Acc o[N1];
 #pragma unroll
-  for (int a = 0; a < N1; ++a) o[a] = Acc(0);
-  StaticFor<0, (int)ipow3(F1)>::run([&](auto bc) __attribute__((always_inline)) {
-    constexpr int beta = decltype(bc)::value;
-    Acc x[1 << F1];
+    for (int a = 0; a < N1; ++a) o[a] = Acc(0);
+    StaticFor<0, (int)ipow3(F1)>::run([&](auto bc) __attribute__((always_inline)) {
+      constexpr int beta = decltype(bc)::value;
+      Acc x[1 << F1];
 #pragma unroll
-    for (int sg = 0; sg < (1 << F1); ++sg) x[sg] = in_to_acc<Tin, Acc>(p[beta * rowstride + sg * L]);
-    wht_regs<F1>(x);
-    StaticFor<0, (1 << F1)>::run([&](auto mc) __attribute__((always_inline)) {
-      constexpr int m = decltype(mc)::value;
-      constexpr int a = fold_index(beta, m, F1);
-      o[a] += x[m];
+      for (int sg = 0; sg < (1 << F1); ++sg) x[sg] = in_to_acc<Tin, Acc>(p[beta * rowstride + sg * L]);
+      wht_regs<F1>(x);
+      StaticFor<0, (1 << F1)>::run([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        constexpr int a = fold_index(beta, m, F1);
+        o[a] += x[m];
+      });
     });
-  });
-  if constexpr (F <= 2) {
+    if constexpr (F <= 2) {
 #pragma unroll
-    for (int a = 0; a < N1; ++a) {
-      const int k = __builtin_popcount((a | (a >> 1)) & 0x5);
-      put(a, div.den[k], div.rc[k], o[a]);
+      for (int a = 0; a < N1; ++a) {
+        const int k = __builtin_popcount((a | (a >> 1)) & 0x5);
+        put(a, div.den[k], div.rc[k], o[a]);
+      }
+    } else {
+#pragma unroll
+      for (int a = 0; a < 16; ++a) mid[(q * 16 + a) * COLS + tid % COLS] = o[a];
     }
-  } else {
+  }
+  if constexpr (F > 2) {
     const int col = tid % COLS;
-#pragma unroll
-    for (int a = 0; a < 16; ++a) mid[(q * 16 + a) * COLS + col] = o[a];
     __syncthreads();
-    for (int t = tid; t < 16 * COLS; t += G::THREADS) {        // column t % COLS = tid % COLS
+    // column t % COLS = tid % COLS
+    for (int t = tid < G::THREADS ? tid : 16 * COLS; t < 16 * COLS; t += G::THREADS) {
       const int code = t / COLS;
       const Acc* __restrict__ m0 = mid + code * COLS + col;
       constexpr int F2 = F - 2, N2 = 1 << (2 * F2);
