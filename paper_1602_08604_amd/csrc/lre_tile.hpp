@@ -236,6 +236,14 @@ __device__ __forceinline__ void tile_put(__amdgpu_buffer_rsrc_t rsrc, int t, int
   }
 }
 
+// Row totals inside the sub-tile pass: load k (of 8) of thread t takes row (t >> 3) + 32 k.  Byte
+// offset of the thread's part of the address; the uniform part 32 k rows + the column is added
+// to it.  Rows beyond the 243 get an offset out of range by itself: whether the range check
+// of a raw buffer counts the uniform part too is not the same in all descriptions of it.
+__host__ __device__ constexpr int subtile_total_offset(int t, int k, int rowbytes) {
+  return (t >> 3) + 32 * k < kTileRows ? (t >> 3) * rowbytes + (t & 7) * 16 : 0x40000000;
+}
+
 // One sub-tile per workgroup of 256 threads, 5 qubits folded (plans too small to fill the
 // chip with anything larger): blockIdx.x = (b_hi, 64-outcome column), blockIdx.y = segment (a
 // streamed slab's outcome segment; counts advance by seg_counts, out and rowpart by seg_out
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(256) void counts_subtile_kernel(const uint16_t* __r
 #pragma unroll
         for (int k = 0; k < 8; ++k)
           u[k] = __builtin_amdgcn_raw_buffer_load_b128(
-              rows, (tid >> 3) * rowbytes + lam * 16, __builtin_amdgcn_readfirstlane(32 * k * rowbytes + c * 128), 0);
+              rows, subtile_total_offset(tid, k, rowbytes), __builtin_amdgcn_readfirstlane(32 * k * rowbytes + c * 128), 0);
 #pragma unroll
         for (int k = 0; k < 8; ++k)
 #pragma unroll

@@ -50,19 +50,43 @@ template <class T, class U> T atomicAdd(T* p, U v);
 template <class T> T __shfl(T, int, int = 64);
 template <class T> T __shfl_xor(T, int, int = 64);
 
-typedef void* __amdgpu_buffer_rsrc_t;
 typedef uint32_t host_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t host_u32x2 __attribute__((ext_vector_type(2)));
-int __builtin_amdgcn_readfirstlane(int);
-int __builtin_amdgcn_mov_dpp(int, int, int, int, bool);
+
+// Raw buffers.  A load is out of range by the thread's offset alone: the narrower of the two
+// readings of the range check (the other counts the uniform offset too).
+struct __amdgpu_buffer_rsrc_t { char* base; int bytes; };
+inline __amdgpu_buffer_rsrc_t __builtin_amdgcn_make_buffer_rsrc(void* p, int, int bytes, int) { return {(char*)p, bytes}; }
+inline host_u32x4 __builtin_amdgcn_raw_buffer_load_b128(__amdgpu_buffer_rsrc_t r, int voff, int soff, int) {
+  host_u32x4 v = {0, 0, 0, 0};
+  if ((int64_t)voff + 16 <= r.bytes) std::memcpy(&v, r.base + voff + soff, 16);
+  return v;
+}
+inline void __builtin_amdgcn_raw_buffer_store_b32(uint32_t v, __amdgpu_buffer_rsrc_t r, int voff, int soff, int) {
+  if ((int64_t)voff + 4 <= r.bytes) std::memcpy(r.base + voff + soff, &v, 4);
+}
+inline void __builtin_amdgcn_raw_buffer_store_b64(host_u32x2 v, __amdgpu_buffer_rsrc_t r, int voff, int soff, int) {
+  if ((int64_t)voff + 8 <= r.bytes) std::memcpy(r.base + voff + soff, &v, 8);
+}
+
+inline uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return v; }   // of values all lanes hold
+inline void __builtin_amdgcn_fence(int, const char*, ...) {}
+inline void __builtin_amdgcn_s_barrier() { __syncthreads(); }
+inline void __builtin_amdgcn_sched_barrier(int) {}
+
+// The data-parallel moves of the kernels, through a table of the workgroup's lanes.
+inline int host_lanes[1024];
+inline int __builtin_amdgcn_mov_dpp(int v, int ctrl, int, int, bool) {
+  const unsigned t = threadIdx.x;
+  host_lanes[t] = v;
+  __syncthreads();
+  const unsigned from = ctrl == 0xB1 ? t ^ 1 : ctrl == 0x4E ? t ^ 2 : ctrl == 0x141 ? t ^ 7 : t ^ 15;
+  const int r = host_lanes[from];
+  __syncthreads();
+  return r;
+}
+
 int __builtin_amdgcn_perm(uint32_t, uint32_t, uint32_t);
 int __builtin_amdgcn_ds_bpermute(int, int);
 int __builtin_amdgcn_ds_swizzle(int, int);
-void __builtin_amdgcn_fence(int, const char*, ...);
-void __builtin_amdgcn_s_barrier();
-void __builtin_amdgcn_sched_barrier(int);
-__amdgpu_buffer_rsrc_t __builtin_amdgcn_make_buffer_rsrc(void*, int, int, int);
-host_u32x4 __builtin_amdgcn_raw_buffer_load_b128(__amdgpu_buffer_rsrc_t, int, int, int);
-void __builtin_amdgcn_raw_buffer_store_b32(uint32_t, __amdgpu_buffer_rsrc_t, int, int, int);
-void __builtin_amdgcn_raw_buffer_store_b64(host_u32x2, __amdgpu_buffer_rsrc_t, int, int, int);
 template <class V> V __builtin_amdgcn_mfma_i32_16x16x64_i8(V, V, V, int, int, int);

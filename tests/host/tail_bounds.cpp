@@ -2,29 +2,14 @@
 // output and its LDS array each ending at a guard page: an access out of range ends the
 // process with a signal.  Outputs are compared with eq. (3)'s fold written out.
 //   tail_bounds F threads   (n = q + F qubits, q = 6: the sizes of the batch's tail stage)
-#include <sys/mman.h>
-#include <unistd.h>
-
 #include <cstdio>
-#include <cstdlib>
-#include <memory>
 #include <thread>
 #include <vector>
 
+#include "guarded.hpp"
 #include "lre_tile.hpp"
 
 using namespace lre;
-
-// `bytes` (a multiple of 16) of zeroed memory that end where unmapped memory begins, with
-// unmapped memory before them too.
-template <class T>
-T* guarded(size_t elems) {
-  const size_t page = (size_t)sysconf(_SC_PAGESIZE), gap = (size_t)64 << 20;
-  const size_t bytes = elems * sizeof(T), mapped = (bytes + page - 1) / page * page;
-  char* p = static_cast<char*>(mmap(nullptr, mapped + 2 * gap, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
-  if (p == MAP_FAILED || mprotect(p + gap, mapped, PROT_READ | PROT_WRITE) != 0) std::abort();
-  return reinterpret_cast<T*>(p + gap + mapped - bytes);
-}
 
 template <int F, class Acc, Out MODE>
 int run(int threads) {

@@ -31,3 +31,10 @@ def tail_bounds(tmp_path_factory):
 def test_last_pass_stays_in_bounds(tail_bounds, qubits, threads):
     run = subprocess.run([tail_bounds, str(qubits), str(threads)], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0, run.stdout + run.stderr
+
+
+def test_row_totals_stay_in_bounds(tmp_path):
+    """The sub-tile pass with totals from the rows (6 to 8 qubits), its last row block."""
+    run = subprocess.run([compile_host("subtile_rows.cpp", tmp_path / "subtile_rows")], capture_output=True, text=True,
+                         timeout=300)
+    assert run.returncode == 0, run.stdout + run.stderr
