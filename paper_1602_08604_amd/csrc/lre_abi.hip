@@ -770,16 +770,19 @@ lre_status lre_check(lre_ctx* ctx, void* stream) {
   if (!g.ok) return LRE_E_HIP;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (hipStreamSynchronize(st) != hipSuccess) return LRE_E_HIP;
-  uint32_t raised = 0;
-  for (int k = 0; k < 16; ++k) raised |= ctx->host_flags[k];
-  if (!raised) return LRE_OK;
+  uint32_t any = 0, raised[16], f = 0;
+  for (int k = 0; k < 16; ++k) any |= ctx->host_flags[k];
+  if (!any) return LRE_OK;
   // Mirror first: a bit raised meanwhile then leaves at worst a mirror word without its bit.
-  for (int k = 0; k < 16; ++k) ctx->host_flags[k] = 0;
-  uint32_t f = 0;
-  if (hipMemcpy(&f, ctx->flags, sizeof f, hipMemcpyDeviceToHost) != hipSuccess) return LRE_E_HIP;
-  if (f) {
-    const uint32_t zero = 0;
-    if (hipMemcpy(ctx->flags, &zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess) return LRE_E_HIP;
+  // If a copy fails, the bits are still raised on the device, whose kernels set the mirror
+  // for a new bit only: the words are set again, for the next check.
+  for (int k = 0; k < 16; ++k) raised[k] = __atomic_exchange_n(ctx->host_flags + k, 0u, __ATOMIC_RELAXED);
+  const uint32_t zero = 0;
+  if (hipMemcpy(&f, ctx->flags, sizeof f, hipMemcpyDeviceToHost) != hipSuccess ||
+      (f && hipMemcpy(ctx->flags, &zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess)) {
+    for (int k = 0; k < 16; ++k)
+      if (raised[k]) ctx->host_flags[k] = 1;
+    return LRE_E_HIP;
   }
   if (f & FLAG_WAIT) return LRE_E_TIMEOUT;
   if (f & FLAG_EIG) return LRE_E_EIG;
