@@ -972,7 +972,12 @@ lre_status lre_stream_create(lre_ctx* ctx, int n, int h, uint64_t shots, uint32_
   }
   S->tV = S->P.npass ? S->P.tout[S->P.npass - 1] : S->P.t1;
   S->slabs = ipow3(h);
-  S->pushed.assign((size_t)S->slabs, 0);
+  try {
+    S->pushed.assign((size_t)S->slabs, 0);
+  } catch (...) {   // host memory
+    delete S;
+    return LRE_E_HIP;
+  }
   const size_t segs = (size_t)1 << h;
   S->seg_rowpart = align256((size_t)S->P.parts * (size_t)ipow3(S->P.q1) * 4);
   // Segments of a slab run side by side as far as their partials stay within 4 GiB (one

@@ -950,45 +950,20 @@ void launch_staged(const lre_batch& B, char* ws, hipStream_t st) {
   }
 }
 
-}  // namespace
-
-extern "C" {
-
-lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uint32_t flags,
-                          lre_batch** plan_out) {
-  if (!plan_out) return LRE_E_ARG;
-  *plan_out = nullptr;
-  if (!ctx || !inst || count < 1) return LRE_E_ARG;
-  if (flags & ~(LRE_NO_RHO | LRE_RHO_FP32)) return LRE_E_ARG;
-  const bool want_rho = !(flags & LRE_NO_RHO);
-  for (int j = 0; j < count; ++j) {
-    const lre_instance& I = inst[j];
-    if (I.n < 1 || !I.counts || !I.coef || !aligned(I.counts, 16) || !aligned(I.coef, 8)) return LRE_E_ARG;
-    if (I.n > LRE_BATCH_MAX_QUBITS) return LRE_E_UNSUPPORTED;
-    if (I.shots == 0 && I.n_per_basis && !aligned(I.n_per_basis, 4)) return LRE_E_ARG;
-    if ((long double)I.shots * (long double)ipow3(I.n) > (long double)INT32_MAX) return LRE_E_ARG;
-    if (want_rho && (!I.rho || !aligned(I.rho, 16))) return LRE_E_ARG;
-  }
-  DeviceGuard g(ctx->device);
-  if (!g.ok) return LRE_E_HIP;
-  lre_batch* B = new (std::nothrow) lre_batch;
-  if (!B) return LRE_E_HIP;
-  B->ctx = ctx;
-  B->flags = flags;
-  B->inst.assign(inst, inst + count);
-  B->meta.resize(count);
-  B->dinst_host.resize(count);
-  if (hipDeviceGetAttribute(&B->num_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess ||
-      B->num_cu < 1) {
-    delete B;
+// Everything of a plan but its checks, context and flags.  (May throw: host tables.)
+lre_status fill_plan(lre_batch& B, const lre_instance* inst, int count) {
+  B.inst.assign(inst, inst + count);
+  B.meta.resize(count);
+  B.dinst_host.resize(count);
+  if (hipDeviceGetAttribute(&B.num_cu, hipDeviceAttributeMultiprocessorCount, B.ctx->device) != hipSuccess ||
+      B.num_cu < 1)
     return LRE_E_HIP;
-  }
-  const int lv = staged_level(inst, count, B->num_cu);
-  B->ctl_bytes = align256((size_t)(1 + 3 * (size_t)count) * 4);
-  size_t off = B->ctl_bytes;
+  const int lv = staged_level(inst, count, B.num_cu);
+  B.ctl_bytes = align256((size_t)(1 + 3 * (size_t)count) * 4);
+  size_t off = B.ctl_bytes;
   for (int j = 0; j < count; ++j) {
     const lre_instance& I = inst[j];
-    InstMeta& m = B->meta[j];
+    InstMeta& m = B.meta[j];
     m.n = I.n;
     m.q1 = I.n < kQ ? I.n : kQ;
     m.F = I.n > kQ ? I.n - kQ : 0;
@@ -996,8 +971,8 @@ lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uin
     m.pb = I.shots == 0;
     m.mad24 = !m.pb && m.q1 == kQ && 27ull * I.shots < (1ull << 23);
     m.counts = ipow3(I.n) << I.n;
-    B->pb = B->pb || m.pb;
-    BInst& d = B->dinst_host[j];
+    B.pb = B.pb || m.pb;
+    BInst& d = B.dinst_host[j];
     d.counts = I.counts;
     d.coef = I.coef;
     d.rho = I.rho;
@@ -1025,37 +1000,57 @@ lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uin
   }
   std::vector<StagedInst> sinst;
   StagedTables tab;
-  plan_staged(*B, lv, off, sinst, tab);
-  B->ws_bytes = off;
-  if (hipMalloc(&B->d_inst, count * sizeof(BInst)) != hipSuccess) {
-    delete B;
+  plan_staged(B, lv, off, sinst, tab);
+  B.ws_bytes = off;
+  if (hipMalloc(&B.d_inst, count * sizeof(BInst)) != hipSuccess ||
+      hipMemcpy(B.d_inst, B.dinst_host.data(), count * sizeof(BInst), hipMemcpyHostToDevice) != hipSuccess)
     return LRE_E_HIP;
-  }
-  if (hipMemcpy(B->d_inst, B->dinst_host.data(), count * sizeof(BInst), hipMemcpyHostToDevice) != hipSuccess) {
-    (void)hipFree(B->d_inst);
-    delete B;
-    return LRE_E_HIP;
-  }
   // The smallest shape (one row group, kBT columns, one row pattern per item) gives
   // the longest list; the list is allocated once at that length.
-  const size_t cap = list_items(*B, lre_batch_tiles{1, 1, kBT, 1, 0, 0}).size();
-  if (cap > (size_t)INT32_MAX) {
-    lre_batch_destroy(B);
-    return LRE_E_UNSUPPORTED;
-  }
-  if (hipMalloc(&B->d_items, std::max<size_t>(cap, 1) * sizeof(BItem)) != hipSuccess ||
-      hipMalloc(&B->d_nitems, 256) != hipSuccess) {
-    lre_batch_destroy(B);
+  const size_t cap = list_items(B, lre_batch_tiles{1, 1, kBT, 1, 0, 0}).size();
+  if (cap > (size_t)INT32_MAX) return LRE_E_UNSUPPORTED;
+  if (hipMalloc(&B.d_items, std::max<size_t>(cap, 1) * sizeof(BItem)) != hipSuccess ||
+      hipMalloc(&B.d_nitems, 256) != hipSuccess)
     return LRE_E_HIP;
+  B.items_cap = cap;
+  if (!upload_staged(B, sinst, tab)) return LRE_E_HIP;
+  B.tiles = lre_batch_tiles{1, 4, kBT * 16, 1, 0, 0};   // the unstaged list's first shape
+  const lre_status s = rebuild(B);
+  B.tiles = lre_batch_tiles{1, 16, kBT * 16, 1, 0, 1};
+  return s;
+}
+
+}  // namespace
+
+extern "C" {
+
+lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uint32_t flags,
+                          lre_batch** plan_out) {
+  if (!plan_out) return LRE_E_ARG;
+  *plan_out = nullptr;
+  if (!ctx || !inst || count < 1) return LRE_E_ARG;
+  if (flags & ~(LRE_NO_RHO | LRE_RHO_FP32)) return LRE_E_ARG;
+  const bool want_rho = !(flags & LRE_NO_RHO);
+  for (int j = 0; j < count; ++j) {
+    const lre_instance& I = inst[j];
+    if (I.n < 1 || !I.counts || !I.coef || !aligned(I.counts, 16) || !aligned(I.coef, 8)) return LRE_E_ARG;
+    if (I.n > LRE_BATCH_MAX_QUBITS) return LRE_E_UNSUPPORTED;
+    if (I.shots == 0 && I.n_per_basis && !aligned(I.n_per_basis, 4)) return LRE_E_ARG;
+    if ((long double)I.shots * (long double)ipow3(I.n) > (long double)INT32_MAX) return LRE_E_ARG;
+    if (want_rho && (!I.rho || !aligned(I.rho, 16))) return LRE_E_ARG;
   }
-  B->items_cap = cap;
-  if (!upload_staged(*B, sinst, tab)) {
-    lre_batch_destroy(B);
-    return LRE_E_HIP;
+  DeviceGuard g(ctx->device);
+  if (!g.ok) return LRE_E_HIP;
+  lre_batch* B = new (std::nothrow) lre_batch;
+  if (!B) return LRE_E_HIP;
+  B->ctx = ctx;
+  B->flags = flags;
+  lre_status s;
+  try {
+    s = fill_plan(*B, inst, count);
+  } catch (...) {   // host memory
+    s = LRE_E_HIP;
   }
-  B->tiles = lre_batch_tiles{1, 4, kBT * 16, 1, 0, 0};   // the unstaged list's first shape
-  const lre_status s = rebuild(*B);
-  B->tiles = lre_batch_tiles{1, 16, kBT * 16, 1, 0, 1};
   if (s != LRE_OK) {
     lre_batch_destroy(B);
     return s;
@@ -1068,9 +1063,15 @@ size_t lre_batch_workspace_bytes(const lre_batch* plan) { return plan ? plan->ws
 
 lre_status lre_batch_set_tiles(lre_batch* plan, const lre_batch_tiles* tiles) {
   if (!plan || !tiles || !valid_tiles(*tiles)) return LRE_E_ARG;
+  const lre_batch_tiles before = plan->tiles;
   plan->tiles = *tiles;
   if (tiles->staged) return LRE_OK;   // its tables do not depend on the shape
-  return rebuild(*plan);
+  try {
+    return rebuild(*plan);
+  } catch (...) {   // host memory, before anything was replaced
+    plan->tiles = before;
+    return LRE_E_HIP;
+  }
 }
 
 lre_status lre_batch_get_tiles(const lre_batch* plan, lre_batch_tiles* tiles, int* num_items) {
