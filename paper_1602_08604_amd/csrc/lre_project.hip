@@ -32,6 +32,9 @@ using lre_detail::DeviceGuard;
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
+// Words beside the solver's info: hetrd_kernel's power of two.
+constexpr int kInfoSolver = 0, kInfoExp = 1, kInfoWords = 2;
+
 struct ProjLayout {
   size_t a, b, w, e, lam, info, total;
 };
@@ -45,7 +48,7 @@ ProjLayout proj_layout(int n) {
   L.w = off; off += align256(8 * d);          // eigenvalues of mu, ascending
   L.e = off; off += align256(8 * d);          // solver scratch (off-diagonal)
   L.lam = off; off += align256(8 * d);        // projected spectrum
-  L.info = off; off += align256(sizeof(rocblas_int));
+  L.info = off; off += align256(kInfoWords * sizeof(rocblas_int));
   L.total = off;
   return L;
 }
@@ -109,18 +112,24 @@ __device__ __forceinline__ int spectrum_cut(const double* w, int d, int tid, dou
   return cut;
 }
 
-// A solver failure (info != 0) raises FLAG_EIG and leaves lambda = 0.
-__global__ __launch_bounds__(kSpectrumThreads) void spectrum_kernel(const double* __restrict__ w, double* __restrict__ lam,
-                                                                    const rocblas_int* __restrict__ info, int d,
+// A solver failure (info != 0) raises FLAG_EIG and leaves lambda = 0.  own: w are those of
+// hetrd_kernel's matrix (its power of two).
+__global__ __launch_bounds__(kSpectrumThreads) void spectrum_kernel(double* __restrict__ w, double* __restrict__ lam,
+                                                                    const rocblas_int* __restrict__ info, bool own, int d,
                                                                     uint32_t* __restrict__ flags,
                                                                     double* __restrict__ eig_out) {
   __shared__ double run[kSpectrumThreads];
   __shared__ int first;
   const int tid = threadIdx.x;
-  if (*info != 0) {
+  if (info[kInfoSolver] != 0) {
     if (tid == 0) lre::raise_flag(flags, lre::FLAG_EIG);
     for (int j = tid; j < d; j += kSpectrumThreads) lam[j] = 0.0;
     return;
+  }
+  const int ex = own ? info[kInfoExp] : 0;
+  if (ex != 0) {
+    for (int j = tid; j < d; j += kSpectrumThreads) w[j] = ldexp(w[j], ex);
+    __syncthreads();
   }
   double shift;
   const int cut = spectrum_cut<kSpectrumThreads>(w, d, tid, run, &first, shift);
@@ -422,11 +431,12 @@ constexpr int kHetrdThreads = 1024;
 
 template <int D>
 __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restrict__ A, double* __restrict__ dg,
-                                                              double* __restrict__ e) {
+                                                              double* __restrict__ e,
+                                                              rocblas_int* __restrict__ info) {
   constexpr int CH = D / 64, WAVES = kHetrdThreads / 64;
   __shared__ double2 vP[D], wP[D], vN[D];     // previous step's v and w, this step's v
   __shared__ double yre[D], yim[D];
-  __shared__ double red[WAVES][2];
+  __shared__ double red[WAVES][2], redm[WAVES];
   __shared__ double2 alpha_s;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -439,6 +449,15 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
     double2 t = make_double2(0.0, 0.0);
     for (int k = 0; k < WAVES; ++k) { t.x += red[k][0]; t.y += red[k][1]; }
     return t;
+  };
+  // Largest m of the block (m >= 0), in every thread.
+  auto block_max = [&](double m) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    if (lane == 0) redm[wave] = m;
+    __syncthreads();
+    for (int k = 0; k < WAVES; ++k) m = fmax(m, redm[k]);
+    return m;
   };
   if (tid < D) vP[tid] = wP[tid] = make_double2(0.0, 0.0);
   __syncthreads();
@@ -455,12 +474,26 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
     }
     if (i == D - 1) break;                     // uniform
     if (tid < D) yre[tid] = yim[tid] = 0.0;
-    const double2 n2 = block_sum(tid < D && tid > i + 1 ? x.x * x.x + x.y * x.y : 0.0, 0.0);
-    const double2 al = alpha_s;
+    auto tail2 = [&] { return block_sum(tid < D && tid > i + 1 ? x.x * x.x + x.y * x.y : 0.0, 0.0).x; };
+    double n2 = tail2();
+    double2 al = alpha_s;
+    // Squares near the ends of the type's range, or none (uniform): the column times a power of
+    // two that brings its largest entry to [1/2, 1).  The reflector is the same, beta scales.
+    int ex = 0;
+    const double all2 = al.x * al.x + al.y * al.y + n2;
+    if (!(all2 > 1e-280 && all2 < 1e280)) {
+      const double big = block_max(tid < D && tid > i ? fmax(fabs(x.x), fabs(x.y)) : 0.0);
+      if (big > 0.0 && big < INFINITY) {
+        (void)frexp(big, &ex);
+        x = make_double2(ldexp(x.x, -ex), ldexp(x.y, -ex));
+        al = make_double2(ldexp(al.x, -ex), ldexp(al.y, -ex));
+        n2 = tail2();
+      }
+    }
     double beta = al.x;
     double2 tau = make_double2(0.0, 0.0), scale = make_double2(0.0, 0.0);
-    if (n2.x != 0.0 || al.y != 0.0) {
-      beta = sqrt(al.x * al.x + al.y * al.y + n2.x);
+    if (n2 != 0.0 || al.y != 0.0) {
+      beta = sqrt(al.x * al.x + al.y * al.y + n2);
       if (al.x >= 0.0) beta = -beta;
       tau = make_double2((beta - al.x) / beta, -al.y / beta);
       const double dx = al.x - beta, q = 1.0 / (dx * dx + al.y * al.y);
@@ -476,7 +509,7 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
       vN[tid] = v;
     }
     if (tid == 0) {
-      e[i] = beta;
+      e[i] = ldexp(beta, ex);
       A[i + (int64_t)i * D] = tau;
     }
     __syncthreads();
@@ -556,6 +589,18 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
     }
     __syncthreads();
   }
+  // T times a power of two that brings its largest entry to [1/2, 1), which the spectrum step takes
+  // back: the library's solver has absolute thresholds (a matrix of 2^-90 had eigenvalues off by
+  // 1 % of their size).
+  __syncthreads();
+  const double td = tid < D ? dg[tid] : 0.0, te = tid < D - 1 ? e[tid] : 0.0;
+  const double big = block_max(fmax(fabs(td), fabs(te)));
+  int ex = 0;
+  if (big < INFINITY) (void)frexp(big, &ex);
+  if (tid == 0) info[kInfoExp] = ex;
+  if (ex == 0) return;                       // uniform
+  if (tid < D) dg[tid] = ldexp(td, -ex);
+  if (tid < D - 1) e[tid] = ldexp(te, -ex);
 }
 
 // B = Q B for the reflectors hetrd_kernel leaves in A: a wave takes a column of B into
@@ -605,8 +650,8 @@ __global__ __launch_bounds__(64) void unmtr_kernel(const double2* __restrict__ A
 }
 
 template <int D>
-void launch_hetrd(double2* A, double* dg, double* e, hipStream_t st) {
-  hipLaunchKernelGGL((hetrd_kernel<D>), dim3(1), dim3(kHetrdThreads), 0, st, A, dg, e);
+void launch_hetrd(double2* A, double* dg, double* e, rocblas_int* info, hipStream_t st) {
+  hipLaunchKernelGGL((hetrd_kernel<D>), dim3(1), dim3(kHetrdThreads), 0, st, A, dg, e, info);
 }
 
 template <int D>
@@ -691,8 +736,8 @@ lre_status lre_project(lre_ctx* ctx, int n, const void* mu, void* rho, double* e
     auto* b2 = reinterpret_cast<double2*>(B);
     hipLaunchKernelGGL(lower_copy_kernel, dim3((unsigned)(d / 16), (unsigned)(d / 16)), dim3(256), 0, st,
                        static_cast<const double2*>(mu), a2, d);
-    if (n == 7) launch_hetrd<128>(a2, W, E, st);
-    else launch_hetrd<256>(a2, W, E, st);
+    if (n == 7) launch_hetrd<128>(a2, W, E, info, st);
+    else launch_hetrd<256>(a2, W, E, info, st);
     if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
     // eigenvectors of the tridiagonal matrix into B, then Q times them
     if (rocsolver_zstedc(h, rocblas_evect_tridiagonal, d, W, E, B, d, info) != rocblas_status_success)
@@ -706,7 +751,8 @@ lre_status lre_project(lre_ctx* ctx, int n, const void* mu, void* rho, double* e
              rocblas_status_success) {
     return LRE_E_HIP;
   }
-  hipLaunchKernelGGL(spectrum_kernel, dim3(1), dim3(kSpectrumThreads), 0, st, W, lam, info, d, ctx->flags, eigvals);
+  hipLaunchKernelGGL(spectrum_kernel, dim3(1), dim3(kSpectrumThreads), 0, st, W, lam, info, n <= kHetrdN, d,
+                     ctx->flags, eigvals);
   const int64_t elems = (int64_t)d * d;
   hipLaunchKernelGGL(scale_columns_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, st,
                      reinterpret_cast<const double2*>(V), lam, reinterpret_cast<double2*>(scaled), n);
