@@ -32,8 +32,8 @@ using lre_detail::DeviceGuard;
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-// Words beside the solver's info: hetrd_kernel's power of two.
-constexpr int kInfoSolver = 0, kInfoExp = 1, kInfoWords = 2;
+// Words beside the solver's info: hetrd_kernel's power of two, whether something is not finite.
+constexpr int kInfoSolver = 0, kInfoExp = 1, kInfoBad = 2, kInfoWords = 3;
 
 struct ProjLayout {
   size_t a, b, w, e, lam, info, total;
@@ -112,24 +112,28 @@ __device__ __forceinline__ int spectrum_cut(const double* w, int d, int tid, dou
   return cut;
 }
 
-// A solver failure (info != 0) raises FLAG_EIG and leaves lambda = 0.  own: w are those of
-// hetrd_kernel's matrix (its power of two).
+// A solver failure (info), or eigenvalues that are not finite, raise FLAG_EIG and leave lambda = 0.
+// own: w are those of hetrd_kernel's matrix (its power of two).
 __global__ __launch_bounds__(kSpectrumThreads) void spectrum_kernel(double* __restrict__ w, double* __restrict__ lam,
-                                                                    const rocblas_int* __restrict__ info, bool own, int d,
+                                                                    rocblas_int* __restrict__ info, bool own, int d,
                                                                     uint32_t* __restrict__ flags,
                                                                     double* __restrict__ eig_out) {
   __shared__ double run[kSpectrumThreads];
-  __shared__ int first;
+  __shared__ int first, bad;
   const int tid = threadIdx.x;
-  if (info[kInfoSolver] != 0) {
+  if (tid == 0) bad = info[kInfoSolver] != 0 || (own && info[kInfoBad] != 0);
+  __syncthreads();
+  const int ex = own ? info[kInfoExp] : 0;
+  for (int j = tid; j < d; j += kSpectrumThreads) {
+    if (!isfinite(w[j])) bad = 1;
+    else if (ex != 0) w[j] = ldexp(w[j], ex);
+  }
+  __syncthreads();
+  if (tid == 0) info[kInfoBad] = bad;
+  if (bad) {                                 // uniform
     if (tid == 0) lre::raise_flag(flags, lre::FLAG_EIG);
     for (int j = tid; j < d; j += kSpectrumThreads) lam[j] = 0.0;
     return;
-  }
-  const int ex = own ? info[kInfoExp] : 0;
-  if (ex != 0) {
-    for (int j = tid; j < d; j += kSpectrumThreads) w[j] = ldexp(w[j], ex);
-    __syncthreads();
   }
   double shift;
   const int cut = spectrum_cut<kSpectrumThreads>(w, d, tid, run, &first, shift);
@@ -591,16 +595,22 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
   }
   // T times a power of two that brings its largest entry to [1/2, 1), which the spectrum step takes
   // back: the library's solver has absolute thresholds (a matrix of 2^-90 had eigenvalues off by
-  // 1 % of their size).
+  // 1 % of their size).  What is not finite has no eigenvalues: zeros,
+  // for matrix and reflectors.
   __syncthreads();
   const double td = tid < D ? dg[tid] : 0.0, te = tid < D - 1 ? e[tid] : 0.0;
-  const double big = block_max(fmax(fabs(td), fabs(te)));
+  const double big = block_max(isfinite(td) && isfinite(te) ? fmax(fabs(td), fabs(te)) : INFINITY);
   int ex = 0;
   if (big < INFINITY) (void)frexp(big, &ex);
-  if (tid == 0) info[kInfoExp] = ex;
-  if (ex == 0) return;                       // uniform
-  if (tid < D) dg[tid] = ldexp(td, -ex);
-  if (tid < D - 1) e[tid] = ldexp(te, -ex);
+  if (tid == 0) {
+    info[kInfoExp] = ex;
+    info[kInfoBad] = big < INFINITY ? 0 : 1;
+  }
+  if (big < INFINITY && ex == 0) return;     // uniform
+  if (tid < D) dg[tid] = big < INFINITY ? ldexp(td, -ex) : 0.0;
+  if (tid < D - 1) e[tid] = big < INFINITY ? ldexp(te, -ex) : 0.0;
+  if (big < INFINITY) return;
+  for (int t = tid; t < D * D; t += kHetrdThreads) A[t] = make_double2(0.0, 0.0);
 }
 
 // B = Q B for the reflectors hetrd_kernel leaves in A: a wave takes a column of B into
@@ -659,16 +669,31 @@ void launch_unmtr(const double2* A, double2* B, hipStream_t st) {
   hipLaunchKernelGGL((unmtr_kernel<D>), dim3(D), dim3(64), 0, st, A, B);
 }
 
-// b[:, j] = a[:, j] * lam[j] (column-major d x d).
+// b[:, j] = a[:, j] * lam[j] (column-major d x d).  Eigenvectors that are not finite are a failure
+// of the solver as well.
 __global__ __launch_bounds__(256) void scale_columns_kernel(const double2* __restrict__ a,
                                                             const double* __restrict__ lam,
-                                                            double2* __restrict__ b, int n) {
+                                                            double2* __restrict__ b, int n,
+                                                            rocblas_int* __restrict__ info,
+                                                            uint32_t* __restrict__ flags) {
   const int64_t d = (int64_t)1 << n;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= d * d) return;
   const double s = lam[i >> n];
   const double2 v = a[i];
   b[i] = make_double2(v.x * s, v.y * s);
+  if (!(isfinite(v.x) && isfinite(v.y))) {
+    info[kInfoBad] = 1;
+    lre::raise_flag(flags, lre::FLAG_EIG);
+  }
+}
+
+// rho = 0 after a failure (the product of a failed solver's vectors need not be).
+__global__ __launch_bounds__(256) void clear_failed_kernel(double2* __restrict__ rho, int64_t elems,
+                                                           const rocblas_int* __restrict__ info) {
+  if (info[kInfoBad] == 0) return;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < elems; i += (int64_t)gridDim.x * 256)
+    rho[i] = make_double2(0.0, 0.0);
 }
 
 }  // namespace
@@ -755,13 +780,16 @@ lre_status lre_project(lre_ctx* ctx, int n, const void* mu, void* rho, double* e
                      ctx->flags, eigvals);
   const int64_t elems = (int64_t)d * d;
   hipLaunchKernelGGL(scale_columns_kernel, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0, st,
-                     reinterpret_cast<const double2*>(V), lam, reinterpret_cast<double2*>(scaled), n);
+                     reinterpret_cast<const double2*>(V), lam, reinterpret_cast<double2*>(scaled), n, info,
+                     ctx->flags);
   if (hipGetLastError() != hipSuccess) return LRE_E_HIP;
   const rocblas_double_complex one = {1.0, 0.0}, zero = {0.0, 0.0};
   if (rocblas_zgemm(h, rocblas_operation_none, rocblas_operation_conjugate_transpose, d, d, d, &one, scaled, d, V,
                     d, &zero, static_cast<rocblas_double_complex*>(rho), d) != rocblas_status_success)
     return LRE_E_HIP;
-  return LRE_OK;
+  hipLaunchKernelGGL(clear_failed_kernel, dim3(256), dim3(256), 0, st, static_cast<double2*>(rho), elems,
+                     static_cast<const rocblas_int*>(info));
+  return hipGetLastError() == hipSuccess ? LRE_OK : LRE_E_HIP;
 }
 
 }  // extern "C"
