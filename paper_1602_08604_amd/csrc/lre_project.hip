@@ -313,7 +313,6 @@ __global__ __launch_bounds__(JacobiGeom<N>::THREADS) void jacobi_project_kernel(
 #pragma unroll 2
     for (int r = 0; r < D; ++r) s += V[r * P + i].x * V[r * P + i].x + V[r * P + i].y * V[r * P + i].y;
     rotq[i] = 1.0 / sqrt(s);
-    lam[i] = 0.0;
   }
   for (int t = tid; t < D * D; t += TH) {        // mu again (the rounds are over)
     const double2 m = element(t / D, t % D);
@@ -326,13 +325,22 @@ __global__ __launch_bounds__(JacobiGeom<N>::THREADS) void jacobi_project_kernel(
     V[r * P + c].y *= rotq[c];
   }
   __syncthreads();
+  static_assert(TH % D == 0, "a thread's elements are of one eigenvector");
+  double quotient = 0.0;
   for (int t = tid; t < D * D; t += TH) {        // (row r, eigenvector i): conj(v_r) (mu v)_r
     const int r = t / D, i = t % D;
     double2 s = make_double2(0.0, 0.0);
 #pragma unroll 2
     for (int k = 0; k < D; ++k) s = cfma(A[r * P + k], V[k * P + i], s);
     const double2 v = V[r * P + i];
-    atomicAdd(&lam[i], v.x * s.x + v.y * s.y);
+    quotient += v.x * s.x + v.y * s.y;
+  }
+  run[tid] = quotient;
+  __syncthreads();
+  for (int i = tid; i < D; i += TH) {            // in a fixed order: two runs give the same bits
+    double q = 0.0;
+    for (int k = i; k < TH; k += D) q += run[k];
+    lam[i] = q;
   }
   __syncthreads();
   for (int i = tid; i < D; i += TH) {
@@ -439,7 +447,8 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
                                                               rocblas_int* __restrict__ info) {
   constexpr int CH = D / 64, WAVES = kHetrdThreads / 64;
   __shared__ double2 vP[D], wP[D], vN[D];     // previous step's v and w, this step's v
-  __shared__ double yre[D], yim[D];
+  __shared__ double ydot[2][D];               // A v: the columns' dot products
+  __shared__ double2 yrow[WAVES][D];          // and the rows' sums over each wave's columns
   __shared__ double red[WAVES][2], redm[WAVES];
   __shared__ double2 alpha_s;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -477,7 +486,6 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
       if (tid == i + 1) alpha_s = x;
     }
     if (i == D - 1) break;                     // uniform
-    if (tid < D) yre[tid] = yim[tid] = 0.0;
     auto tail2 = [&] { return block_sum(tid < D && tid > i + 1 ? x.x * x.x + x.y * x.y : 0.0, 0.0).x; };
     double n2 = tail2();
     double2 al = alpha_s;
@@ -563,7 +571,7 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
       const double s = wave_sum4(dot[0].x, dot[0].y, dot[1].x, dot[1].y);
       // lane 0: dot[0].x, 32: dot[0].y, 16: dot[1].x, 48: dot[1].y
       const int cl = c0 + ((lane & 16) ? WAVES : 0);
-      if ((lane & 15) == 0 && cl < D) atomicAdd((lane & 32) ? &yim[cl] : &yre[cl], s);
+      if ((lane & 15) == 0 && cl < D) ydot[(lane & 32) ? 1 : 0][cl] = s;
     };
     for (int c0 = i + 1 + wave; c0 < D; c0 += 2 * WAVES) {
       double2 a[2][CH];
@@ -572,18 +580,21 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
     }
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
-      const int r = 64 * j + lane;
-      if (r > i + 1) {
-        atomicAdd(&yre[r], ya[j].x);
-        atomicAdd(&yim[r], ya[j].y);
-      }
+      if (64 * j + 63 > i) yrow[wave][64 * j + lane] = ya[j];    // uniform
     }
     __syncthreads();
     // w = tau y - (1/2) tau (tau y)^H v v
     double2 xt = make_double2(0.0, 0.0), vt = make_double2(0.0, 0.0);
     if (tid < D && tid > i) {
       vt = vN[tid];
-      xt = cmul(tau, make_double2(yre[tid], yim[tid]));
+      double2 y = make_double2(ydot[0][tid], ydot[1][tid]);
+#pragma unroll
+      for (int k = 0; k < WAVES; ++k) {         // in a fixed order: two runs give the same bits
+        const double2 p = yrow[k][tid];
+        y.x += p.x;
+        y.y += p.y;
+      }
+      xt = cmul(tau, y);
     }
     const double2 dp = block_sum(xt.x * vt.x + xt.y * vt.y, xt.x * vt.y - xt.y * vt.x);   // conj(x) v
     const double2 half = cmul(make_double2(-0.5 * tau.x, -0.5 * tau.y), dp);
