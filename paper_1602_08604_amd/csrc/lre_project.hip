@@ -714,8 +714,13 @@ __global__ __launch_bounds__(64) void unmtr_kernel(const double2* __restrict__ A
       load(i - kAhead, v[k], tau[k]);
     }
   }
+  // to unit length: the solver's vectors and the reflectors' rounding are off by some 1e-15
+  double n2 = 0.0;
 #pragma unroll
-  for (int j = 0; j < CH; ++j) col[64 * j + lane] = b[j];
+  for (int j = 0; j < CH; ++j) n2 += b[j].x * b[j].x + b[j].y * b[j].y;
+  const double unit = 1.0 / sqrt(__shfl(wave_sum4(n2, 0.0, 0.0, 0.0), 0));
+#pragma unroll
+  for (int j = 0; j < CH; ++j) col[64 * j + lane] = make_double2(b[j].x * unit, b[j].y * unit);
 }
 
 template <int D>
