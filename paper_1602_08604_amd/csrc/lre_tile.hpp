@@ -226,6 +226,11 @@ struct TileStages {
 // flags).
 __device__ __forceinline__ double tile_reciprocal(uint32_t N) { return N ? 1.0 / (double)N : 0.0; }
 
+// Whether partials are stored with the nontemporal hint, unless the launch says so: binary64
+// partials of 7-qubit tiles, which are read again only after more than the caches hold (plain
+// stores: n = 13 6.99 instead of 6.84 ms).
+constexpr bool tile_nt(int lv, bool pb) { return pb && lv >= 2; }
+
 template <bool NT, typename Acc>
 __device__ __forceinline__ void tile_put(__amdgpu_buffer_rsrc_t rsrc, int t, int i, Acc v) {
   const int soff = __builtin_amdgcn_readfirstlane(i * (int)sizeof(Acc));
@@ -397,16 +402,13 @@ struct TileLds {
 };
 
 // The nt tiles of `tiles`, in sequence.  out of a tile: [4^Q] partial sums; part: [3^Q], the
-// row sums over the block's tiles of one row group.
-template <int LV, bool PB, typename Acc, class Tiles>
+// row sums over the block's tiles of one row group.  NT: partials stored with the nontemporal hint.
+template <int LV, bool PB, typename Acc, bool NT, class Tiles>
 __device__ __forceinline__ void counts_tiles_block(const Tiles& tiles, int nt, TileLds<LV, PB>& lds) {
   static_assert(LV == 1 || LV == 2, "levels above the sub-tile");
   using G = TileGeom<LV>;
   using S = TileStages<PB>;
   using Elem = typename S::Elem;
-  // Binary64 partials of the larger plans are read again only after more than the caches
-  // hold (plain stores: n = 13 6.99 instead of 6.84 ms, n = 12 integers 921 instead of 941 us).
-  constexpr bool kNT = PB && LV >= 2;
   const int nsteps = nt * G::NL * G::NS;                       // sub-tiles
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   Elem* const W = lds.W;
@@ -532,14 +534,14 @@ __device__ __forceinline__ void counts_tiles_block(const Tiles& tiles, int nt, T
           stages(0);
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
-            tile_put<kNT>(o, tid, 1024 * (l5 + 1) + 256 * k, (Acc)(T0[k] - T1[k]));
+            tile_put<NT>(o, tid, 1024 * (l5 + 1) + 256 * k, (Acc)(T0[k] - T1[k]));
             i5S[k] += (Acc)(T0[k] + T1[k]);
           }
           flush(l5);
           if constexpr (l5 == 2) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-              tile_put<kNT>(o, tid, 256 * k, i5S[k]);
+              tile_put<NT>(o, tid, 256 * k, i5S[k]);
               i5S[k] = Acc(0);
             }
           }
@@ -561,7 +563,7 @@ __device__ __forceinline__ void counts_tiles_block(const Tiles& tiles, int nt, T
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
               const Acc Sk = (Acc)(T0[k] + T1[k]), Dk = (Acc)(T0[k] - T1[k]);
-              tile_put<kNT>(o, tid, 4096 * (l6 + 1) + 1024 * (l5 + 1) + 256 * k, hD[k] - Dk);
+              tile_put<NT>(o, tid, 4096 * (l6 + 1) + 1024 * (l5 + 1) + 256 * k, hD[k] - Dk);
               i5S[k] += hS[k] + Sk;
               i5D[k] += hS[k] - Sk;
               i6[l5 + 1][k] += hD[k] + Dk;
@@ -570,7 +572,7 @@ __device__ __forceinline__ void counts_tiles_block(const Tiles& tiles, int nt, T
             if constexpr (l5 == 2) {
 #pragma unroll
               for (int k = 0; k < 4; ++k) {
-                tile_put<kNT>(o, tid, 4096 * (l6 + 1) + 256 * k, i5D[k]);
+                tile_put<NT>(o, tid, 4096 * (l6 + 1) + 256 * k, i5D[k]);
                 i6[0][k] += i5S[k];
                 i5S[k] = i5D[k] = Acc(0);
               }
@@ -579,7 +581,7 @@ __device__ __forceinline__ void counts_tiles_block(const Tiles& tiles, int nt, T
                 for (int q = 0; q < 4; ++q)
 #pragma unroll
                   for (int k = 0; k < 4; ++k) {
-                    tile_put<kNT>(o, tid, 1024 * q + 256 * k, i6[q][k]);
+                    tile_put<NT>(o, tid, 1024 * q + 256 * k, i6[q][k]);
                     i6[q][k] = Acc(0);
                   }
               }
@@ -594,7 +596,7 @@ __device__ __forceinline__ void counts_tiles_block(const Tiles& tiles, int nt, T
 
 // blockIdx.x: `per_block` consecutive tiles of an instance; blockIdx.y: segment, as for the
 // sub-tile kernel.  out: [3^(n-Q)][2^(n-Q)][4^Q]; rowpart: [b_hi + block][3^Q].
-template <int LV, bool PB, typename Acc>
+template <int LV, bool PB, typename Acc, bool NT>
 __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
     const uint16_t* __restrict__ counts, int n, int lrow, int64_t tiles, int64_t per_block,
     const uint32_t* __restrict__ nb, Acc* __restrict__ out, uint32_t* __restrict__ rowpart, int64_t seg_counts,
@@ -609,7 +611,7 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void counts_tile_kernel(
   T.n = n;
   T.lrow = lrow;
   T.lgT = n - TileGeom<LV>::WB;
-  counts_tiles_block<LV, PB, Acc>(T, (int)(tiles - T.t0 < per_block ? tiles - T.t0 : per_block), lds);
+  counts_tiles_block<LV, PB, Acc, NT>(T, (int)(tiles - T.t0 < per_block ? tiles - T.t0 : per_block), lds);
 }
 
 // The same over a table of tiles; part of a block's row group: [group + block][3^Q].
@@ -620,7 +622,7 @@ __global__ __launch_bounds__(512, PB ? 2 : 4) void batch_tiles_kernel(const Tile
   __shared__ TileLds<LV, PB> lds;
   const int t0 = (int)blockIdx.x * per_block;
   const BatchTiles<LV, Acc> T{(const __attribute__((address_space(4))) TileEntry*)(table + t0), ws, rowpart};
-  counts_tiles_block<LV, PB, Acc>(T, tiles - t0 < per_block ? tiles - t0 : per_block, lds);
+  counts_tiles_block<LV, PB, Acc, tile_nt(LV, PB)>(T, tiles - t0 < per_block ? tiles - t0 : per_block, lds);
 }
 
 // Row totals: where the parts of basis row group g = b / rows are.  per_block > 0: part
