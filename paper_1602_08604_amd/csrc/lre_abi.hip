@@ -1142,7 +1142,10 @@ namespace {
 // n = 12: 94 as 7 + 5, 117 as 6 + 4 + 2; n = 14: 2.18 ms as 7 + 4 + 3, 2.27 as 6 + 4 + 4).
 int povm_first_digits(int n) { return n <= 7 ? n : (n <= 10 ? 6 : 7); }
 
-// (32-bit offsets in povm_high5_kernel: lo <= 9; 5 digits are left for n = 12, lo = 7, only.)
+// Digits of a pass over `left` digits from lo on: 4, or what is left.  5 only as the last pass
+// (n = 12, as 7 + 5): where digits remain after it, its 128 KiB tiles cost more than the later
+// pass gains (n = 13: 576 us as 7 + 5 + 1, 542 as 7 + 4 + 2; n = 14: 2387 us as 7 + 5 + 2, 2175 as
+// 7 + 4 + 3).  (32-bit offsets in povm_high5_kernel: lo <= 9.)
 int povm_next_digits(int left, int lo) { return left == 5 && lo <= 9 ? 5 : (left >= 4 ? 4 : left); }
 
 template <int J, bool FINAL>
@@ -1155,13 +1158,11 @@ void launch_povm_tiles(const uint16_t* counts, double* coef, const double* M, un
                      flags, tiles);
 }
 
-template <bool FINAL>
 void launch_povm_high5(double* coef, int lo, const double* M, const unsigned long long* total, uint32_t* flags,
                        int64_t tiles, hipStream_t st) {
   const int64_t blocks =
-      std::min<int64_t>(tiles, resident_blocks(povm_high5_kernel<FINAL>, 1024, 1024LL * kPovmWideCols * 8));
-  hipLaunchKernelGGL((povm_high5_kernel<FINAL>), dim3((unsigned)blocks), dim3(1024), 0, st, coef, lo, M, total, flags,
-                     tiles);
+      std::min<int64_t>(tiles, resident_blocks(povm_high5_kernel, 1024, 1024LL * kPovmWideCols * 8));
+  hipLaunchKernelGGL(povm_high5_kernel, dim3((unsigned)blocks), dim3(1024), 0, st, coef, lo, M, total, flags, tiles);
 }
 
 }  // namespace
@@ -1219,8 +1220,7 @@ lre_status lre_povm_estimate(lre_ctx* ctx, int n, const uint16_t* counts, const 
     const dim3 grid((unsigned)((cols + 255) / 256));
     switch (F) {
       case 5:
-        if (last) launch_povm_high5<true>(coef, lo, Mc, tot, ctx->flags, cols / kPovmWideCols, st);
-        else launch_povm_high5<false>(coef, lo, Mc, tot, ctx->flags, cols / kPovmWideCols, st);
+        launch_povm_high5(coef, lo, Mc, tot, ctx->flags, cols / kPovmWideCols, st);
         break;
       case 4:
         if (last)

@@ -262,12 +262,12 @@ __global__ __launch_bounds__(PovmTileGeom<J>::TH) void povm_tile_kernel(const ui
   }
 }
 
-// Five digits lo .. lo + 4 (2 <= lo <= 9) of the vector, in place: tiles of 16 consecutive low
+// The last five digits lo .. lo + 4 (2 <= lo <= 9) of the vector, in place: tiles of 16 consecutive low
 // indices (one 128-byte line a row) x the 1024 values of the five digits, 128 KiB of LDS, tiles
 // blockIdx.x, + gridDim.x, ...  A thread loads 16 rows of one column straight into the first
 // two digits' registers (the block's next tile is loaded ahead), the next two digits pass
-// through LDS and the fifth stores to coef; FINAL divides by N.  Bound by memory: n = 12, one
-// pass of 57 us, 4.7 TB/s, where passes of 4 and 2 digits took 43 + 45.
+// through LDS and the fifth, divided by N, stores to coef.  Bound by memory: n = 12, one
+// pass of 47 us, 5.7 TB/s, where passes of 4 and 2 digits took 43 + 45.
 constexpr int kPovmWideCols = 16;
 
 // Rows of one half-wave's access differ in one digit bit: it picks the half of the banks.
@@ -286,14 +286,13 @@ struct PovmWideSlots {
   }
 };
 
-template <bool FINAL>
-__global__ __launch_bounds__(1024) void povm_high5_kernel(double* __restrict__ coef, int lo, const double* __restrict__ M,
+static __global__ __launch_bounds__(1024) void povm_high5_kernel(double* __restrict__ coef, int lo, const double* __restrict__ M,
                                                          const unsigned long long* __restrict__ total,
                                                          uint32_t* __restrict__ flags, int64_t tiles) {
   __shared__ double blk[1024 * kPovmWideCols];
   double m[16];
   povm_load_m(M, m);
-  const double N = FINAL ? povm_total(total, flags) : 1.0;
+  const double N = povm_total(total, flags);
   const int64_t L = (int64_t)1 << (2 * lo);
   const int gshift = 2 * lo - 4;                       // log2 of the tiles per high index
   const int col = threadIdx.x % kPovmWideCols, o = threadIdx.x / kPovmWideCols;   // o: 64 values
@@ -338,7 +337,7 @@ __global__ __launch_bounds__(1024) void povm_high5_kernel(double* __restrict__ c
       for (int k = 0; k < 4; ++k) z[k] = blk[s4(64 * q + 256 * k)];
       povm_apply1(m, z, 1);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) *reinterpret_cast<double*>(tile_base(b) + (off + (64 * q + 256 * k) * Lb)) = FINAL ? z[k] / N : z[k];
+      for (int k = 0; k < 4; ++k) *reinterpret_cast<double*>(tile_base(b) + (off + (64 * q + 256 * k) * Lb)) = z[k] / N;
     }
   }
 }
