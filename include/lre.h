@@ -247,8 +247,8 @@ lre_status lre_batch_set_tiles(lre_batch* plan, const lre_batch_tiles* tiles);
 /* The plan's current work-item shape and work-item count (staged: workgroups). */
 lre_status lre_batch_get_tiles(const lre_batch* plan, lre_batch_tiles* tiles, int* num_items);
 
-/* Autotuner: runs the batch (lre_batch_run) for each of 82 candidate work-item shapes
- * (72 unstaged and 10 staged; 41 for a plan with per-basis instances, whose list runs one
+/* Autotuner: runs the batch (lre_batch_run) for each of 77 candidate work-item shapes
+ * (72 unstaged and 5 staged; 41 for a plan with per-basis instances, whose list runs one
  * workgroup per CU),
  * `reps` timed runs each after one warm-up, keeps the fastest shape and returns its
  * mean time in *best_ms (may be NULL).  Synchronous on `stream`; overwrites the

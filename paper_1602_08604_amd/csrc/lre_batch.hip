@@ -1136,9 +1136,9 @@ lre_status lre_batch_tune(lre_batch* plan, void* workspace, size_t workspace_byt
           for (int il : {0, 1}) {
             if (w == 2 && plan->pb) continue;  // per-basis plans run one workgroup per CU
             // unstaged: 1, 2 or 4 row groups per counts item; staged: the fold and
-            // step-(ii) shapes are those of their own kernels
+            // step-(ii) shapes are those of their own kernels, and there are no workers
             if (!sg && ct > 4) continue;
-            if (sg && (fc != kBT * 16 || rb != 1 || il != 0)) continue;
+            if (sg && (w != 1 || fc != kBT * 16 || rb != 1 || il != 0)) continue;
             const lre_batch_tiles t{w, ct, fc, rb, il, sg};
             if ((s = lre_batch_set_tiles(plan, &t)) != LRE_OK) goto done;
             if ((s = lre_batch_run(plan, workspace, workspace_bytes, stream)) != LRE_OK) goto done;
