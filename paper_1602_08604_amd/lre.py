@@ -164,9 +164,16 @@ def context(device: int | None = None) -> int:
     return _contexts[dev]
 
 
+# The current stream's handle without a Stream object; not part of PyTorch's public API, so the public
+# one serves where it is missing.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
     index = torch.cuda.current_device() if device is None or device.index is None else device.index
-    return torch._C._cuda_getCurrentRawStream(index)
+    return _raw_stream(index)
 
 
 def _num_qubits(counts: torch.Tensor) -> int:
