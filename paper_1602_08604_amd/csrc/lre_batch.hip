@@ -636,9 +636,10 @@ struct lre_batch {
   std::vector<InstMeta> meta;
   std::vector<BInst> dinst_host;
   lre_batch_tiles tiles{};
+  char* d_block = nullptr;      // the plan's one device allocation; all below are inside
   BInst* d_inst = nullptr;
-  BItem* d_items = nullptr;     // work list, allocated once at the largest list any
-  int* d_nitems = nullptr;      // shape can give (fixed addresses for captured runs)
+  BItem* d_items = nullptr;     // work list, as long as the largest list any shape can give
+  int* d_nitems = nullptr;      // (fixed addresses for captured runs)
   // staged form: counts passes and, per block of its other kernels, what the block does
   std::vector<TilePass> passes;
   StagedInst* d_sinst = nullptr;
@@ -878,18 +879,56 @@ void plan_staged(lre_batch& B, int lv, size_t& off, std::vector<StagedInst>& sin
   B.nunits = (int)tab.units.size();
 }
 
-template <typename T>
-bool upload(T** dst, const std::vector<T>& v) {
-  if (v.empty()) return true;
-  return hipMalloc(dst, v.size() * sizeof(T)) == hipSuccess &&
-         hipMemcpy(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) == hipSuccess;
+// The length of the longest work list: one row group, kBT columns, one row pattern and
+// kTotalsPerItem bases per item.
+size_t longest_list(const lre_batch& B) {
+  const bool want_rho = !(B.flags & LRE_NO_RHO);
+  size_t n = 0;
+  for (const InstMeta& m : B.meta) {
+    if (m.n <= kQ) {
+      ++n;
+      continue;
+    }
+    n += (size_t)ipow3(m.n - kQ) + (size_t)((ipow4(kQ) + kBT - 1) / kBT) + (want_rho ? (size_t)1 << (m.n - kJ) : 0);
+    if (m.pb) n += (size_t)((ipow3(m.n) + kTotalsPerItem - 1) / kTotalsPerItem);
+  }
+  return n;
 }
 
-bool upload_staged(lre_batch& B, const std::vector<StagedInst>& sinst, const StagedTables& tab) {
+// The plan's device memory: the instances and the staged form's tables, copied in one piece
+// (an allocation and a copy each made a plan of one instance take 75 us instead of 50), then
+// the work list and its length, which lre_batch_set_tiles fills.
+lre_status upload_plan(lre_batch& B, const std::vector<StagedInst>& sinst, const StagedTables& tab) {
+  size_t off = 0;
+  std::vector<char> host;
+  auto put = [&](const auto& v) {
+    const size_t at = off, bytes = v.size() * sizeof v[0];
+    off += align256(bytes);
+    host.resize(off);
+    if (bytes) std::memcpy(host.data() + at, v.data(), bytes);
+    return at;
+  };
+  const size_t o_inst = put(B.dinst_host), o_sinst = put(sinst), o_small = put(tab.small), o_sums = put(tab.sums),
+               o_tail = put(tab.tail), o_units = put(tab.units);
+  std::vector<size_t> o_tiles;
+  for (const auto& t : tab.tiles) o_tiles.push_back(put(t));
+  const size_t o_items = off, o_nitems = o_items + align256(B.items_cap * sizeof(BItem));
+  if (hipMalloc(&B.d_block, o_nitems + 256) != hipSuccess) {
+    B.d_block = nullptr;
+    return LRE_E_HIP;
+  }
+  if (hipMemcpy(B.d_block, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return LRE_E_HIP;
+  B.d_inst = reinterpret_cast<BInst*>(B.d_block + o_inst);
+  B.d_sinst = reinterpret_cast<StagedInst*>(B.d_block + o_sinst);
+  B.d_small = reinterpret_cast<int32_t*>(B.d_block + o_small);
+  B.d_sums = reinterpret_cast<int2*>(B.d_block + o_sums);
+  B.d_tail = reinterpret_cast<int2*>(B.d_block + o_tail);
+  B.d_units = reinterpret_cast<int2*>(B.d_block + o_units);
   for (size_t k = 0; k < B.passes.size(); ++k)
-    if (!upload(&B.passes[k].d_table, tab.tiles[k])) return false;
-  return upload(&B.d_sinst, sinst) && upload(&B.d_small, tab.small) && upload(&B.d_sums, tab.sums) &&
-         upload(&B.d_tail, tab.tail) && upload(&B.d_units, tab.units);
+    B.passes[k].d_table = reinterpret_cast<TileEntry*>(B.d_block + o_tiles[k]);
+  B.d_items = reinterpret_cast<BItem*>(B.d_block + o_items);
+  B.d_nitems = reinterpret_cast<int*>(B.d_block + o_nitems);
+  return LRE_OK;
 }
 
 // Workgroups of the staged form's launches.
@@ -1002,22 +1041,10 @@ lre_status fill_plan(lre_batch& B, const lre_instance* inst, int count) {
   StagedTables tab;
   plan_staged(B, lv, off, sinst, tab);
   B.ws_bytes = off;
-  if (hipMalloc(&B.d_inst, count * sizeof(BInst)) != hipSuccess ||
-      hipMemcpy(B.d_inst, B.dinst_host.data(), count * sizeof(BInst), hipMemcpyHostToDevice) != hipSuccess)
-    return LRE_E_HIP;
-  // The smallest shape (one row group, kBT columns, one row pattern per item) gives
-  // the longest list; the list is allocated once at that length.
-  const size_t cap = list_items(B, lre_batch_tiles{1, 1, kBT, 1, 0, 0}).size();
-  if (cap > (size_t)INT32_MAX) return LRE_E_UNSUPPORTED;
-  if (hipMalloc(&B.d_items, std::max<size_t>(cap, 1) * sizeof(BItem)) != hipSuccess ||
-      hipMalloc(&B.d_nitems, 256) != hipSuccess)
-    return LRE_E_HIP;
-  B.items_cap = cap;
-  if (!upload_staged(B, sinst, tab)) return LRE_E_HIP;
-  B.tiles = lre_batch_tiles{1, 4, kBT * 16, 1, 0, 0};   // the unstaged list's first shape
-  const lre_status s = rebuild(B);
+  B.items_cap = longest_list(B);
+  if (B.items_cap > (size_t)INT32_MAX) return LRE_E_UNSUPPORTED;
   B.tiles = lre_batch_tiles{1, 16, kBT * 16, 1, 0, 1};
-  return s;
+  return upload_plan(B, sinst, tab);
 }
 
 }  // namespace
@@ -1170,14 +1197,7 @@ void lre_batch_destroy(lre_batch* plan) {
   if (!plan) return;
   {
     DeviceGuard g(plan->ctx->device);
-    if (plan->d_items) (void)hipFree(plan->d_items);
-    if (plan->d_nitems) (void)hipFree(plan->d_nitems);
-    if (plan->d_inst) (void)hipFree(plan->d_inst);
-    for (TilePass& p : plan->passes)
-      if (p.d_table) (void)hipFree(p.d_table);
-    void* const tables[] = {plan->d_sinst, plan->d_small, plan->d_sums, plan->d_tail, plan->d_units};
-    for (void* p : tables)
-      if (p) (void)hipFree(p);
+    if (plan->d_block) (void)hipFree(plan->d_block);
   }
   delete plan;
 }
