@@ -23,8 +23,10 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <numeric>
+#include <utility>
 #include <vector>
 
 #include "lre.h"
@@ -900,12 +902,11 @@ size_t longest_list(const lre_batch& B) {
 // the work list and its length, which lre_batch_set_tiles fills.
 lre_status upload_plan(lre_batch& B, const std::vector<StagedInst>& sinst, const StagedTables& tab) {
   size_t off = 0;
-  std::vector<char> host;
+  std::vector<std::pair<const void*, size_t>> parts;          // of the copy, each 256-byte aligned
   auto put = [&](const auto& v) {
     const size_t at = off, bytes = v.size() * sizeof v[0];
+    parts.emplace_back(v.data(), bytes);
     off += align256(bytes);
-    host.resize(off);
-    if (bytes) std::memcpy(host.data() + at, v.data(), bytes);
     return at;
   };
   const size_t o_inst = put(B.dinst_host), o_sinst = put(sinst), o_small = put(tab.small), o_sums = put(tab.sums),
@@ -913,11 +914,17 @@ lre_status upload_plan(lre_batch& B, const std::vector<StagedInst>& sinst, const
   std::vector<size_t> o_tiles;
   for (const auto& t : tab.tiles) o_tiles.push_back(put(t));
   const size_t o_items = off, o_nitems = o_items + align256(B.items_cap * sizeof(BItem));
+  const std::unique_ptr<char[]> host(new char[o_items]);
+  size_t at = 0;
+  for (const auto& p : parts) {
+    if (p.second) std::memcpy(host.get() + at, p.first, p.second);
+    at += align256(p.second);
+  }
   if (hipMalloc(&B.d_block, o_nitems + 256) != hipSuccess) {
     B.d_block = nullptr;
     return LRE_E_HIP;
   }
-  if (hipMemcpy(B.d_block, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return LRE_E_HIP;
+  if (hipMemcpy(B.d_block, host.get(), o_items, hipMemcpyHostToDevice) != hipSuccess) return LRE_E_HIP;
   B.d_inst = reinterpret_cast<BInst*>(B.d_block + o_inst);
   B.d_sinst = reinterpret_cast<StagedInst*>(B.d_block + o_sinst);
   B.d_small = reinterpret_cast<int32_t*>(B.d_block + o_small);
