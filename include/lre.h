@@ -8,7 +8,7 @@
  *             coefficients Theta = (X^T X)^{-1} sum_j p_j Gamma^(j), where every
  *             Gamma^(j) has 2^n nonzero entries and X^T X = (x)_k diag{3,1,1,1};
  *   step (ii) Sec. II eq. (4): mu = sum_i theta_i Omega_i with Omega_i of eq. (5).
- * Step (iii) (projection onto physical states) is not part of this library.
+ * Step (iii) (projection onto physical states) is a call of its own, lre_project.
  *
  * Data layout (all device memory, row-major, caller-owned):
  *   counts : uint16 [3^n][2^n].  Row b is one measurement setting,
@@ -26,7 +26,7 @@
  * Conventions common to every entry point:
  *   - Calls enqueue work on `stream` (a hipStream_t; NULL = default stream) and return
  *     without synchronising.  No entry point allocates device memory except
- *     lre_create (a 64-byte flag word) and lre_batch_plan (the work list);
+ *     lre_create (a 64-byte flag word) and lre_batch_plan (the plan's tables);
  *     lre_project's solver libraries allocate their own scratch.
  *   - Host-checkable problems (bad n, NULL or misaligned pointers, workspace too
  *     small) return an error before anything is launched.
@@ -72,7 +72,8 @@ typedef enum {
 typedef struct lre_ctx lre_ctx;
 
 /* Create a context on HIP device `hip_device`: allocates the 64-byte device flag
- * word and its 64-byte mirror in pinned host memory.  *out receives the context.  Errors: LRE_E_ARG (out == NULL), LRE_E_HIP. */
+ * word and its 64-byte mirror in pinned host memory.  *out receives the context.
+ * Errors: LRE_E_ARG (out == NULL), LRE_E_HIP. */
 lre_status lre_create(lre_ctx** out, int hip_device);
 
 /* Destroy a context created by lre_create (NULL is ignored). */
@@ -129,7 +130,8 @@ lre_status lre_estimate_noalloc(lre_ctx* ctx, int n, const uint16_t* counts, uin
                                 void* stream);
 
 /* Synchronise `stream`, read and clear the context's device flag word.  Returns
- * LRE_E_SHOTS, LRE_E_EMPTY_BASIS, LRE_E_TIMEOUT, LRE_E_HIP or LRE_OK. */
+ * LRE_E_TIMEOUT, LRE_E_EIG, LRE_E_ARG, LRE_E_EMPTY_BASIS or LRE_E_SHOTS (the first that was
+ * raised), LRE_E_HIP (the flags are kept for the next check) or LRE_OK. */
 lre_status lre_check(lre_ctx* ctx, void* stream);
 
 /* Profiling hook.  events: `count` (<= 4) caller-created hipEvent_t handles, or NULL to
@@ -165,9 +167,12 @@ lre_status lre_signed_sums(lre_ctx* ctx, int n, const uint16_t* counts, const in
 
 /* ---------------------------------------------------------------------------------
  * Batched estimation: many independent instances (each its own n, counts and shots)
- * in one launch of a persistent kernel.  Every instance gets exactly what
- * lre_estimate returns for it (steps (i) and (ii), Sec. II eqs. 3-4): the same
- * kernels' arithmetic, bit-identical coefficients and rho.
+ * in a few launches.  Every instance gets what lre_estimate returns for it (steps (i) and
+ * (ii), Sec. II eqs. 3-4).  With uniform shots that is the same to the bit, coefficients and
+ * rho.  With per-basis totals the binary64 sums are the same terms added in another order:
+ * staged, a fixed one that depends on the other instances of the plan too (how many qubits
+ * the counts passes fold first); unstaged, by LDS atomics, which two runs may order
+ * differently.  Equal to rounding, below 1e-13 for coefficients.
  *
  * A plan runs in one of two forms (lre_batch_tiles.staged).  Staged (a new plan's form): one
  * launch per stage over all instances -- row sums, counts passes over a table of tiles,
@@ -221,12 +226,13 @@ typedef struct lre_batch lre_batch;
 
 /* Plan a batch of `count` instances (count >= 1).  flags: LRE_NO_RHO | LRE_RHO_FP32
  * (applied to every instance).  The instance array is copied; the buffers it points
- * to must stay valid while the plan is used.  Allocates the device work list and the staged
- * form's tables (once: lre_batch_set_tiles and lre_batch_tune reuse them).
+ * to must stay valid while the plan is used.  One device allocation holds the instances, the
+ * staged form's tables and room for the work list (lre_batch_set_tiles and lre_batch_tune
+ * reuse it).
  * Unstaged, a plan with a per-basis instance (shots == 0) runs one workgroup per compute unit
  * (its binary64 accumulators fill the LDS), whatever workers_per_cu says.
  * Errors: LRE_E_ARG (bad instance: n < 1, pointer, alignment, shots too large),
- * LRE_E_UNSUPPORTED (n > LRE_BATCH_MAX_QUBITS), LRE_E_HIP. */
+ * LRE_E_UNSUPPORTED (n > LRE_BATCH_MAX_QUBITS), LRE_E_HIP (also where host memory runs out). */
 lre_status lre_batch_plan(lre_ctx* ctx, const lre_instance* inst, int count, uint32_t flags,
                           lre_batch** plan_out);
 
@@ -295,9 +301,10 @@ typedef struct lre_stream lre_stream;
 lre_status lre_stream_create(lre_ctx* ctx, int n, int h, uint64_t shots, uint32_t flags, lre_stream** out);
 
 /* Device workspace bytes every call of the stream object needs (256-byte aligned,
- * caller-owned, one buffer for all calls): one segment's pass buffers, the 2^h segment
- * sums, their row-sum parts, the staging slab with LRE_STREAM_HOST, and step (ii)'s
- * intermediate (16 * 4^n bytes, aliased onto the rest).  0 for NULL. */
+ * caller-owned, one buffer for all calls): the pass buffers of the segments that run side by
+ * side (1 to 2^h, as many as keep their partial sums within 4 GiB; one with LRE_WHT_MFMA),
+ * the 2^h segment sums, their row-sum parts, the staging slab with LRE_STREAM_HOST, and step
+ * (ii)'s intermediate (16 * 4^n bytes, aliased onto the rest).  0 for NULL. */
 size_t lre_stream_workspace_bytes(const lre_stream* s);
 
 /* Start an estimate: coef (device double [4^n], 8-byte aligned) becomes the accumulator
@@ -365,9 +372,11 @@ lre_status lre_povm_estimate(lre_ctx* ctx, int n, const uint16_t* counts, const 
  *   eigvals   : device double [2^n] out, the eigenvalues of mu in ascending order, or
  *               NULL.
  *   workspace : at least lre_project_workspace_bytes(n) bytes, 256-byte aligned.
- * Enqueued on `stream` (eigensolver and product from rocSOLVER / rocBLAS, which may
- * allocate their own scratch).  A solver failure raises LRE_E_EIG through lre_check
- * (rho is then 0). */
+ * Enqueued on `stream`: up to 6 qubits one kernel; beyond, the tridiagonal (7, 8 qubits) or the
+ * whole eigenproblem and the product are rocSOLVER's / rocBLAS's, which may allocate their
+ * own scratch.  A solver failure, which input or a result that is not finite is too, raises
+ * LRE_E_EIG through lre_check (rho is then 0).  Up to 8 qubits repeated calls give the same
+ * bits. */
 size_t lre_project_workspace_bytes(int n);
 lre_status lre_project(lre_ctx* ctx, int n, const void* mu, void* rho, double* eigvals, void* workspace,
                        size_t workspace_bytes, void* stream);

@@ -491,7 +491,7 @@ void launch_tail_rho(const FoldArgs& a, void* rho, bool fp32) {
 // The last pass and step (ii) of n = 6 .. 8 qubits in one launch or two: a unit of 8 qubits reads up to
 // 216 partials a thread, which takes 7.6 us from integers (two launches: 4.0 + 4.0 and a
 // gap, 12.1 -> 11.1 us a call) but 11.8 from binary64 (13.1 -> 17.4 a call); up to 7 qubits
-// at most 36 (n = 7 12.1 -> 8.3 us a call, binary64 12.3 -> 9.2).
+// at most 36 (n = 7 12.1 -> 8.9 us a call, binary64 12.3 -> 9.9).
 bool fuses_rho(const Plan& P) {
   return !P.mfma && P.q1 == 5 && (P.n <= 7 || (P.n == 8 && P.t1 == Ty::U32));
 }

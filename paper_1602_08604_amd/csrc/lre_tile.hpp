@@ -817,7 +817,7 @@ __global__ __launch_bounds__(FoldTailGeom<F>::THREADS) void fold_tail_kernel(
 // z bits t >> 6 of qubits 3..5 (one wave), all 2^H z patterns of the qubits above, whose x
 // pattern X says which of their 6 inputs matter: all for I and Z, those of X and Y otherwise.
 // Bound by the loads' latency, once per letter of qubit 5 (the sched_barrier keeps a letter's
-// loads together: n = 7 9.2 -> 8.3 us a call); n = 7 4.9 us where the two launches took 3.8 + 3.3
+// loads together: 0.9 us of a call of 7 qubits); n = 7 4.9 us where the two launches took 3.8 + 3.3
 // and the gap between them, n = 8 (integers) 7.6 against 4.0 + 4.0.
 template <int H, int X, typename Tin, typename Acc>
 __device__ __forceinline__ void tail_unit_fold(const Tin* __restrict__ p, int letter5, Acc (&out)[1 << H]) {

@@ -399,7 +399,7 @@ def set_stage_events(events, device=None):
 
 
 class Batch:
-    """lre_batch_*: many instances (n <= 9) in one persistent launch.
+    """lre_batch_*: many instances (n <= 9) in a few launches.
 
     counts: list of uint16 device tensors [3^n, 2^n]; shots: list of ints (0 = per-basis
     totals, then n_per_basis[j] is a 32-bit device tensor [3^n] or None for the row
