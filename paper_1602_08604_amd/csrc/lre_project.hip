@@ -507,10 +507,9 @@ __global__ __launch_bounds__(kHetrdThreads) void hetrd_kernel(double2* __restric
     if (lane == 0) red[wave][0] = s;
     if (lane == 32) red[wave][1] = s;
     __syncthreads();
-    double2 t = make_double2(0.0, 0.0);
-    for (int k = 0; k < WAVES; ++k) { t.x += red[k][0]; t.y += red[k][1]; }
-    return t;
+    return make_double2(row_sum16(red[lane & 15][0]), row_sum16(red[lane & 15][1]));
   };
+  static_assert(WAVES == 16, "a row of lanes takes the waves' sums");
   // Largest m of the block (m >= 0), in every thread.
   auto block_max = [&](double m) {
 #pragma unroll
