@@ -267,7 +267,7 @@ __global__ __launch_bounds__(PovmTileGeom<J>::TH) void povm_tile_kernel(const ui
 // blockIdx.x, + gridDim.x, ...  A thread loads 16 rows of one column straight into the first
 // two digits' registers (the block's next tile is loaded ahead), the next two digits pass
 // through LDS and the fifth, divided by N, stores to coef.  Bound by memory: n = 12, one
-// pass of 47 us, 5.7 TB/s, where passes of 4 and 2 digits took 43 + 45.
+// pass of 49 us, 5.5 TB/s, where passes of 4 and 2 digits took 43 + 45.
 constexpr int kPovmWideCols = 16;
 
 // Rows of one half-wave's access differ in one digit bit: it picks the half of the banks.

@@ -54,8 +54,8 @@ ProjLayout proj_layout(int n) {
 }
 
 constexpr int kJacobiN = 6;   // mu and its eigenvectors (2 x 64 KiB) fit the LDS
-// One CU against a launch per column and step, whole calls: n = 7 1.55 ms (library 3.07),
-// n = 8 3.66 (7.35); its time grows by 8 a qubit, the library's by 2 (n = 9: 13.9 ms).
+// One CU against a launch per column and step, whole calls: n = 7 1.53 ms (library 3.05),
+// n = 8 3.69 (7.45); its time grows by 8 a qubit, the library's by 2 (n = 9: 13.8 ms).
 constexpr int kHetrdN = 8;
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
@@ -148,10 +148,11 @@ __global__ __launch_bounds__(kSpectrumThreads) void spectrum_kernel(double* __re
 // thread (i, j) applies those of pairs i and j to its own 2 x 2 block of mu, and every column
 // pair of the eigenvectors is rotated; two barriers a round, d - 1 rounds a sweep, until a
 // sweep finds no element above 1e-17 of mu's norm (7 to 10 sweeps).  The lower triangle of mu
-// is read (before rho is written: the two may be one buffer).  Then the spectrum step and rho = V diag(lambda) V^H, its lower triangle computed
-// and mirrored.  Bound by the rounds' latency (two barriers, a square root and two divisions,
-// LDS): n = 1 .. 6 take 21, 32, 58, 129, 320, 1067 us whole calls; the library's solver and
-// the launches around it took 126, 144, 242, 592, 990, 1936.
+// is read (before rho is written: the two may be one buffer).  Then the spectrum step and
+// rho = V diag(lambda) V^H, its lower triangle computed and mirrored.  Sums are in a fixed order.
+// Bound by the rounds' latency (two barriers, a square root and two divisions, LDS): n = 1 .. 6
+// take 25, 33, 61, 129, 310, 1110 us whole calls; the library's solver and the launches around it
+// took 126, 141, 247, 607, 987, 1952.
 constexpr int kJacobiSweeps = 40;
 
 template <int N>
@@ -483,10 +484,11 @@ __global__ __launch_bounds__(256) void lower_copy_kernel(const double2* __restri
 // over the trailing lower triangle then applies the update to it and forms A v: a wave takes
 // two columns at a time, lanes along the rows, so that each element is read and written once
 // and serves both its column's dot product and its row's sum.  One pass and five barriers a
-// step, all within one CU, against five launches a step in the library.  Bound by the one CU:
-// per step some 4.4k cycles of binary64 arithmetic, 5k of L2 traffic and the barriers' serial
-// parts: 2.09 ms at n = 8 (8 us a step; the library: 28).  512 threads with the next columns
-// loaded ahead: 2.72 ms.
+// step, all within one CU, against five launches a step in the library.  Every sum is taken in a
+// fixed order (each wave's row sums of A v in LDS of their own, 64 KiB at n = 8).  Bound by the one
+// CU: per step some 4.4k cycles of binary64 arithmetic, 5k of L2 traffic and the barriers'
+// serial parts: 2.10 ms at n = 8 (8 us a step; the library: 28), 0.54 at n = 7.  512 threads with
+// the next columns loaded ahead: 2.72 ms.
 constexpr int kHetrdThreads = 1024;
 
 template <int D>
