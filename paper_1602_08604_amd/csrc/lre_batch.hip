@@ -817,6 +817,23 @@ void plan_staged(lre_batch& B, int lv, size_t& off, std::vector<StagedInst>& sin
   std::vector<int> order(count);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B.meta[a].counts > B.meta[b].counts; });
+  // Sizes first: growing the tables took 20 of the 190 us of a plan for 40 instances.
+  size_t ntiles[2][2] = {{0, 0}, {0, 0}}, nsums = 0, ntail = 0, nunits = 0;   // [level - 1][per-basis]
+  auto sum_blocks = [](int n) { return (ipow3(n) + sums_per_block(n) - 1) / sums_per_block(n); };
+  auto fold_blocks = [](int q, int h) { return ipow4(q) / (h <= 2 ? 256 : FoldTailGeom<3>::COLS); };
+  auto check_blocks = [](int n) { return (ipow3(n) + 255) / 256; };
+  for (int j = 0; j < count; ++j) {
+    const InstMeta& m = B.meta[j];
+    if (m.n <= kSmallN) continue;
+    const int q = staged_qubits(m.n, lv), h = m.n - q;
+    ntiles[q - 6][m.pb] += (size_t)(ipow3(h) << h);
+    if (m.pb && !B.dinst_host[j].nb_in) nsums += (size_t)sum_blocks(m.n);
+    ntail += (size_t)(fold_blocks(q, h) + check_blocks(m.n));
+    if (want_rho) nunits += (size_t)8 << (m.n - kJ);
+  }
+  tab.sums.reserve(nsums);
+  tab.tail.reserve(ntail);
+  tab.units.reserve(nunits);
   std::vector<int64_t> groups;
   auto pass_of = [&](int level, bool pb) {
     for (size_t k = 0; k < B.passes.size(); ++k)
@@ -826,6 +843,7 @@ void plan_staged(lre_batch& B, int lv, size_t& off, std::vector<StagedInst>& sin
     p.pb = pb;
     B.passes.push_back(p);
     tab.tiles.emplace_back();
+    tab.tiles.back().reserve(ntiles[level - 1][pb]);
     groups.push_back(0);
     return (int)B.passes.size() - 1;
   };
@@ -859,15 +877,14 @@ void plan_staged(lre_batch& B, int lv, size_t& off, std::vector<StagedInst>& sin
     groups[k] += row_groups;
     p.tiles = (int)tab.tiles[k].size();
     if (m.pb && !d.nb_in)
-      for (int64_t b = 0; b * sums_per_block(m.n) < ipow3(m.n); ++b) tab.sums.push_back(make_int2(j, (int)b));
-    const int64_t fold_blocks = ipow4(q) / (h <= 2 ? 256 : FoldTailGeom<3>::COLS);
-    for (int64_t b = 0; b < fold_blocks; ++b) tab.tail.push_back(make_int2(j, (int)b));
+      for (int64_t b = 0, nb = sum_blocks(m.n); b < nb; ++b) tab.sums.push_back(make_int2(j, (int)b));
+    for (int64_t b = 0, nb = fold_blocks(q, h); b < nb; ++b) tab.tail.push_back(make_int2(j, (int)b));
     if (want_rho)
       for (int u = 0; u < (8 << (m.n - kJ)); ++u) tab.units.push_back(make_int2(j, u));
   }
   for (int j : order)
     if (B.meta[j].n > kSmallN)
-      for (int64_t b = 0; b * 256 < ipow3(B.meta[j].n); ++b) tab.tail.push_back(make_int2(j, (int)(-1 - b)));
+      for (int64_t b = 0, nb = check_blocks(B.meta[j].n); b < nb; ++b) tab.tail.push_back(make_int2(j, (int)(-1 - b)));
   for (size_t k = 0; k < B.passes.size(); ++k) {
     TilePass& p = B.passes[k];
     p.off_rowpart = (int64_t)off;
